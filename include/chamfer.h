@@ -64,8 +64,8 @@ enum chamfer_status {
 };
 
 enum chamfer_precision {
-    CHAMFER_FP32 = 0,  /* exact canonical float32 arg-mins (l2: certified    *
-                        * candidates from bf16-split MFMA tiles)             */
+    CHAMFER_FP32 = 0,  /* exact canonical float32 arg-mins (l2: rows ruled   *
+                        * out by bounded FP16 MFMA scores)                   */
     CHAMFER_BF16 = 1,  /* l2 distance tiles on bf16 MFMA + float32 re-rank    */
     CHAMFER_FP8 = 2    /* l2 distance tiles on fp8-e4m3 MFMA + float32 re-rank*/
 };
@@ -119,11 +119,10 @@ typedef struct chamfer_aux {
      * 1 calibration and tables done, 2 B bucketed, 3 CrudeNN done (D_a),
      * 4 weights and draws done, 5 exact pass over the draws done, 6 end.
      * Stage 4->5 is the nearest-neighbour pass over the draws: for l2 with
-     * 12 <= d <= 256 the BF16 split table of the draws, the matrix-core
-     * record kernel, the per-draw resolve kernel and, when B's chunks are
-     * longer than 512 rows, the rescan kernel (B's split table is written
-     * in stage 1->2 by the kernel that hashes B, or in stage 4->5 for the
-     * uniform-sampling baseline); otherwise one vector-ALU kernel. */
+     * d <= 10 one matrix-core kernel, with 12 <= d <= 256 the FP16 table of
+     * the draws and that kernel (B's table is written in stage 1->2 by the
+     * kernel that hashes B, or in stage 4->5 for the uniform-sampling
+     * baseline); otherwise one vector-ALU kernel. */
     void **stage_events;
 } chamfer_aux;
 
@@ -455,15 +454,21 @@ int32_t chamfer_default_scales(int64_t n_A, int64_t n_B, double eps); /* L defau
  * coordinates. */
 int chamfer_embedding_matrix(uint64_t seed, int32_t d, int32_t embed_dim, int8_t *Z_host);
 const char *chamfer_strerror(int status);
-/* The bound E of the l2 exact pass's certificate (the exact pass of
- * chamfer_exact, chamfer_nn_min and chamfer_estimate for l2 with
- * 12 <= d <= 256, FP32 precision): for a query x with float32 |x|^2 = xn2
- * and rows b with float32 |b|^2 <= b2max, the matrix-core score of every b
- * is within E of |b|^2 - 2 x.b, assuming the matrix cores add each product
- * to their float32 accumulator with one rounding to nearest.  terms = 3
- * (the estimator's draws, batches below 16384 queries) or 4 (larger
- * batches).  Returns -1 for d outside 1..256 or other terms. */
+/* The bound E of a score from products of two-term BF16 splits: for a query
+ * x with float32 |x|^2 = xn2 and rows b with float32 |b|^2 <= b2max, the sum
+ * of terms = 3 (hh, mh, hm) or 4 products per coordinate is within E of
+ * |b|^2 - 2 x.b, assuming that each product is added to a float32 accumulator
+ * with one rounding to nearest.  Returns -1 for d outside 1..256 or other
+ * terms. */
 double chamfer_split_score_bound(int32_t d, int32_t terms, float xn2, float b2max);
+/* The bound of the l2 exact pass (chamfer_exact, chamfer_nn_min and
+ * chamfer_estimate for l2 with d <= 10 or 12 <= d <= 256, FP32 precision): its
+ * score v of a query z against rows y, both centred, scaled and held as FP16
+ * values z~, y~ (d <= 10: as sums of two), is within this of z.y - |y|^2 / 2
+ * for zt >= |z~|, ze >= |z - z~|, by >= |y|, be >= |y - y~|, assuming that each
+ * exact product is added to the float32 accumulator with an error of at most
+ * 2^-23 of the sum.  Returns -1 for other d. */
+double chamfer_half_score_bound(int32_t d, double zt, double ze, double by, double be);
 
 #ifdef __cplusplus
 }

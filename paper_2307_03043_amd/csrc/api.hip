@@ -186,19 +186,25 @@ int make_plan(Plan &pl, int64_t nA, int64_t nB, int32_t d, int32_t metric, doubl
     pl.off_P = take(e_ * nA * sizeof(uint64_t));
     pl.off_idx = take(e_ * pl.T * sizeof(int32_t));
     pl.off_best = take((size_t)nrow * sizeof(uint64_t));
+    // thresholds of the l2 exact pass: the draws' live in the hash tables'
+    // region (done with by then), in copies where they fit; otherwise one copy
+    // right after best, so that one fill resets both
+    const size_t gb = !lowp_supported(d, metric, o.precision) && half_supported(d, metric)
+                          ? (size_t)(estimating ? pl.T : nA) * sizeof(uint32_t)
+                          : 0;
+    const size_t room = h ? table_bytes(pl.L, lc, pl.window) : 0;
+    pl.thr_copies = gb == 0 ? 0 : half_copies(pl.T, nB);
+    if (pl.thr_copies * gb > room) pl.thr_copies = 1;
+    pl.off_gthr = gb <= room ? pl.off_tables : take(gb);
     pl.off_partial = take((size_t)(nn_finalize_blocks(nrow) + 1) * sizeof(double));
-    pl.off_nb2 = take(mfma_supported(d, metric) ? (size_t)nB * sizeof(float) : 0);
-    // low precision: cast rows of B and of the queries, scales and norms
+    // low precision: cast rows of B and of the queries, scales and norms;
+    // float32 l2 with 12 <= d <= 256: the FP16 tables of B and of the queries
     const bool lp = lowp_supported(d, metric, pl.precision);
-    const bool split = !lp && mfma_supported(d, metric);
-    pl.off_bsplit = take(split ? split_table_bytes(nB, d) : 0);
-    pl.off_xsplit = take(split ? split_table_bytes(nrow, d) : 0);
-    pl.off_xn2 = take(split ? (size_t)nrow * sizeof(float) : 0);
-    // the deferred exact pass over the draws: its (draw, chunk) records live
-    // in the hash tables' region when that is large enough (the tables are
-    // done with before the draws are taken)
-    const size_t srec = split && estimating ? split_record_bytes(pl.T, nB, d) : 0;
-    pl.off_srec = h && srec <= table_bytes(pl.L, lc, pl.window) ? pl.off_tables : take(srec);
+    const bool half = !lp && half_supported(d, metric) && half_tabled(d);
+    pl.off_nbh = take(half ? (size_t)nB * sizeof(float) : 0);
+    pl.off_bhalf = take(half ? half_table_bytes(nB, d) : 0);
+    pl.off_xhalf = take(half ? half_table_bytes(nrow, d) : 0);
+    pl.off_xstat = take(half ? (size_t)nrow * sizeof(float4) : 0);
     const size_t rb = lp ? lowp_row_bytes(d, pl.precision) : 0;
     pl.off_bq = take(rb * (size_t)nB);
     pl.off_xq = take(rb * (size_t)nrow);
@@ -257,8 +263,17 @@ int hash_prologue(const Plan &pl, const float *A, const float *B, uint64_t seed,
                               hipMemcpyHostToDevice, st));
     }
     CH_TRY(launch_minmax_pair(A, pl.nA, B, pl.nB, pl.d, lohi, p, st));
-    CH_TRY(launch_calib_final(lohi, pl.d, p, st));
+    CH_TRY(launch_calib_final(lohi, pl.d, p, half_supported(pl.d, pl.metric) ? B : nullptr, pl.nB,
+                              true, st));
     return CHAMFER_OK;
+}
+
+// 64-bit words of best and the thresholds after it (entry points that lay
+// them out one after the other).
+int64_t reset_words(const Plan &pl) {
+    const size_t end = pl.thr_copies ? pl.off_gthr + align_up(pl.nA * sizeof(uint32_t))
+                                     : pl.off_best + (size_t)pl.nA * sizeof(uint64_t);
+    return (int64_t)((end - pl.off_best) / sizeof(uint64_t));
 }
 
 // Record stage event i if the caller asked for stage events.
@@ -267,19 +282,17 @@ hipError_t mark(void **ev, int i, hipStream_t st) {
     return hipEventRecord(static_cast<hipEvent_t>(ev[i]), st);
 }
 
-// CrudeNN into D/nn/scale.  nb2 (l2 only, may be null): |b|^2 per row of B,
-// computed while B is bucketed, for the nearest-neighbour pass.  With k LSH
-// structures (reps) the tables are rebuilt for each structure r (grid stream
-// word r) and each probe keeps the better of its candidate and the stored
-// one; with a window W the tables hold W points per bucket.
-// nb2 given: the hash of B also fills |b|^2 and p->b2max_rep (inputs of the
-// l2 exact pass).
+// CrudeNN into D/nn/scale.  With k LSH structures (reps) the tables are
+// rebuilt for each structure r (grid stream word r) and each probe keeps the
+// better of its candidate and the stored one; with a window W the tables hold
+// W points per bucket.  table_of_B: the hash of B also writes B's FP16 table
+// of the l2 exact pass (B is read once for both).
 int crude_core(const Plan &pl, const float *A, const float *B, uint64_t seed, float *D,
                int32_t *nn, int32_t *scale, void *ws, hipStream_t st, void **ev = nullptr,
-               float *nb2 = nullptr, uint16_t *bsplit = nullptr) {
-    // bsplit (l2 only, may be null): B's split table for the exact pass,
-    // written by the kernel that hashes B (B is read once for both)
-    const int sdp = bsplit ? split_dpad(pl.d) : 0;
+               bool table_of_B = false) {
+    float *nbh = table_of_B ? at<float>(ws, pl.off_nbh) : nullptr;
+    uint16_t *bhalf = table_of_B ? at<uint16_t>(ws, pl.off_bhalf) : nullptr;
+    const int hdp = bhalf ? (int)(half_table_bytes(1, pl.d) / 2) : 0;
     CH_TRY(mark(ev, 0, st));
     const int W = pl.window;
     int rc = hash_prologue(pl, A, B, seed, ws, st);
@@ -300,16 +313,16 @@ int crude_core(const Plan &pl, const float *A, const float *B, uint64_t seed, fl
             if (r == 0) CH_TRY(mark(ev, 1, st));
             CH_TRY(launch_hash(5, B, pl.nB, B, pl.nB, pl.d, pl.metric, pl.L, pl.ke, lohi, emb, zf,
                                mt, nullptr, pl.log2cap, pw.keys, nullptr, nullptr, nullptr,
-                               r == 0 ? nb2 : nullptr, p, 1, 0, st, r == 0 ? bsplit : nullptr,
-                               sdp));
+                               r == 0 ? nbh : nullptr, p, 1, 0, st, r == 0 ? bhalf : nullptr,
+                               hdp));
             CH_TRY(launch_part_build(pw, pl.nB, pl.L, pl.log2cap, tables, st));
         } else {
             CH_TRY(launch_tables_empty(tables, pl.L, pl.log2cap, W, st));
             if (r == 0) CH_TRY(mark(ev, 1, st));
             CH_TRY(launch_hash(W == 1 ? 0 : 3, B, pl.nB, B, pl.nB, pl.d, pl.metric, pl.L, pl.ke,
                                lohi, emb, zf, mt, tables, pl.log2cap, nullptr, nullptr, nullptr,
-                               nullptr, r == 0 ? nb2 : nullptr, p, W, 0, st,
-                               r == 0 ? bsplit : nullptr, sdp));
+                               nullptr, r == 0 ? nbh : nullptr, p, W, 0, st,
+                               r == 0 ? bhalf : nullptr, hdp));
         }
         if (r == 0) CH_TRY(mark(ev, 2, st));
         const int flags = (r > 0 ? kProbeMerge : 0) | (r == pl.reps - 1 ? kProbeLast : 0);
@@ -322,14 +335,14 @@ int crude_core(const Plan &pl, const float *A, const float *B, uint64_t seed, fl
 }
 
 // Exact pass over queries (rows of X, or X[rows[q]]): the low-precision
-// form when requested and supported, else the float32 result (split-BF16
-// matrix cores for l2 when nb2 is given, vector ALU otherwise).  split_ready:
-// the split tables of B and of the queries are already in the workspace.
-// draws: X rows are the estimator's draws (the deferred split pass may use
-// its record region).
+// form when requested and supported, else the float32 result (FP16 matrix
+// cores and canonical distances for l2 where half_supported, after the
+// calibration with B; vector ALU otherwise).  B_ready: B's FP16 table is
+// already in the workspace.  seed (may be null): seed[row of X] bounds the
+// distance of the query from above.
 int nn_pass(const Plan &pl, void *ws, const float *X, const int32_t *rows, int64_t nx,
-            const float *B, int64_t nB, unsigned long long *best, float *nb2, DevParams *p,
-            hipStream_t st, bool split_ready = false, bool draws = false) {
+            const float *B, int64_t nB, unsigned long long *best, DevParams *p, hipStream_t st,
+            bool B_ready = false, const float *seed = nullptr) {
     if (lowp_supported(pl.d, pl.metric, pl.precision)) {
         uint8_t *bq = at<uint8_t>(ws, pl.off_bq);
         uint8_t *xq = at<uint8_t>(ws, pl.off_xq);
@@ -341,17 +354,21 @@ int nn_pass(const Plan &pl, void *ws, const float *X, const int32_t *rows, int64
                                  best, p, st));
         return CHAMFER_OK;
     }
-    if (nb2 != nullptr && mfma_supported(pl.d, pl.metric)) {
-        uint16_t *bs = at<uint16_t>(ws, pl.off_bsplit);
-        uint16_t *xs = at<uint16_t>(ws, pl.off_xsplit);
-        float *xn2 = at<float>(ws, pl.off_xn2);
-        if (!split_ready) {
-            CH_TRY(launch_split_rows(B, nB, pl.d, bs, p, st));
-            CH_TRY(launch_split_queries(X, rows, nx, pl.d, xs, xn2, p, st));
+    if (half_supported(pl.d, pl.metric)) {
+        const uint32_t *lohi = at<uint32_t>(ws, pl.off_lohi);
+        uint16_t *bs = nullptr, *xs = nullptr;
+        float *nbh = nullptr;
+        float4 *stat = nullptr;
+        if (half_tabled(pl.d)) {
+            bs = at<uint16_t>(ws, pl.off_bhalf);
+            xs = at<uint16_t>(ws, pl.off_xhalf);
+            nbh = at<float>(ws, pl.off_nbh);
+            stat = at<float4>(ws, pl.off_xstat);
+            CH_TRY(launch_half_rows(B_ready ? nullptr : B, nB, bs, nbh, X, rows, nx, xs, stat, pl.d,
+                                    lohi, p, st));
         }
-        uint4 *rec = draws && split_record_bytes(nx, nB, pl.d) ? at<uint4>(ws, pl.off_srec)
-                                                               : nullptr;
-        CH_TRY(launch_nnmin_split(X, rows, nx, xs, xn2, B, bs, nB, pl.d, best, nb2, p, st, rec));
+        CH_TRY(launch_nnmin_half(X, rows, nx, xs, stat, seed, B, bs, nB, pl.d, nbh, lohi, best,
+                                 at<uint32_t>(ws, pl.off_gthr), pl.thr_copies, p, st));
         return CHAMFER_OK;
     }
     CH_TRY(launch_nnmin(X, rows, nx, B, nB, pl.d, pl.metric, best, p, st));
@@ -419,12 +436,17 @@ int job_prepare(const float *A, const float *B, int64_t nA, int64_t nB, int32_t 
     J.P = at<unsigned long long>(ws, pl.off_P);
     J.idx = at<int32_t>(ws, pl.off_idx);
     J.best = at<unsigned long long>(ws, pl.off_best);
-    J.nb2 = mfma_supported(d, metric) ? at<float>(ws, pl.off_nb2) : nullptr;
-    // low precision: the cast rows of B; float32 l2: the split table of B
-    J.bq = lp ? at<uint8_t>(ws, pl.off_bq)
-              : mfma_supported(d, metric) ? at<uint8_t>(ws, pl.off_bsplit) : nullptr;
+    const bool half = !lp && half_supported(d, metric);
+    const bool tabled = half && half_tabled(d);
+    J.bq = lp ? at<uint8_t>(ws, pl.off_bq) : nullptr;
     J.xq = lp ? at<uint8_t>(ws, pl.off_xq) : nullptr;
     J.lpf = lp ? at<float>(ws, pl.off_lpf) : nullptr;
+    J.bhalf = tabled ? at<uint16_t>(ws, pl.off_bhalf) : nullptr;
+    J.xhalf = tabled ? at<uint16_t>(ws, pl.off_xhalf) : nullptr;
+    J.nbh = tabled ? at<float>(ws, pl.off_nbh) : nullptr;
+    J.xstat = tabled ? at<float4>(ws, pl.off_xstat) : nullptr;
+    J.gthr = half ? at<uint32_t>(ws, pl.off_gthr) : nullptr;
+    J.thr_copies = pl.thr_copies;
     J.eta = eta;
     J.aux = aux;
     J.aux.stage_events = nullptr;
@@ -432,12 +454,11 @@ int job_prepare(const float *A, const float *B, int64_t nA, int64_t nB, int32_t 
     J.nb_init = (int32_t)init_blocks(d);
     J.nb_grid = (int32_t)grid_table_blocks(pl.L, pl.kh);
     J.nb_fill = (int32_t)table_fill_blocks((size_t)J.table_count);
-    J.mm_vec4 = minmax_vec4(A, d) && minmax_vec4(B, d);
     int64_t blocks, stride;
-    minmax_geom(nA, d, J.mm_vec4 != 0, &blocks, &stride);
+    minmax_geom(nA, d, true, &blocks, &stride);
     J.nb_mmA = (int32_t)blocks;
     J.mm_strideA = stride;
-    minmax_geom(nB, d, J.mm_vec4 != 0, &blocks, &stride);
+    minmax_geom(nB, d, true, &blocks, &stride);
     J.nb_mmB = (int32_t)blocks;
     J.mm_strideB = stride;
     J.nb_hashB = (int32_t)hash_blocks(nB);
@@ -449,12 +470,12 @@ int job_prepare(const float *A, const float *B, int64_t nA, int64_t nB, int32_t 
         J.nb_castB = (int32_t)cast_blocks(nB);
         J.nb_castX = (int32_t)cast_blocks(pl.T);
         g = lowp_geom(pl.T, nB, d, pl.precision);
-    } else if (mfma_supported(d, metric)) {
-        J.xsplit = at<uint16_t>(ws, pl.off_xsplit);
-        J.xn2 = at<float>(ws, pl.off_xn2);
-        J.nb_castB = (int32_t)split_blocks(nB, d);
-        J.nb_castX = (int32_t)split_blocks(pl.T, d);
-        g = split_geom(pl.T, nB, d);
+    } else if (half) {
+        if (tabled) {
+            J.nb_castB = (int32_t)half_row_blocks(nB, d, true);
+            J.nb_castX = (int32_t)half_row_blocks(pl.T, d, false);
+        }
+        g = half_geom(pl.T, nB, d);
     } else {
         g = valu_geom(pl.T, nB, d);
     }
@@ -484,15 +505,15 @@ void job_share_nn(Job *jobs, int n) {
     if (n <= 1) return;
     const Job &J0 = jobs[0];
     if (lowp_supported(J0.d, J0.metric, J0.precision)) return;
-    const bool mfma = mfma_supported(J0.d, J0.metric);
+    const bool half = half_supported(J0.d, J0.metric);
     double total = 0.0;
     for (int j = 0; j < n; ++j) total += (double)jobs[j].T * (double)jobs[j].nB;
-    const double target = mfma ? (double)split_target_wgs(J0.d) : (double)kValuTargetWGs;
+    const double target = half ? (double)half_target_wgs(J0.d) : (double)kValuTargetWGs;
     for (int j = 0; j < n; ++j) {
         Job &J = jobs[j];
         const double share = target * ((double)J.T * (double)J.nB) / total;
         const int64_t t = share < 1.0 ? 1 : (int64_t)std::ceil(share);
-        const NNGeom g = mfma ? split_geom(J.T, J.nB, J.d, t) : valu_geom(J.T, J.nB, J.d, t);
+        const NNGeom g = half ? half_geom(J.T, J.nB, J.d, t) : valu_geom(J.T, J.nB, J.d, t);
         J.nn_chunk = g.chunk;
         J.nn_nchunk = g.nchunk;
         J.nb_nn = (int32_t)g.blocks;
@@ -510,8 +531,8 @@ int launch_estimate_batch(const Batch *bt, int d, int metric, int ke, int precis
     CH_TRY(launch_batch_sample(bt, st));
     if (lowp_supported(d, metric, precision))
         CH_TRY(launch_batch_cast(bt, d, precision, st));
-    else if (mfma_supported(d, metric))
-        CH_TRY(launch_batch_split_rows(bt, st));
+    else if (half_supported(d, metric) && half_tabled(d))
+        CH_TRY(launch_batch_half_rows(bt, st));
     CH_TRY(launch_batch_nn(bt, d, metric, precision, st));
     CH_TRY(launch_batch_final(bt, metric, st));
     return CHAMFER_OK;
@@ -587,15 +608,9 @@ int chamfer_exact(const float *A, const float *B, int64_t n_A, int64_t n_B, int3
     double *partial = at<double>(ws, pl.off_partial);
     CH_TRY(launch_init_params(p, lohi, d, st));
     CH_TRY(launch_minmax_pair(A, n_A, B, n_B, d, lohi, p, st));
-    CH_TRY(launch_calib_final(lohi, d, p, st));
-    CH_TRY(launch_fill_u64(best, n_A, ~0ull, st));
-    float *nb2 = nullptr;
-    const bool lp = lowp_supported(d, metric, pl.precision);
-    if (!lp && mfma_supported(d, metric)) {
-        nb2 = at<float>(ws, pl.off_nb2);
-        CH_TRY(launch_rownorm(B, n_B, d, nb2, p, st));
-    }
-    if ((rc = nn_pass(pl, ws, A, nullptr, n_A, B, n_B, best, nb2, p, st))) return rc;
+    CH_TRY(launch_calib_final(lohi, d, p, half_supported(d, metric) ? B : nullptr, n_B, true, st));
+    CH_TRY(launch_fill_u64(best, reset_words(pl), ~0ull, st));
+    if ((rc = nn_pass(pl, ws, A, nullptr, n_A, B, n_B, best, p, st))) return rc;
     CH_TRY(launch_nn_finalize(best, n_A, metric, rowmin_out, rownn_out, partial, p, st));
     CH_TRY(launch_sum_final(partial, nn_finalize_blocks(n_A), p, ch_out, st));
     return CHAMFER_OK;
@@ -613,15 +628,18 @@ int chamfer_nn_min(const float *X, const int32_t *rows, int64_t n_x, const float
     hipStream_t st = static_cast<hipStream_t>(stream);
     DevParams *p = at<DevParams>(ws, pl.off_params);
     auto *best = at<unsigned long long>(ws, pl.off_best);
-    CH_TRY(launch_init_params(p, nullptr, d, st));
-    CH_TRY(launch_fill_u64(best, n_x, ~0ull, st));
-    float *nb2 = nullptr;
-    const bool lp = lowp_supported(d, metric, pl.precision);
-    if (!lp && mfma_supported(d, metric)) {
-        nb2 = at<float>(ws, pl.off_nb2);
-        CH_TRY(launch_rownorm(B, n_B, d, nb2, p, st));
+    if (!lowp_supported(d, metric, pl.precision) && half_supported(d, metric)) {
+        // the scale and centre of the exact pass, from B alone (the number of
+        // rows of X is not known here); inputs are not checked
+        uint32_t *lohi = at<uint32_t>(ws, pl.off_lohi);
+        CH_TRY(launch_init_params(p, lohi, d, st));
+        CH_TRY(launch_minmax(B, n_B, d, true, lohi, p, st));
+        CH_TRY(launch_calib_final(lohi, d, p, B, n_B, false, st));
+    } else {
+        CH_TRY(launch_init_params(p, nullptr, d, st));
     }
-    if ((rc = nn_pass(pl, ws, X, rows, n_x, B, n_B, best, nb2, p, st))) return rc;
+    CH_TRY(launch_fill_u64(best, reset_words(pl), ~0ull, st));
+    if ((rc = nn_pass(pl, ws, X, rows, n_x, B, n_B, best, p, st))) return rc;
     CH_TRY(launch_nn_finalize(best, n_x, metric, min_out, arg_out, nullptr, p, st));
     return CHAMFER_OK;
 }
@@ -665,43 +683,38 @@ int chamfer_estimate(const float *A, const float *B, int64_t n_A, int64_t n_B, i
     float *D = ax.crude_D ? ax.crude_D : at<float>(ws, pl.off_D);
     int32_t *scale = ax.crude_scale;
     void **ev = ax.stage_events;
-    float *nb2 = mfma_supported(d, metric) ? at<float>(ws, pl.off_nb2) : nullptr;
-    uint16_t *bsplit = nb2 && !lowp_supported(d, metric, pl.precision)
-                           ? at<uint16_t>(ws, pl.off_bsplit)
-                           : nullptr;
+    const bool tabled = half_supported(d, metric) && half_tabled(d) &&
+                        !lowp_supported(d, metric, pl.precision);
+    const bool uniform = pl.sampling == CHAMFER_UNIFORM;
     DevParams *p = at<DevParams>(ws, pl.off_params);
-    if (pl.sampling == CHAMFER_UNIFORM) {
+    if (uniform) {
         // the baseline: no CrudeNN, every D_a = 1 (inputs still checked)
         uint32_t *lohi = at<uint32_t>(ws, pl.off_lohi);
         CH_TRY(mark(ev, 0, st));
         CH_TRY(launch_init_params(p, lohi, d, st));
         CH_TRY(launch_minmax_pair(A, n_A, B, n_B, d, lohi, p, st));
-        CH_TRY(launch_calib_final(lohi, d, p, st));
+        CH_TRY(launch_calib_final(lohi, d, p, half_supported(d, metric) ? B : nullptr, n_B, true,
+                                  st));
         CH_TRY(mark(ev, 1, st));
-        if (bsplit) CH_TRY(launch_rownorm(B, n_B, d, nb2, p, st));
         CH_TRY(mark(ev, 2, st));
         CH_TRY(launch_unit_weights(D, ax.crude_nn, scale, n_A, p, st));
         CH_TRY(mark(ev, 3, st));
     } else {
         int32_t *nn = ax.crude_nn ? ax.crude_nn : at<int32_t>(ws, pl.off_nn);
-        if ((rc = crude_core(pl, A, B, seed, D, nn, scale, ws, st, ev, nb2, bsplit))) return rc;
+        if ((rc = crude_core(pl, A, B, seed, D, nn, scale, ws, st, ev, tabled))) return rc;
     }
     uint64_t *P = at<uint64_t>(ws, pl.off_P);  // in-block prefixes of the weights
     int32_t *idx = at<int32_t>(ws, pl.off_idx);
     auto *best = at<unsigned long long>(ws, pl.off_best);
     CH_TRY(launch_weights(D, n_A, pl.q, at<uint64_t>(ws, pl.off_blocksums), P, p, st));
+    uint32_t *gthr = pl.thr_copies ? at<uint32_t>(ws, pl.off_gthr) : nullptr;
     CH_TRY(launch_sample(seed, P, at<uint64_t>(ws, pl.off_blocksums), n_A, pl.T, pl.q, idx, best,
-                         p, st));
+                         gthr, pl.thr_copies, p, st));
     CH_TRY(mark(ev, 4, st));
-    // the split table of the draws (part of the exact pass); B's was written
-    // while B was hashed, except for the uniform baseline, which does not
-    // hash B
-    if (bsplit) {
-        if (pl.sampling == CHAMFER_UNIFORM) CH_TRY(launch_split_rows(B, n_B, d, bsplit, p, st));
-        CH_TRY(launch_split_queries(A, idx, pl.T, d, at<uint16_t>(ws, pl.off_xsplit),
-                                    at<float>(ws, pl.off_xn2), p, st));
-    }
-    if ((rc = nn_pass(pl, ws, A, idx, pl.T, B, n_B, best, nb2, p, st, bsplit != nullptr, true)))
+    // B's FP16 table was written while B was hashed (the uniform baseline does
+    // not hash B); the crude distance of a draw bounds its minimum from above
+    if ((rc = nn_pass(pl, ws, A, idx, pl.T, B, n_B, best, p, st, tabled && !uniform,
+                      uniform ? nullptr : D)))
         return rc;
     CH_TRY(mark(ev, 5, st));
     CH_TRY(launch_estimate_final(best, idx, D, pl.T, metric, p, eta_out, ax, st));
@@ -821,6 +834,25 @@ const char *chamfer_strerror(int status) {
             return "problem needs more workspace than the static scratch buffer holds";
         default: return "unknown status";
     }
+}
+
+// The two-term BF16 split's score bound: see chamfer.h.
+double chamfer_split_score_bound(int32_t d, int32_t terms, float xn2, float b2max) {
+    if (d < 1 || d > 256 || (terms != 3 && terms != 4)) return -1.0;
+    const int dp = d <= 32 ? 32 : d <= 64 ? 64 : d <= 128 ? 128 : 256;
+    constexpr double kU = 1.0 / 16777216.0;           // 2^-24
+    constexpr double kTiny = 1.1754943508222875e-38;  // 2^-126
+    const double rho = (double)(d + 4) * kU * 1.1;
+    const double crel = (double)((terms == 4 ? 1 : 3) * dp + 8) * kU * 1.1;
+    const double cnrm = (double)(d + 1) * kU * 1.1;
+    const double ctr = (terms == 4 ? 2.01 : 3.03) / 65536.0 * 1.1;
+    const double cabs = (double)(20 * dp + 16) * kTiny * 1.1;
+    const double cden = 8.0 * std::sqrt((double)dp) * kTiny * 1.1;
+    const double b2m = (double)b2max * (1.0 + rho);
+    const double bm = std::sqrt(b2m);
+    const double xabs = std::sqrt((double)xn2 * (1.0 + rho));
+    return cabs + cden * (xabs + bm) + crel * (b2m + 2.04 * xabs * bm) + cnrm * b2m +
+           2.0 * ctr * xabs * bm;
 }
 
 }  // extern "C"

@@ -32,10 +32,14 @@ __device__ __forceinline__ void init_params(DevParams *p, uint32_t *lohi, int d,
         p->W = 0;
         p->S = 0.0;
         p->fallbacks = 0;
-        p->nredo = 0;
+        p->he = 0;
+        p->half_box = 0.0f;
     }
-    for (int64_t k = t; k < 2 * kMaxRepl; k += b.n * blockDim.x)
-        (k < kMaxRepl ? p->max_d_rep : p->b2max_rep)[(k % kMaxRepl) * kReplStride] = 0u;
+    for (int64_t k = t; k < kMaxRepl; k += b.n * blockDim.x) {
+        p->max_d_rep[k * kReplStride] = 0u;
+        p->half_rep[k * kReplStride] = 0u;
+        p->half_rep[k * kReplStride + 1] = 0u;
+    }
     if (lohi != nullptr)
         for (int64_t k = t; k < (int64_t)kLohiReps * 2 * d; k += b.n * blockDim.x)
             lohi[k] = (k % (2 * d)) < d ? 0xffffffffu : 0u;  // running min / max (ordered)
@@ -89,66 +93,57 @@ hipError_t launch_grid_tables(uint64_t seed, int L, int kh, float *zfrac, uint64
 // flat element e has coordinate e mod d; the grid stride is a multiple of d,
 // so every thread keeps one coordinate.  Min/max use integer atomics on an
 // order-preserving encoding, whose result does not depend on their order.
-__device__ __forceinline__ void minmax(const float *__restrict__ X, int64_t total, int d,
-                                       int64_t stride, uint32_t *lohi, DevParams *p, Blk b) {
-    extern __shared__ uint32_t sm[];
-    const bool use_lds = d <= 2048;
-    if (use_lds) {
-        for (int i = threadIdx.x; i < d; i += blockDim.x) {
-            sm[i] = 0xffffffffu;
-            sm[d + i] = 0u;
-        }
-        __syncthreads();
-    }
-    const int64_t g = b.id * blockDim.x + threadIdx.x;
-    uint32_t lo = 0xffffffffu, hi = 0u;
-    int bad = 0;
-    if (g < stride) {
-        for (int64_t e = g; e < total; e += stride) {
-            const float v = ro(X)[e];
-            bad |= !isfinite(v);
-            const uint32_t o = float_to_ordered(v);
-            lo = min(lo, o);
-            hi = max(hi, o);
-        }
-        const int k = (int)(g % d);
-        if (use_lds) {
-            atomicMin(&sm[k], lo);
-            atomicMax(&sm[d + k], hi);
-        } else {
-            uint32_t *rep = lohi + (b.id % kLohiReps) * 2 * d;
-            atomicMin(&rep[k], lo);
-            atomicMax(&rep[d + k], hi);
-        }
-    }
-    if (bad) atomicOr(&p->nonfinite, 1u);
-    if (use_lds) {
-        __syncthreads();
-        uint32_t *rep = lohi + (b.id % kLohiReps) * 2 * d;
-        for (int i = threadIdx.x; i < d; i += blockDim.x) {
-            if (sm[i] != 0xffffffffu) atomicMin(&rep[i], sm[i]);
-            if (sm[d + i] != 0u) atomicMax(&rep[d + i], sm[d + i]);
-        }
-    }
+// This form (4-byte loads) serves d > 2048 only.
+__device__ __forceinline__ uint32_t *lohi_copy(uint32_t *lohi, int d, bool isB, int64_t id) {
+    constexpr int kHalf = kLohiReps / 2;
+    return lohi + ((isB ? kHalf : 0) + (int)(id % kHalf)) * 2 * (int64_t)d;
 }
 
 __global__ __launch_bounds__(256) void k_minmax(const float *__restrict__ X, int64_t total,
-                                                int d, int64_t stride, uint32_t *lohi,
+                                                int d, int64_t stride, bool isB, uint32_t *lohi,
                                                 DevParams *p) {
-    minmax(X, total, d, stride, lohi, p, grid_blk());
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= stride) return;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    int bad = 0;
+    for (int64_t e = g; e < total; e += stride) {
+        const float v = ro(X)[e];
+        bad |= !isfinite(v);
+        const uint32_t o = float_to_ordered(v);
+        lo = min(lo, o);
+        hi = max(hi, o);
+    }
+    uint32_t *rep = lohi_copy(lohi, d, isB, blockIdx.x);
+    const int k = (int)(g % d);
+    atomicMin(&rep[k], lo);
+    atomicMax(&rep[d + k], hi);
+    if (bad) atomicOr(&p->nonfinite, 1u);
 }
 
-// Same with 16-byte loads when d is a multiple of 4: thread g keeps the four
-// coordinates of float4 column (g mod d/4).
-__device__ __forceinline__ void minmax4(const float4 *__restrict__ X4, int64_t total4, int d,
-                                        int64_t stride4, uint32_t *lohi, DevParams *p, Blk b) {
+// Same with 16-byte loads, any d <= 2048 and any 4-byte aligned X: the
+// elements before the first 16-byte boundary and after the last are taken by
+// block 0, and thread g keeps the four coordinates (4 g + i + head) mod d of
+// float4 g (the stride, in float4, is a multiple of d / gcd(d, 4)).  Small d
+// would send a wavefront's LDS atomics to a few words, so the block's min/max
+// is kept in C copies that lanes pick by id (minmax_copies) and folds them at
+// the end.  d = 3, 2 10^5 rows: 19.2 us with 4-byte loads, see minmax_geom.
+__host__ __device__ inline int minmax_copies(int d) {
+    return d <= 64 ? 16 : d <= 256 ? 2 : 1;
+}
+inline size_t minmax_lds(int d) { return (size_t)minmax_copies(d) * 2 * d * sizeof(uint32_t); }
+
+__device__ __forceinline__ void minmax4(const float *__restrict__ X, int64_t total, int d,
+                                        int64_t stride4, bool isB, uint32_t *lohi, DevParams *p,
+                                        Blk b) {
     extern __shared__ uint32_t sm[];
-    const int d4 = d >> 2;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) {
-        sm[i] = 0xffffffffu;
-        sm[d + i] = 0u;
-    }
+    const int C = minmax_copies(d);
+    for (int i = threadIdx.x; i < C * 2 * d; i += blockDim.x) sm[i] = i < C * d ? 0xffffffffu : 0u;
     __syncthreads();
+    uint32_t *mine_lo = sm + (threadIdx.x & (C - 1)) * d, *mine_hi = mine_lo + C * d;
+    const int64_t head =
+        min(total, (int64_t)(((16 - (reinterpret_cast<uintptr_t>(X) & 15)) & 15) >> 2));
+    const int64_t total4 = (total - head) / 4;
+    const auto *Xr = reinterpret_cast<const CH_RO float4 *>(ro(X) + head);
     const int64_t g = b.id * blockDim.x + threadIdx.x;
     uint32_t lo[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
     uint32_t hi[4] = {0u, 0u, 0u, 0u};
@@ -163,9 +158,8 @@ __device__ __forceinline__ void minmax4(const float4 *__restrict__ X4, int64_t t
             hi[i] = max(hi[i], o);
         }
     };
-    if (g < stride4) {
+    if (g < stride4 && g < total4) {
         int64_t e = g;
-        const auto *Xr = ro(X4);
         // up to 16 loads per thread (10^5 x 128 points: exactly 16) eight go
         // out together; on longer runs eight at a time was slower (10^6:
         // 0.21 -> 0.23 ms), so those keep four
@@ -186,58 +180,68 @@ __device__ __forceinline__ void minmax4(const float4 *__restrict__ X4, int64_t t
             take(v3);
         }
         for (; e < total4; e += stride4) take(ld(Xr + e));
-        const int k0 = (int)(g % d4) * 4;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            atomicMin(&sm[k0 + i], lo[i]);
-            atomicMax(&sm[d + k0 + i], hi[i]);
+            const int k = (int)((4 * g + i + head) % d);
+            atomicMin(&mine_lo[k], lo[i]);
+            atomicMax(&mine_hi[k], hi[i]);
         }
+    }
+    // the ends: elements [0, head) and [head + 4 total4, total)
+    if (b.id == 0 && (int64_t)threadIdx.x < total - 4 * total4) {
+        const int64_t e =
+            (int64_t)threadIdx.x < head ? (int64_t)threadIdx.x : 4 * total4 + threadIdx.x;
+        const float v = ro(X)[e];
+        bad |= !isfinite(v);
+        const int k = (int)(e % d);
+        atomicMin(&mine_lo[k], float_to_ordered(v));
+        atomicMax(&mine_hi[k], float_to_ordered(v));
     }
     if (bad) atomicOr(&p->nonfinite, 1u);
     __syncthreads();
-    uint32_t *rep = lohi + (b.id % kLohiReps) * 2 * d;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) {
-        if (sm[i] != 0xffffffffu) atomicMin(&rep[i], sm[i]);
-        if (sm[d + i] != 0u) atomicMax(&rep[d + i], sm[d + i]);
+    uint32_t *rep = lohi_copy(lohi, d, isB, b.id);
+    for (int i = threadIdx.x; i < 2 * d; i += blockDim.x) {
+        const bool low = i < d;
+        const uint32_t *s = low ? sm + i : sm + (C - 1) * d + i;
+        uint32_t v = s[0];
+        for (int c = 1; c < C; ++c) v = low ? min(v, s[c * d]) : max(v, s[c * d]);
+        if (low) {
+            if (v != 0xffffffffu) atomicMin(&rep[i], v);
+        } else if (v != 0u) {
+            atomicMax(&rep[i], v);
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void k_minmax4(const float4 *__restrict__ X4, int64_t total4,
-                                                 int d, int64_t stride4, uint32_t *lohi,
+// Blocks [0, nbA) take A, the rest B.
+__global__ __launch_bounds__(256) void k_minmax4(const float *__restrict__ A, int64_t totalA,
+                                                 int64_t strideA, int64_t nbA,
+                                                 const float *__restrict__ B, int64_t totalB,
+                                                 int64_t strideB, int d, uint32_t *lohi,
                                                  DevParams *p) {
-    minmax4(X4, total4, d, stride4, lohi, p, grid_blk());
-}
-
-// Both point sets in one launch: blocks [0, nbA) take A, the rest B.
-__global__ __launch_bounds__(256) void k_minmax4_pair(const float4 *__restrict__ A4,
-                                                      int64_t totalA4, int64_t strideA4,
-                                                      int64_t nbA, const float4 *__restrict__ B4,
-                                                      int64_t totalB4, int64_t strideB4, int d,
-                                                      uint32_t *lohi, DevParams *p) {
     const int64_t b = blockIdx.x;
     if (b < nbA)
-        minmax4(A4, totalA4, d, strideA4, lohi, p, Blk{b, nbA});
+        minmax4(A, totalA, d, strideA, false, lohi, p, Blk{b, nbA});
     else
-        minmax4(B4, totalB4, d, strideB4, lohi, p, Blk{b - nbA, (int64_t)gridDim.x - nbA});
+        minmax4(B, totalB, d, strideB, true, lohi, p, Blk{b - nbA, (int64_t)gridDim.x - nbA});
 }
 
-bool minmax_vec4(const float *X, int d) {
-    return (d & 3) == 0 && d <= 2048 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
-}
+bool minmax_wide(int d) { return d <= 2048; }
 
-void minmax_geom(int64_t n, int d, bool vec4, int64_t *blocks_out, int64_t *stride_out) {
+void minmax_geom(int64_t n, int d, bool wide, int64_t *blocks_out, int64_t *stride_out) {
     const int64_t total = n * (int64_t)d;
     int64_t blocks;
-    // about 64 coordinates per thread: each block ends with 2d global atomics
-    // on the same 2d words, so small inputs want few blocks
-    if (vec4) {
-        const int64_t total4 = total / 4;
-        const int d4 = d / 4;
-        blocks = (total4 + 4095) / 4096;
+    if (wide) {
+        // float4 per thread: 16 where a block ends with many global atomics
+        // (2 d of them), 4 for small d, whose clouds are a few MB and would
+        // otherwise leave most of the chip idle
+        const int64_t per = d > 64 ? 16 : 4;
+        const int64_t total4 = total / 4, p4 = (d & 3) == 0 ? d / 4 : (d & 1) == 0 ? d / 2 : d;
+        blocks = (total4 + 256 * per - 1) / (256 * per);
         if (blocks > 1024) blocks = 1024;
-        const int64_t min_blocks = (d4 + 255) / 256;
+        const int64_t min_blocks = (p4 + 255) / 256;
         if (blocks < min_blocks) blocks = min_blocks;
-        *stride_out = (blocks * 256 / d4) * d4;
+        *stride_out = (blocks * 256 / p4) * p4;
     } else {
         blocks = (total + 16383) / 16384;
         if (blocks > 2048) blocks = 2048;
@@ -248,68 +252,120 @@ void minmax_geom(int64_t n, int d, bool vec4, int64_t *blocks_out, int64_t *stri
     *blocks_out = blocks;
 }
 
-hipError_t launch_minmax(const float *X, int64_t n, int d, uint32_t *lohi, DevParams *p,
+hipError_t launch_minmax(const float *X, int64_t n, int d, bool isB, uint32_t *lohi, DevParams *p,
                          hipStream_t st) {
-    const int64_t total = n * (int64_t)d;
+    if (minmax_wide(d))
+        return isB ? launch_minmax_pair(nullptr, 0, X, n, d, lohi, p, st)
+                   : launch_minmax_pair(X, n, nullptr, 0, d, lohi, p, st);
     int64_t blocks, stride;
-    if (minmax_vec4(X, d)) {
-        minmax_geom(n, d, true, &blocks, &stride);
-        k_minmax4<<<(unsigned)blocks, 256, 2 * (size_t)d * sizeof(uint32_t), st>>>(
-            reinterpret_cast<const float4 *>(X), total / 4, d, stride, lohi, p);
-        return hipGetLastError();
-    }
     minmax_geom(n, d, false, &blocks, &stride);
-    const size_t lds = d <= 2048 ? 2 * (size_t)d * sizeof(uint32_t) : 0;
-    k_minmax<<<(unsigned)blocks, 256, lds, st>>>(X, total, d, stride, lohi, p);
+    k_minmax<<<(unsigned)blocks, 256, 0, st>>>(X, n * (int64_t)d, d, stride, isB, lohi, p);
     return hipGetLastError();
 }
 
 hipError_t launch_minmax_pair(const float *A, int64_t nA, const float *B, int64_t nB, int d,
                               uint32_t *lohi, DevParams *p, hipStream_t st) {
-    if (nA <= 0 || !minmax_vec4(A, d) || !minmax_vec4(B, d)) {
-        hipError_t e = nA > 0 ? launch_minmax(A, nA, d, lohi, p, st) : hipSuccess;
-        return e != hipSuccess ? e : launch_minmax(B, nB, d, lohi, p, st);
+    if (!minmax_wide(d)) {
+        hipError_t e = nA > 0 ? launch_minmax(A, nA, d, false, lohi, p, st) : hipSuccess;
+        return e != hipSuccess || nB <= 0 ? e : launch_minmax(B, nB, d, true, lohi, p, st);
     }
-    int64_t nbA, sA, nbB, sB;
-    minmax_geom(nA, d, true, &nbA, &sA);
-    minmax_geom(nB, d, true, &nbB, &sB);
-    k_minmax4_pair<<<(unsigned)(nbA + nbB), 256, 2 * (size_t)d * sizeof(uint32_t), st>>>(
-        reinterpret_cast<const float4 *>(A), nA * (int64_t)d / 4, sA, nbA,
-        reinterpret_cast<const float4 *>(B), nB * (int64_t)d / 4, sB, d, lohi, p);
+    int64_t nbA = 0, sA = 0, nbB = 0, sB = 0;
+    if (nA > 0) minmax_geom(nA, d, true, &nbA, &sA);
+    if (nB > 0) minmax_geom(nB, d, true, &nbB, &sB);
+    if (nbA + nbB == 0) return hipSuccess;
+    k_minmax4<<<(unsigned)(nbA + nbB), 256, minmax_lds(d), st>>>(
+        A, nA * (int64_t)d, sA, nbA, B, nB * (int64_t)d, sB, d, lohi, p);
     return hipGetLastError();
 }
 
-// Fold the kLohiReps copies of the running min/max into the first.
-__device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d) {
+// Fold the kLohiReps copies of the running min/max into the first.  With B
+// (d <= 256), also the centre and the scale of the l2 exact pass: c_k the mean
+// of up to 16 rows spread over B (any c is valid; near the mean it keeps the
+// operands, and so their rounding errors, small), the scale 2^he that takes the
+// largest |b_k - c_k| to [2^10, 2^11) (less where A's largest would leave
+// [0, 2^15); rows that were not in the min/max may be 2^5 times larger), and for d <= kHalfRawDim the corner distance of
+// B's box from c, which bounds |y|.
+__device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
+                                          const float *__restrict__ B, int64_t nB) {
+    __shared__ uint32_t mxs, mbs;
+    __shared__ float box[kHalfRawDim];
+    if (threadIdx.x == 0) mxs = mbs = 0u;
+    __syncthreads();
     for (int k = threadIdx.x; k < d; k += blockDim.x) {
-        uint32_t lo = lohi[k], hi = lohi[d + k];
-        for (int r = 1; r < kLohiReps; ++r) {
-            lo = min(lo, lohi[(size_t)r * 2 * d + k]);
-            hi = max(hi, lohi[(size_t)r * 2 * d + d + k]);
+        float c = 0.0f;
+        if (B) {
+            // up to 16 rows in one batch of loads (rows repeat when nB < 16)
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = ro(B)[(nB * i / 16) * d + k];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) c += v[i] * 0.0625f;
+            if (!isfinite(c)) c = 0.0f;
         }
-        lohi[k] = lo;
-        lohi[d + k] = hi;
+        uint32_t lo[2], hi[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            lo[h] = 0xffffffffu;
+            hi[h] = 0u;
+#pragma unroll
+            for (int r = 0; r < kLohiReps / 2; ++r) {  // one batch of loads, with B's
+                const uint32_t *rep = lohi + (size_t)(h * (kLohiReps / 2) + r) * 2 * d;
+                lo[h] = min(lo[h], rep[k]);
+                hi[h] = max(hi[h], rep[d + k]);
+            }
+        }
+        lohi[k] = min(lo[0], lo[1]);
+        lohi[d + k] = max(hi[0], hi[1]);
+        if (B) {
+            lohi[2 * d + k] = __float_as_uint(c);
+            const float hb = ordered_to_float(hi[1]), lb = ordered_to_float(lo[1]);
+            const float mb = isfinite(hb) && isfinite(lb) ? fmaxf(hb - c, c - lb) : INFINITY;
+            const float ma = fmaxf(ordered_to_float(max(hi[0], hi[1])) - c,
+                                   c - ordered_to_float(min(lo[0], lo[1])));
+            atomicMax(&mxs, __float_as_uint(fabsf(ma)));
+            atomicMax(&mbs, __float_as_uint(fabsf(mb)));
+            if (k < kHalfRawDim) box[k] = mb;
+        }
     }
     __syncthreads();
+    if (B && threadIdx.x == blockDim.x - 1) {
+        const float M = __uint_as_float(mxs);
+        const float MB = __uint_as_float(mbs);
+        int he = 0;
+        if (M > 0.0f && isfinite(M)) {
+            he = 14 - ilogbf(M);
+            if (MB > 0.0f && isfinite(MB)) he = min(he, 10 - ilogbf(MB));
+        }
+        p->he = he;
+        if (d <= kHalfRawDim) {
+            float s = 0.0f;
+            for (int k = 0; k < d; ++k) {
+                const float y = ldexpf(box[k], he);
+                s = fmaf(y, y, s);
+            }
+            p->half_box = sqrtf(s) * 1.00001f;
+        }
+    }
 }
 
-__global__ void k_calib_final_wide(uint32_t *lohi, int d, DevParams *p) {
-    fold_lohi(lohi, d);
+__global__ void k_calib_final_wide(uint32_t *lohi, int d, DevParams *p, bool check) {
+    fold_lohi(lohi, d, p, nullptr, 0);
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     double S = 0.0;
     for (int k = 0; k < d; ++k)
         S = S + ((double)ordered_to_float(lohi[d + k]) - (double)ordered_to_float(lohi[k]));
     p->S = S;
     p->e_top = S > 0.0 ? ceil_log2_pos(S) : 0;
-    if (p->nonfinite) p->status = CHAMFER_ENONFINITE;
+    if (check && p->nonfinite) p->status = CHAMFER_ENONFINITE;
 }
 
 // S = sum_k (hi_k - lo_k) in double, k ascending; e_top = ceil(log2 S).
 // The per-coordinate spans are gathered in parallel; one thread sums them
 // in order.
-__device__ __forceinline__ void calib_final(uint32_t *lohi, int d, DevParams *p) {
+__device__ __forceinline__ void calib_final(uint32_t *lohi, int d, DevParams *p,
+                                            const float *__restrict__ B, int64_t nB, bool check) {
     extern __shared__ double span[];
-    fold_lohi(lohi, d);
+    fold_lohi(lohi, d, p, B, nB);
     for (int k = threadIdx.x; k < d; k += blockDim.x)
         span[k] = (double)ordered_to_float(lohi[d + k]) - (double)ordered_to_float(lohi[k]);
     __syncthreads();
@@ -318,20 +374,25 @@ __device__ __forceinline__ void calib_final(uint32_t *lohi, int d, DevParams *p)
     for (int k = 0; k < d; ++k) S = S + span[k];
     p->S = S;
     p->e_top = S > 0.0 ? ceil_log2_pos(S) : 0;
-    if (p->nonfinite) p->status = CHAMFER_ENONFINITE;
+    if (check && p->nonfinite) p->status = CHAMFER_ENONFINITE;
 }
 
-__global__ __launch_bounds__(256) void k_calib_final(uint32_t *lohi, int d, DevParams *p) {
-    calib_final(lohi, d, p);
+__global__ __launch_bounds__(256) void k_calib_final(uint32_t *lohi, int d, DevParams *p,
+                                                     const float *__restrict__ B, int64_t nB,
+                                                     bool check) {
+    calib_final(lohi, d, p, B, nB, check);
 }
 
-hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, hipStream_t st) {
+hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, const float *B, int64_t nB,
+                              bool check, hipStream_t st) {
     if ((size_t)d * sizeof(double) > 60000) {
         // very wide points: spans recomputed by the summing thread
-        k_calib_final_wide<<<1, 64, 0, st>>>(lohi, d, p);
+        if (B != nullptr) return hipErrorInvalidValue;
+        k_calib_final_wide<<<1, 64, 0, st>>>(lohi, d, p, check);
         return hipGetLastError();
     }
-    k_calib_final<<<1, 256, (size_t)d * sizeof(double), st>>>(lohi, d, p);
+    if (B != nullptr && nB < 1) return hipErrorInvalidValue;
+    k_calib_final<<<1, 256, (size_t)d * sizeof(double), st>>>(lohi, d, p, B, nB, check);
     return hipGetLastError();
 }
 
@@ -832,38 +893,41 @@ __device__ __forceinline__ float quad_dist(const float *__restrict__ X, int64_t 
 // first hit (or once another wavefront has hit at a finer scale); the first
 // colliding scale is the smallest over the four.
 // EC: coordinates of x staged per pass of the l2 embedding.
-// B's split table for the l2 exact pass, written from the staged rows while B
-// is hashed (B is read once): row r of the table holds h = bf16(x_k) for
-// k < split_dp, then m = bf16(x_k - h) (zero past d), as the separate split
-// pass writes them.  Coordinates [k0, k0 + kc) of the tile's np points are
-// staged at xs[point * ld + k - k0]; the last chunk also writes the padding
-// [k0 + kc, split_dp).  Thread t takes 16 consecutive coordinates of point
-// t / 4 per 64-coordinate step.
-__device__ __forceinline__ void split_staged(const float *xs, int ld, int64_t p0, int np, int k0,
-                                             int kc, bool last, int split_dp, uint16_t *out) {
+// B's FP16 table for the l2 exact pass (half_of of (x_k - c_k) 2^he for
+// k < half_dp, zero past d), written from the staged rows while B is hashed (B
+// is read once), with the same values as k_half_rows.  Coordinates
+// [k0, k0 + kc) of the tile's np points are staged at xs[point * ld + k - k0],
+// the centre's at cen; the last chunk also writes the padding
+// [k0 + kc, half_dp).  Thread t takes 16 consecutive coordinates of point
+// t / 4 per 64-coordinate step and adds their squares and those of their
+// rounding errors to s2 and e2.
+__device__ __forceinline__ void half_staged(const float *xs, int ld, const float *cen, int he,
+                                            int64_t p0, int np, int k0, int kc, bool last,
+                                            int half_dp, uint16_t *out, float &s2, float &e2) {
     const int pp = threadIdx.x >> 2;
     if (pp >= np) return;
-    uint16_t *row = out + (size_t)(p0 + pp) * (2 * split_dp);
-    const int kend = last ? split_dp : k0 + kc;
+    uint16_t *row = out + (size_t)(p0 + pp) * half_dp;
+    const int kend = last ? half_dp : k0 + kc;
     for (int c = k0 + (threadIdx.x & 3) * 16; c < kend; c += 64) {
-        uint32_t hw[8], mw[8];
+        uint32_t w[8];
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
-            const int a = c + e - k0;
-            const float v0 = a < kc ? xs[pp * ld + a] : 0.0f;
-            const float v1 = a + 1 < kc ? xs[pp * ld + a + 1] : 0.0f;
-            uint32_t h0, m0, h1, m1;
-            split2(v0, h0, m0);
-            split2(v1, h1, m1);
-            hw[e / 2] = h0 | (h1 << 16);
-            mw[e / 2] = m0 | (m1 << 16);
+            uint32_t hb[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int a = c + e + q - k0;
+                const float v = a < kc ? ldexpf(xs[pp * ld + a] - cen[a], he) : 0.0f;
+                const _Float16 h = half_of(v);
+                const float r = half_rest(v, h);
+                s2 = fmaf(v, v, s2);
+                e2 = fmaf(r, r, e2);
+                hb[q] = half_bits(h);
+            }
+            w[e / 2] = hb[0] | (hb[1] << 16);
         }
         uint4 *hd = reinterpret_cast<uint4 *>(row + c);
-        uint4 *md = reinterpret_cast<uint4 *>(row + split_dp + c);
-        hd[0] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-        hd[1] = make_uint4(hw[4], hw[5], hw[6], hw[7]);
-        md[0] = make_uint4(mw[0], mw[1], mw[2], mw[3]);
-        md[1] = make_uint4(mw[4], mw[5], mw[6], mw[7]);
+        hd[0] = make_uint4(w[0], w[1], w[2], w[3]);
+        hd[1] = make_uint4(w[4], w[5], w[6], w[7]);
     }
 }
 
@@ -873,8 +937,8 @@ __device__ __forceinline__ void hash_tile(
     const uint32_t *__restrict__ lohi, const int8_t *__restrict__ embed,
     const float *__restrict__ zfrac, const uint64_t *__restrict__ mult, Bucket *tables,
     int log2cap, unsigned long long *keys_out, float *D_out, int32_t *nn_out,
-    int32_t *scale_out, float *nb2_out, DevParams *p, int64_t nB, int W, int flags, Blk blk,
-    uint16_t *split_out = nullptr, int split_dp = 0) {
+    int32_t *scale_out, float *nbh_out, DevParams *p, int64_t nB, int W, int flags, Blk blk,
+    uint16_t *half_out = nullptr, int half_dp = 0) {
     extern __shared__ float smem[];
     __shared__ float los[EC > kEmbedChunk ? EC : kEmbedChunk];
     __shared__ int hit_scale[kTile];
@@ -915,8 +979,7 @@ __device__ __forceinline__ void hash_tile(
         // int32 accumulator per byte; then Y_j = sum_a 2^(8a) (acc_a + 128 R_j)
         // with R_j = sum_k Zq_jk, and y_j = (float)((Y_j 2^(e_top - 24)) inv),
         // inv = 1 / (beta KE 32).  The raw rows are staged 64 coordinates at a
-        // time; for B, wavefront 0 also accumulates |x|^2 per row (fma chain,
-        // coordinates ascending) for the l2 nearest-neighbour pass.
+        // time; B's FP16 table of the l2 exact pass is written from them too.
         constexpr int NT = (KE + 15) / 16;
         constexpr int ECM = kEmbedChunk;  // one 64-coordinate MFMA step per staged chunk
         const int nks = (d + ECM - 1) / ECM;
@@ -929,23 +992,23 @@ __device__ __forceinline__ void hash_tile(
 #pragma unroll
             for (int t = 0; t < NT; ++t) acc[a][t] = v4i{0, 0, 0, 0};
         const auto *zpk = reinterpret_cast<const CH_RO uint4 *>(ro(embed));
-        float n2 = 0.0f;
-        const bool want_n2 =
-            (MODE == 0 || MODE == 3 || MODE == 5) && nb2_out != nullptr && wave == 0;
+        constexpr bool kHalfMode = MODE == 0 || MODE == 3 || MODE == 5;
+        __shared__ float cens[ECM];
+        __shared__ uint32_t hmx[2];
+        const bool want_half = kHalfMode && half_out != nullptr;
+        float s2 = 0.0f, e2 = 0.0f;
+        if (kHalfMode && tid < 2) hmx[tid] = 0u;
         for (int ks = 0; ks < nks; ++ks) {
             const int k0 = ks * ECM;
             const int kc = min(ECM, d - k0);
             __syncthreads();
             stage_rows<16>(X, p0, np, d, k0, kc, xs, ECM + 1, nullptr);
             if (tid < kc) los[tid] = ordered_to_float(ro(lohi)[k0 + tid]);
+            if (want_half && tid < kc) cens[tid] = half_centre(lohi, d)[k0 + tid];
             __syncthreads();
-            if (want_n2 && active)
-                for (int k = 0; k < kc; ++k) {
-                    const float xraw = xs[lane * (ECM + 1) + k];
-                    n2 = fmaf(xraw, xraw, n2);
-                }
-            if ((MODE == 0 || MODE == 3 || MODE == 5) && split_out != nullptr)
-                split_staged(xs, ECM + 1, p0, np, k0, kc, ks == nks - 1, split_dp, split_out);
+            if (want_half)
+                half_staged(xs, ECM + 1, cens, p->he, p0, np, k0, kc, ks == nks - 1, half_dp,
+                            half_out, s2, e2);
             // A: 16 coordinates k0 + 16 g4 + e of point 16 wave + i16, as the
             // three bytes of u, each offset by -128 (xor 0x80); four
             // coordinates at a time give one dword of each byte's operand
@@ -994,12 +1057,27 @@ __device__ __forceinline__ void hash_tile(
                         (float)(ldexp((double)Y, e_top - 24) * inv);
             }
         }
-        if (want_n2 && active) nb2_out[pt] = n2;
-        if (want_n2) {
-            uint32_t m = __float_as_uint(n2);
-            for (int off = 32; off > 0; off >>= 1)
-                m = max(m, (uint32_t)__shfl_xor((int)m, off));
-            if (lane == 0) rep_max(p->b2max_rep, blk.id, m);
+        if (want_half) {
+            // four lanes per point; one atomic per maximum and tile
+#pragma unroll
+            for (int off = 1; off < 4; off <<= 1) {
+                s2 += __shfl_xor(s2, off);
+                e2 += __shfl_xor(e2, off);
+            }
+            const HalfErr he_ = half_err(d, half_dp);
+            if ((tid & 3) == 0 && (tid >> 2) < np)
+                nbh_out[p0 + (tid >> 2)] = half_norm(s2, e2, he_.s2, he_.e2);
+            uint32_t my = __float_as_uint(s2), me = __float_as_uint(e2);
+            for (int off = 32; off > 2; off >>= 1) {
+                my = max(my, (uint32_t)__shfl_xor((int)my, off));
+                me = max(me, (uint32_t)__shfl_xor((int)me, off));
+            }
+            if (lane == 0) {
+                atomicMax(&hmx[0], my);
+                atomicMax(&hmx[1], me);
+            }
+            __syncthreads();
+            if (tid < 2) rep_max(p->half_rep + tid, blk.id, hmx[tid]);
         }
     }
     if (MODE == 1 && wave == 0) hit_scale[lane] = L;
@@ -1248,11 +1326,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WAVES)
     const uint32_t *__restrict__ lohi, const int8_t *__restrict__ embed,
     const float *__restrict__ zfrac, const uint64_t *__restrict__ mult, Bucket *tables,
     int log2cap, unsigned long long *keys_out, float *D_out, int32_t *nn_out,
-    int32_t *scale_out, float *nb2_out, DevParams *p, int64_t nB, int W, int flags,
-    uint16_t *split_out, int split_dp) {
+    int32_t *scale_out, float *nbh_out, DevParams *p, int64_t nB, int W, int flags,
+    uint16_t *half_out, int half_dp) {
     hash_tile<METRIC, MODE, KE, YG, EC>(X, n, Bpts, d, L, lohi, embed, zfrac, mult, tables,
-                                        log2cap, keys_out, D_out, nn_out, scale_out, nb2_out, p,
-                                        nB, W, flags, grid_blk(), split_out, split_dp);
+                                        log2cap, keys_out, D_out, nn_out, scale_out, nbh_out, p,
+                                        nB, W, flags, grid_blk(), half_out, half_dp);
 }
 
 
@@ -1268,13 +1346,13 @@ static hipError_t launch_hash_t(int mode, const float *X, int64_t n, const float
                                 int64_t nB, int d, int L, const uint32_t *lohi,
                                 const int8_t *embed, const float *zfrac, const uint64_t *mult,
                                 Bucket *tables, int log2cap, uint64_t *keys_out, float *D_out,
-                                int32_t *nn_out, int32_t *scale_out, float *nb2_out,
+                                int32_t *nn_out, int32_t *scale_out, float *nbh_out,
                                 DevParams *p, int W, int flags, hipStream_t st,
-                                uint16_t *split_out, int split_dp) {
+                                uint16_t *half_out, int half_dp) {
     const unsigned blocks = (unsigned)hash_blocks(n);
     auto *ko = reinterpret_cast<unsigned long long *>(keys_out);
 #define CH_KARGS X, n, Bpts, d, L, lohi, embed, zfrac, mult, tables, log2cap, ko, D_out, nn_out, \
-                 scale_out, nb2_out, p, nB, W, flags, split_out, split_dp
+                 scale_out, nbh_out, p, nB, W, flags, half_out, half_dp
     // Four wavefronts per SIMD for every mode: measured against six and
     // eight (l2, 10^5 points: probe 90, 117 and 141 us; keys and insert
     // within noise or slower).
@@ -1318,18 +1396,18 @@ hipError_t launch_hash(int mode, const float *X, int64_t n, const float *Bpts, i
                        int d, int metric, int L, int ke, const uint32_t *lohi,
                        const int8_t *embed, const float *zfrac, const uint64_t *mult,
                        Bucket *tables, int log2cap, uint64_t *keys_out, float *D_out,
-                       int32_t *nn_out, int32_t *scale_out, float *nb2_out, DevParams *p,
-                       int W, int flags, hipStream_t st, uint16_t *split_out, int split_dp) {
+                       int32_t *nn_out, int32_t *scale_out, float *nbh_out, DevParams *p,
+                       int W, int flags, hipStream_t st, uint16_t *half_out, int half_dp) {
     if (n <= 0) return hipSuccess;
     if (W < 1 || W > kMaxWindow) return hipErrorInvalidValue;
-    // the split table is written from the l2 embedding's staged rows (B's
-    // hashing modes only; split_dp a multiple of 64 at or above d, or 32)
-    if (split_out != nullptr &&
-        (metric != CHAMFER_L2 || !(mode == 0 || mode == 3 || mode == 5) || split_dp < d ||
-         (split_dp % 64 != 0 && split_dp != 32)))
+    // the FP16 table is written from the l2 embedding's staged rows (B's
+    // hashing modes only; half_dp a multiple of 64 at or above d, or 32)
+    if (half_out != nullptr &&
+        (metric != CHAMFER_L2 || !(mode == 0 || mode == 3 || mode == 5) || half_dp < d ||
+         (half_dp % 64 != 0 && half_dp != 32)))
         return hipErrorInvalidValue;
 #define CH_ARGS mode, X, n, Bpts, nB, d, L, lohi, embed, zfrac, mult, tables, log2cap, keys_out, \
-                D_out, nn_out, scale_out, nb2_out, p, W, flags, st, split_out, split_dp
+                D_out, nn_out, scale_out, nbh_out, p, W, flags, st, half_out, half_dp
     if (metric == CHAMFER_L1) {
         // the window probe also keeps W ints per lane in LDS
         const int room = mode == 4 ? kMaxLdsL1Dim - W : kMaxLdsL1Dim;
@@ -1812,19 +1890,17 @@ __global__ __launch_bounds__(256) void kb_setup(const Batch *__restrict__ bt) {
 __global__ __launch_bounds__(256) void kb_minmax(const Batch *__restrict__ bt) {
     batch_loop(bt, kBsMinmax, [&](const Job &J, Blk b) {
         const bool isA = b.id < J.nb_mmA;
-        const float *X = isA ? J.A : J.B;
-        const int64_t total = (isA ? J.nA : J.nB) * (int64_t)J.d;
-        const int64_t stride = isA ? J.mm_strideA : J.mm_strideB;
-        const Blk c = isA ? Blk{b.id, J.nb_mmA} : Blk{b.id - J.nb_mmA, J.nb_mmB};
-        if (J.mm_vec4)
-            minmax4(reinterpret_cast<const float4 *>(X), total / 4, J.d, stride, J.lohi, J.p, c);
-        else
-            minmax(X, total, J.d, stride, J.lohi, J.p, c);
+        minmax4(isA ? J.A : J.B, (isA ? J.nA : J.nB) * (int64_t)J.d, J.d,
+                isA ? J.mm_strideA : J.mm_strideB, !isA, J.lohi, J.p,
+                isA ? Blk{b.id, J.nb_mmA} : Blk{b.id - J.nb_mmA, J.nb_mmB});
     });
 }
 
 __global__ __launch_bounds__(256) void kb_calib(const Batch *__restrict__ bt) {
-    batch_loop(bt, kBsCalib, [&](const Job &J, Blk) { calib_final(J.lohi, J.d, J.p); });
+    batch_loop(bt, kBsCalib, [&](const Job &J, Blk) {
+        const bool half = J.metric == CHAMFER_L2 && J.d <= 256;
+        calib_final(J.lohi, J.d, J.p, half ? J.B : nullptr, J.nB, true);
+    });
 }
 
 template <int METRIC, int MODE, int KE, bool YG>
@@ -1833,7 +1909,7 @@ __global__ __launch_bounds__(kThreads) void kb_hash(const Batch *__restrict__ bt
         if (MODE == 0)
             hash_tile<METRIC, 0, KE, YG>(J.B, J.nB, J.B, J.d, J.L, J.lohi, J.embed, J.zfrac,
                                          J.mult, J.tables, J.log2cap, nullptr, nullptr, nullptr,
-                                         nullptr, J.nb2, J.p, J.nB, 1, 0, b);
+                                         nullptr, nullptr, J.p, J.nB, 1, 0, b);
         else
             hash_tile<METRIC, 1, KE, YG>(J.A, J.nA, J.B, J.d, J.L, J.lohi, J.embed, J.zfrac,
                                          J.mult, J.tables, J.log2cap, nullptr, J.D, J.nn,
@@ -1848,7 +1924,7 @@ hipError_t launch_batch_setup(const Batch *bt, hipStream_t st) {
 
 hipError_t launch_batch_minmax(const Batch *bt, int d, hipStream_t st) {
     if (d > 2048) return hipErrorInvalidValue;
-    kb_minmax<<<kGridMinmax, 256, 2 * (size_t)d * sizeof(uint32_t), st>>>(bt);
+    kb_minmax<<<kGridMinmax, 256, minmax_lds(d), st>>>(bt);
     return hipGetLastError();
 }
 

@@ -18,10 +18,12 @@ constexpr uint32_t kPurposePart = 5;    // shifts and multipliers of the partiti
 constexpr uint32_t kPurposePad = 6;     // signs of the padding coordinates
 constexpr uint64_t kEmptyKey = ~0ull;   // bucket keys are < 2^63
 constexpr int kMaxScales = 64;
-// The per-coordinate min/max is accumulated in kLohiReps copies (workgroup
-// id mod kLohiReps picks one) so that the global atomics of many workgroups
-// do not queue on the same 2d words; the calibration folds the copies into
-// the first, [lo(d) | hi(d)], which every later kernel reads.
+// The per-coordinate min/max is accumulated in kLohiReps copies, half of them
+// for A and half for B (workgroup id mod kLohiReps / 2 picks one), so that the
+// global atomics of many workgroups do not queue on the same 2d words; the
+// calibration folds the copies into the first, [lo(d) | hi(d)], which every
+// later kernel reads, and keeps the centre of the l2 exact pass in the words
+// after it (half_centre).
 constexpr int kLohiReps = 8;
 inline size_t lohi_bytes(int d) { return (size_t)kLohiReps * 2 * (size_t)d * sizeof(uint32_t); }
 constexpr int kMaxWindow = 32;          // W of the multi-probe CrudeNN
@@ -43,16 +45,18 @@ struct DevParams {
     uint32_t nonfinite;  // an input coordinate is NaN or Inf
     uint64_t W;          // fixed-point total
     double S;            // sum_k (hi_k - lo_k)
-    uint32_t fallbacks;  // (query, chunk) pairs rescanned exactly by the MFMA pass
-    uint32_t nredo;      // (query, chunk) pairs listed for the deferred pass's rescan
-    uint32_t pad32[2];
+    uint32_t fallbacks;  // 32-row blocks the l2 exact pass evaluated in full
+    int32_t he;          // l2 exact pass: the operands' scale is 2^he
+    float half_box;      // l2 exact pass: upper bound of |(b - centre) 2^he| over B (d <= 10)
+    uint32_t pad32[1];
     uint64_t pad[1];
-    // The maxima of D_a and |b|^2 reduced over thousands of workgroups: each
+    // The maxima of D_a and (l2 exact pass) of |y|^2 and |y - y~|^2 (words 0
+    // and 1 of a replica) reduced over thousands of workgroups: each
     // workgroup's atomicMax goes to replica (id mod kMaxRepl), one 128-byte
     // line each, since atomics queued on one address serialise at its cache
     // channel; readers take the max over the replicas (rep_fold).
     uint32_t max_d_rep[kMaxRepl * kReplStride];
-    uint32_t b2max_rep[kMaxRepl * kReplStride];
+    uint32_t half_rep[kMaxRepl * kReplStride];
 };
 
 __device__ __forceinline__ void rep_max(uint32_t *rep, int64_t id, uint32_t m) {
@@ -125,12 +129,14 @@ struct Plan {
     // problem
     int64_t nA, nB, T;
     int32_t d, metric, L, ke, kh, q, precision, window, reps, sampling;
+    int32_t thr_copies;  // of the l2 exact pass's thresholds (0: it keeps none)
     uint64_t seed;
     int log2cap;  // per-scale table capacity is 2^log2cap
     bool part;    // B's tables come from the partitioned build (W = 1)
     // byte offsets into the workspace
     size_t off_params, off_lohi, off_zfrac, off_mult, off_embed, off_tables, off_D,
-        off_nn, off_scale, off_blocksums, off_P, off_idx, off_best, off_partial, off_nb2, off_bsplit, off_xsplit, off_xn2, off_srec, off_part,
+        off_nn, off_scale, off_blocksums, off_P, off_idx, off_best, off_partial, off_nbh, off_bhalf,
+        off_xhalf, off_xstat, off_gthr, off_part,
         off_bq, off_xq, off_lpf, total;
 };
 
@@ -188,16 +194,18 @@ struct Job {
     unsigned long long *blocksums, *P;  // block totals (then offsets); in-block prefixes
     int32_t *idx;
     unsigned long long *best;
-    float *nb2;
-    uint8_t *bq, *xq;  // low precision: cast B and draws; float32 l2: B's split table at bq
+    uint8_t *bq, *xq;  // low precision: cast B and draws
     float *lpf;
-    uint16_t *xsplit;  // float32 l2: the draws' split table and |x|^2
-    float *xn2;
+    uint16_t *bhalf, *xhalf;  // float32 l2: the FP16 tables of B and of the draws,
+    float *nbh;               // -|y|^2 / 2 per row of B and the draws' norms
+    float4 *xstat;
+    uint32_t *gthr;  // float32 l2: thresholds of the exact pass
+    int32_t thr_copies;
     double *eta;
     chamfer_aux aux;
     // geometry
     int32_t nb_init, nb_grid, nb_fill;
-    int32_t nb_mmA, nb_mmB, mm_vec4;
+    int32_t nb_mmA, nb_mmB, mm_wide;
     int64_t mm_strideA, mm_strideB;
     int32_t nb_hashB, nb_hashA, nb_scan, nb_sample;
     int32_t nb_castB, nb_castX, nn_nchunk, nb_nn;
@@ -214,7 +222,7 @@ enum BatchStage {
     kBsWsum,    // fixed-point weights: block sums
     kBsWscan,   // scan of the block sums, W and s
     kBsSample,  // T draws
-    kBsCast,    // low-precision copies of B and of the sampled rows, or B's split table
+    kBsCast,    // low-precision copies, or the FP16 tables, of B and of the sampled rows
     kBsNN,      // exact nearest neighbours of the samples
     kBsFinal,   // eta and the per-request outputs
     kBsCount
@@ -257,23 +265,75 @@ __device__ __forceinline__ uint4 ld(const CH_RO uint4 *p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// Padded dimension of the split tables of the l2 exact pass (12 <= d <= 256).
-__host__ __device__ inline int split_dpad(int d) {
-    return d <= 32 ? 32 : d <= 64 ? 64 : d <= 128 ? 128 : 256;
+// The centre of the l2 exact pass (d floats), in the words after the folded
+// min/max.
+__device__ __forceinline__ const CH_RO float *half_centre(const uint32_t *lohi, int d) {
+    return ro(reinterpret_cast<const float *>(lohi + 2 * d));
 }
 
-// BF16 bits of f, round to nearest even (f finite or infinite).
-__device__ __forceinline__ uint32_t bf16_rne_bits(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
+// FP16 of v for the l2 exact pass, with subnormals replaced by zero (whatever
+// the matrix cores do with them); a value beyond FP16's range returns its
+// largest.  half_rest: the rounding error, infinite outside FP16's range.
+__device__ __forceinline__ _Float16 half_of(float v) {
+    const _Float16 h = (_Float16)fmaxf(fminf(v, 65504.0f), -65504.0f);
+    return fabsf(v) < 6.103515625e-05f ? (_Float16)0.0f : h;
+}
+__device__ __forceinline__ float half_rest(float v, _Float16 h) {
+    return fabsf(v) <= 65504.0f ? v - (float)h : INFINITY;
+}
+__device__ __forceinline__ uint32_t half_bits(_Float16 h) {
+    return (uint32_t)__builtin_bit_cast(uint16_t, h);
 }
 
-// The two-term split of the l2 exact pass: (h, m) of v as BF16 bit patterns,
-// h = bf16(v), m = bf16(v - h) (v - h is exact in float32).
-__device__ __forceinline__ void split2(float v, uint32_t &h, uint32_t &m) {
-    h = bf16_rne_bits(v);
-    m = bf16_rne_bits(v - __uint_as_float(h << 16));
+// The l2 exact pass's score of a query z against a row y is within
+// half_err_query(z) + half_err_row(y) of z.y - |y|^2 / 2.  Every term is a
+// product of a query's and a row's magnitude or a square, and a product is split
+// by 2 a b <= l a^2 + b^2 / l, so that a row far out costs itself a wide margin
+// and no other row anything; for a query far out the products with the largest
+// of the rows (by >= |y|, be >= |y - y~|) are less.  With zt >= |z~|, ze >= |z - z~| (half_stat), s2
+// the computed |y|^2 and e2 the computed |y - y~|^2, u = 2^-24:
+//   operands      zt |y - y~| + ze |y|, split with l near the
+//                 ratio of an operand's rounding error to its size;
+//   three products (d <= kHalfRawDim; slots 16 or 32): the dropped m m, and
+//                 |y - y~| <= 1.1 2^-22 |y| + sqrt(d) 2^-14 in place of e2;
+//   accumulation  of exact products into float32, from -|y|^2 / 2 on, every step
+//                 with an error of at most 2 u of the partial sum;
+//   |y|^2 / 2     (d + 8) u, and x - c, b - c u of their own.
+struct HalfErr {
+    float q2, e2q, q1;  // query: q2 zt^2 + e2q ze^2 + q1 zt,
+    float p1;           // or zt (be + p1 by) + ze by + q1 zt, whichever is less
+    float s2, e2;       // row: s2 |y|^2 + e2 |y - y~|^2
+};
+constexpr int kHalfRawDim = 10;
+__host__ __device__ inline HalfErr half_err(int d, int slots) {
+    constexpr float kU = 1.0f / 16777216.0f;
+    const bool raw = d <= kHalfRawDim;
+    const float split = raw ? 1.0f / 8388608.0f : 1.0f / 4096.0f;
+    const float three = raw ? 2.12f / 4194304.0f : 0.0f;
+    const float acc = (float)(slots + 8) * (kU * 2.2f), nrm = (float)(d + 9) * (kU * 1.1f);
+    HalfErr h;  // (the factors also cover the roundings of these expressions)
+    h.q2 = 0.50002f * (split + three + 1.02f * acc);
+    h.e2q = 0.50002f / split;
+    h.p1 = 1.00001f * (three + 1.02f * acc);
+    h.q1 = raw ? sqrtf((float)d) * (1.01f / 16384.0f) : 0.0f;
+    h.s2 = 0.51f * (split + three + 2.02f * acc + nrm) + 1e-9f;
+    h.e2 = raw ? 0.0f : 0.51f / split;
+    return h;
+}
+// -|y|^2 / 2 raised by the row's part of the bound: the score's first term.  A
+// row outside FP16's range (non-finite points of chamfer_nn_min) has the operand
+// 0 and kHalfAlways, above any threshold.
+constexpr float kHalfAlways = 3e38f;
+__device__ __forceinline__ float half_norm(float s2, float e2, float es2, float ee2) {
+    return fmaf(e2, ee2, fmaf(s2, es2, -0.5f * s2));
+}
+
+// (|z|^2, |z| rounded up, |z - z~| rounded up, 0) from the float32 sums of
+// squares of a row's coordinates and of their rounding errors (at most 256
+// terms: relative error below 1.8e-5), the difference x - c included.
+__device__ __forceinline__ float4 half_stat(float s2, float e2) {
+    const float zn = sqrtf(s2 * 1.00004f) * 1.000001f + 1e-18f;
+    return make_float4(s2, zn, sqrtf(e2 * 1.00004f) * 1.000001f + zn * 1.3e-7f, 0.0f);
 }
 
 // Canonical float32 distance accumulator between rows a and b: k ascending,
@@ -381,27 +441,29 @@ hipError_t launch_setup(DevParams *p, uint32_t *lohi, int d, uint64_t seed, int 
 // rep: index of the independent LSH structure (0 for the single one)
 hipError_t launch_grid_tables(uint64_t seed, int L, int kh, float *zfrac, uint64_t *mult,
                               int rep, hipStream_t st);
-hipError_t launch_minmax(const float *X, int64_t n, int d, uint32_t *lohi, DevParams *p,
+hipError_t launch_minmax(const float *X, int64_t n, int d, bool isB, uint32_t *lohi, DevParams *p,
                          hipStream_t st);
-// The same over A and then B in one launch (two launches when either set
-// is not 16-byte aligned with d a multiple of 4).
+// The same over A and B in one launch (two when d > 2048).
 hipError_t launch_minmax_pair(const float *A, int64_t nA, const float *B, int64_t nB, int d,
                               uint32_t *lohi, DevParams *p, hipStream_t st);
-hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, hipStream_t st);
+// B (may be null): also the centre and scale of the l2 exact pass
+// (half_supported).  check: a non-finite coordinate sets the status.
+hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, const float *B, int64_t nB,
+                              bool check, hipStream_t st);
 hipError_t launch_table_fill(Bucket *tables, size_t count, hipStream_t st);
-// mode 0: insert B into the tables (l2: also |b|^2 into nb2_out and
-// p->b2max_rep when nb2_out is set); 1: probe A (CrudeNN); 2: write keys;
+// mode 0: insert B into the tables; 1: probe A (CrudeNN); 2: write keys;
 // 5: write B's keys for launch_part_build (duplicates within a wavefront
-// dropped; |b|^2 as mode 0);
-// 3 / 4: insert / probe with a window of W points per bucket (the tables
-// are then keys [L][cap] followed by members [L][cap][W]).  flags: kProbe*.
+// dropped); 3 / 4: insert / probe with a window of W points per bucket (the
+// tables are then keys [L][cap] followed by members [L][cap][W]).  Modes 0, 3
+// and 5 also write B's FP16 table of the l2 exact pass when half_out is set
+// (with nbh_out and the maxima in p).  flags: kProbe*.
 hipError_t launch_hash(int mode, const float *X, int64_t n, const float *Bpts, int64_t nB,
                        int d, int metric, int L, int ke, const uint32_t *lohi,
                        const int8_t *embed, const float *zfrac, const uint64_t *mult,
                        Bucket *tables, int log2cap, uint64_t *keys_out, float *D_out,
-                       int32_t *nn_out, int32_t *scale_out, float *nb2_out, DevParams *p,
-                       int W, int flags, hipStream_t st, uint16_t *split_out = nullptr,
-                       int split_dp = 0);
+                       int32_t *nn_out, int32_t *scale_out, float *nbh_out, DevParams *p,
+                       int W, int flags, hipStream_t st, uint16_t *half_out = nullptr,
+                       int half_dp = 0);
 // Bytes of the tables of L scales of 2^log2cap buckets with window W.
 size_t table_bytes(int L, int log2cap, int W);
 // The partitioned build of the W = 1 tables (no global atomics): keys of B
@@ -427,10 +489,10 @@ hipError_t launch_tables_empty(Bucket *tables, int L, int log2cap, int W, hipStr
 hipError_t launch_weights(const float *D, int64_t nA, int q, uint64_t *blocksums, uint64_t *Ploc,
                           DevParams *p, hipStream_t st);
 // Draws from P_a = offs[a / kScanBlock] + Ploc_a (launch_weights' outputs;
-// q as for launch_weights).
+// q as for launch_weights); best[l] and gthr[c T + l], c < copies, are reset.
 hipError_t launch_sample(uint64_t seed, const uint64_t *Ploc, const uint64_t *offs, int64_t nA,
-                         int64_t T, int q, int32_t *idx, unsigned long long *best, DevParams *p,
-                         hipStream_t st);
+                         int64_t T, int q, int32_t *idx, unsigned long long *best, uint32_t *gthr,
+                         int copies, DevParams *p, hipStream_t st);
 hipError_t launch_estimate_final(const unsigned long long *best, const int32_t *idx,
                                  const float *D, int64_t T, int metric, DevParams *p,
                                  double *eta_out, chamfer_aux aux, hipStream_t st);
@@ -441,32 +503,37 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long 
 hipError_t launch_nnmin(const float *X, const int32_t *rows, int64_t nx, const float *B,
                         int64_t nB, int d, int metric, unsigned long long *best, DevParams *p,
                         hipStream_t st);
-// The l2 exact pass on the BF16 matrix cores (12 <= d <= 256) with a two-term
-// split of every coordinate: launch_rownorm (or the hash of B) fills nb2 and
-// p->b2max_rep, launch_split_rows (or the hash of B) the split table of B
-// (split_table_bytes), then launch_nnmin_split returns the canonical float32
-// minima.
-bool mfma_supported(int d, int metric);
-hipError_t launch_rownorm(const float *B, int64_t nB, int d, float *nb2, DevParams *p,
-                          hipStream_t st);
-size_t split_table_bytes(int64_t nB, int d);
-int64_t split_blocks(int64_t nB, int d);
-hipError_t launch_split_rows(const float *B, int64_t nB, int d, uint16_t *out,
-                             const DevParams *p, hipStream_t st);
-// The queries' split table (rows X[rows[i]], i < nx) and their |x|^2.
-hipError_t launch_split_queries(const float *X, const int32_t *rows, int64_t nx, int d,
-                                uint16_t *out, float *n2, const DevParams *p, hipStream_t st);
-// Xs, xn2: the queries' split table and norms (launch_split_queries).
-// rec (may be null): split_record_bytes(nx, nB, d) bytes for the deferred
-// form of launches over fewer than 16384 queries (the pass records its
-// chunk candidates, a second kernel certifies them per query and lists the
-// chunks to rescan, a third rescans them); null, or a launch over more
-// queries, certifies inside the pass.
-size_t split_record_bytes(int64_t nx, int64_t nB, int d);
-hipError_t launch_nnmin_split(const float *X, const int32_t *rows, int64_t nx, const uint16_t *Xs,
-                              const float *xn2, const float *B, const uint16_t *Bs, int64_t nB,
-                              int d, unsigned long long *best, const float *nb2, DevParams *p,
-                              hipStream_t st, uint4 *rec = nullptr);
+// The l2 exact pass on the FP16 matrix cores (d <= 10 and 12 <= d <= 256),
+// after launch_calib_final with B: for d >= 12 (half_tabled) launch_half_rows
+// writes the tables (half_table_bytes) of B (unless the hash of B did: nbh,
+// bs) and of the queries (rows X[rows[i]], i < nx, or X[i]; xs, stat), then
+// launch_nnmin_half returns the canonical float32 minima.  seed (may be
+// null): seed[row of X] bounds the query's distance from above.  best [nx] and
+// gthr [copies][nx] (the thresholds known so far) start as all ones; copies is 8 (one
+// per XCD) or 1.
+// Copies for an estimate's draws (gthr lies in table space that is dead by then;
+// the passes over all points keep to one).  A few thousand queries are in use by
+// all XCDs at once, and their thresholds lie on few cache lines: each XCD gets a
+// copy, used through its own L2, unless B is large and the queries many, where a
+// threshold known to all XCDs is worth more than the contention costs (exact pass
+// of 2000 draws over 10^6 x 128 points: 605 us with 8 copies, 547 with 1; whole
+// call with 300 draws over 3 10^5 x 128: 466 and 480).  With many queries the XCDs
+// work on different ones at a time.
+__host__ __device__ inline int half_copies(int64_t nx, int64_t nB) {
+    return nx < 16384 && (nB < 262144 || nx < 1024) ? 8 : 1;
+}
+bool half_supported(int d, int metric);
+bool half_tabled(int d);
+size_t half_table_bytes(int64_t n, int d);
+int64_t half_row_blocks(int64_t n, int d, bool isB);
+hipError_t launch_half_rows(const float *B, int64_t nB, uint16_t *bs, float *nbh, const float *X,
+                            const int32_t *rows, int64_t nx, uint16_t *xs, float4 *stat, int d,
+                            const uint32_t *lohi, DevParams *p, hipStream_t st);
+hipError_t launch_nnmin_half(const float *X, const int32_t *rows, int64_t nx, const uint16_t *Xs,
+                             const float4 *stat, const float *seed, const float *B,
+                             const uint16_t *Bs, int64_t nB, int d, const float *nbh,
+                             const uint32_t *lohi, unsigned long long *best, uint32_t *gthr,
+                             int copies, DevParams *p, hipStream_t st);
 // Low-precision (BF16 / FP8-E4M3) l2 nearest neighbours with float32 re-rank.
 int lowp_dpad(int d, int precision);
 bool lowp_supported(int d, int metric, int precision);
@@ -496,9 +563,10 @@ int nn_finalize_blocks(int64_t nx);
 int64_t init_blocks(int d);
 int64_t grid_table_blocks(int L, int kh);
 int64_t table_fill_blocks(size_t count);
-// minmax over n rows: float4 form when vec4; stride in elements (or float4)
-void minmax_geom(int64_t n, int d, bool vec4, int64_t *blocks, int64_t *stride);
-bool minmax_vec4(const float *X, int d);
+// minmax over n rows: the 16-byte form when wide (d <= 2048), stride in float4;
+// else in elements
+void minmax_geom(int64_t n, int d, bool wide, int64_t *blocks, int64_t *stride);
+bool minmax_wide(int d);
 int64_t hash_blocks(int64_t n);
 int64_t scan_blocks(int64_t nA);
 int64_t sample_blocks(int64_t T);
@@ -509,8 +577,8 @@ struct NNGeom {
 };
 // target: workgroups the split of B aims for (0: the direct-launch target)
 NNGeom valu_geom(int64_t nx, int64_t nB, int d, int64_t target = 0);
-NNGeom split_geom(int64_t nx, int64_t nB, int d, int64_t target = 0);
-int64_t split_target_wgs(int d);  // the direct-launch target of split_geom
+NNGeom half_geom(int64_t nx, int64_t nB, int d, int64_t target = 0);
+int64_t half_target_wgs(int d);  // the direct-launch target of half_geom
 constexpr int64_t kValuTargetWGs = 4096;
 NNGeom lowp_geom(int64_t nx, int64_t nB, int d, int precision);
 constexpr int kMaxLdsL1Dim = 240;  // widest l1 tile staged in LDS by the hash
@@ -527,8 +595,8 @@ hipError_t launch_batch_weights(const Batch *bt, hipStream_t st);
 hipError_t launch_batch_sample(const Batch *bt, hipStream_t st);
 hipError_t launch_batch_cast(const Batch *bt, int d, int precision, hipStream_t st);
 hipError_t launch_batch_nn(const Batch *bt, int d, int metric, int precision, hipStream_t st);
-hipError_t launch_batch_split_rows(const Batch *bt, hipStream_t st);
-hipError_t launch_batch_split(const Batch *bt, int d, hipStream_t st);
+hipError_t launch_batch_half_rows(const Batch *bt, hipStream_t st);
+hipError_t launch_batch_half(const Batch *bt, int d, hipStream_t st);
 hipError_t launch_batch_lowp(const Batch *bt, int d, int precision, hipStream_t st);
 hipError_t launch_batch_final(const Batch *bt, int metric, hipStream_t st);
 

@@ -154,7 +154,8 @@ constexpr int kFences = 1024;
 __device__ __forceinline__ void sample(uint64_t seed, const unsigned long long *__restrict__ Ploc,
                                        const unsigned long long *__restrict__ offs, int64_t nA,
                                        int64_t T, int32_t *idx, unsigned long long *best,
-                                       DevParams *p, int q, bool local, Blk blk) {
+                                       uint32_t *gthr, int copies, DevParams *p, int q, bool local,
+                                       Blk blk) {
     __shared__ unsigned long long fence[kFences];
     __shared__ unsigned long long boff[kOffsLds];
     __shared__ unsigned long long sbuf[4];
@@ -210,6 +211,7 @@ __device__ __forceinline__ void sample(uint64_t seed, const unsigned long long *
     __syncthreads();
     if (l >= T) return;
     best[l] = ~0ull;
+    for (int c = 0; c < copies; ++c) gthr[c * T + l] = 0xffffffffu;
     if (!ok) {
         idx[l] = 0;
         return;
@@ -252,22 +254,22 @@ __global__ __launch_bounds__(256) void k_sample(uint64_t seed,
                                                 const unsigned long long *__restrict__ Ploc,
                                                 const unsigned long long *__restrict__ offs,
                                                 int64_t nA, int64_t T, int32_t *idx,
-                                                unsigned long long *best, DevParams *p, int q,
-                                                int local) {
-    sample(seed, Ploc, offs, nA, T, idx, best, p, q, local != 0, grid_blk());
+                                                unsigned long long *best, uint32_t *gthr,
+                                                int copies, DevParams *p, int q, int local) {
+    sample(seed, Ploc, offs, nA, T, idx, best, gthr, copies, p, q, local != 0, grid_blk());
 }
 
 int64_t sample_blocks(int64_t T) { return (T + 255) / 256; }
 
 hipError_t launch_sample(uint64_t seed, const uint64_t *Ploc, const uint64_t *offs, int64_t nA,
-                         int64_t T, int q, int32_t *idx, unsigned long long *best, DevParams *p,
-                         hipStream_t st) {
+                         int64_t T, int q, int32_t *idx, unsigned long long *best, uint32_t *gthr,
+                         int copies, DevParams *p, hipStream_t st) {
     const bool local = sample_scans(nA);
     if (T <= 0 && !local) return hipSuccess;
     // with T <= 0 one workgroup still stores W and s
     k_sample<<<(unsigned)(T > 0 ? sample_blocks(T) : 1), 256, 0, st>>>(
         seed, reinterpret_cast<const unsigned long long *>(Ploc),
-        reinterpret_cast<const unsigned long long *>(offs), nA, T, idx, best, p, q,
+        reinterpret_cast<const unsigned long long *>(offs), nA, T, idx, best, gthr, copies, p, q,
         local ? 1 : 0);
     return hipGetLastError();
 }
@@ -397,7 +399,7 @@ __global__ __launch_bounds__(1024) void kb_wscan(const Batch *__restrict__ bt) {
 
 __global__ __launch_bounds__(256) void kb_sample(const Batch *__restrict__ bt) {
     batch_loop(bt, kBsSample, [&](const Job &J, Blk b) {
-        sample(J.seed, J.P, J.blocksums, J.nA, J.T, J.idx, J.best, J.p, J.q, false, b);
+        sample(J.seed, J.P, J.blocksums, J.nA, J.T, J.idx, J.best, J.gthr, J.thr_copies, J.p, J.q, false, b);
     });
 }
 
