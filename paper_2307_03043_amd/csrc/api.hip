@@ -122,6 +122,15 @@ int64_t default_samples(int64_t nA, double eps) {
     return T < 1 ? 1 : T;
 }
 
+// Whether the exact pass takes the l1 byte form, and whether it needs a box or
+// centre of B (launch_calib_final).
+bool sad_pass(int64_t nx, int64_t nB, int d, int metric) {
+    return sad_supported(d, metric) && sad_pays(nx, nB, d);
+}
+bool boxed(int64_t nx, int64_t nB, int d, int metric) {
+    return half_supported(d, metric) || sad_pass(nx, nB, d, metric);
+}
+
 // Validate and lay out the workspace.  estimating: the entry point draws T
 // points (needs eps, the weight, prefix and draw regions) and, with
 // importance sampling, runs CrudeNN (the table regions); otherwise only the
@@ -189,12 +198,16 @@ int make_plan(Plan &pl, int64_t nA, int64_t nB, int32_t d, int32_t metric, doubl
     // thresholds of the l2 exact pass: the draws' live in the hash tables'
     // region (done with by then), in copies where they fit; otherwise one copy
     // right after best, so that one fill resets both
-    const size_t gb = !lowp_supported(d, metric, o.precision) && half_supported(d, metric)
-                          ? (size_t)(estimating ? pl.T : nA) * sizeof(uint32_t)
-                          : 0;
     const size_t room = h ? table_bytes(pl.L, lc, pl.window) : 0;
-    pl.thr_copies = gb == 0 ? 0 : half_copies(pl.T, nB);
-    if (pl.thr_copies * gb > room) pl.thr_copies = 1;
+    size_t gb = (size_t)(estimating ? pl.T : nA) * sizeof(uint32_t);
+    if (!lowp_supported(d, metric, o.precision) && half_supported(d, metric)) {
+        pl.thr_copies = half_copies(pl.T, nB);
+        if (pl.thr_copies * gb > room) pl.thr_copies = 1;
+    } else if (sad_supported(d, metric) && (gb <= room || !estimating)) {
+        pl.thr_copies = 1;
+    } else {
+        gb = 0;
+    }
     pl.off_gthr = gb <= room ? pl.off_tables : take(gb);
     pl.off_partial = take((size_t)(nn_finalize_blocks(nrow) + 1) * sizeof(double));
     // low precision: cast rows of B and of the queries, scales and norms;
@@ -263,8 +276,8 @@ int hash_prologue(const Plan &pl, const float *A, const float *B, uint64_t seed,
                               hipMemcpyHostToDevice, st));
     }
     CH_TRY(launch_minmax_pair(A, pl.nA, B, pl.nB, pl.d, lohi, p, st));
-    CH_TRY(launch_calib_final(lohi, pl.d, p, half_supported(pl.d, pl.metric) ? B : nullptr, pl.nB,
-                              true, st));
+    const float *box = boxed(pl.T, pl.nB, pl.d, pl.metric) ? B : nullptr;
+    CH_TRY(launch_calib_final(lohi, pl.d, p, box, pl.nB, pl.metric, true, st));
     return CHAMFER_OK;
 }
 
@@ -371,6 +384,11 @@ int nn_pass(const Plan &pl, void *ws, const float *X, const int32_t *rows, int64
                                  at<uint32_t>(ws, pl.off_gthr), pl.thr_copies, p, st));
         return CHAMFER_OK;
     }
+    if (sad_pass(nx, nB, pl.d, pl.metric)) {
+        CH_TRY(launch_nnmin_sad(X, rows, nx, seed, B, nB, pl.d, at<uint32_t>(ws, pl.off_lohi), best,
+                                pl.thr_copies ? at<uint32_t>(ws, pl.off_gthr) : nullptr, p, st));
+        return CHAMFER_OK;
+    }
     CH_TRY(launch_nnmin(X, rows, nx, B, nB, pl.d, pl.metric, best, p, st));
     return CHAMFER_OK;
 }
@@ -445,7 +463,7 @@ int job_prepare(const float *A, const float *B, int64_t nA, int64_t nB, int32_t 
     J.xhalf = tabled ? at<uint16_t>(ws, pl.off_xhalf) : nullptr;
     J.nbh = tabled ? at<float>(ws, pl.off_nbh) : nullptr;
     J.xstat = tabled ? at<float4>(ws, pl.off_xstat) : nullptr;
-    J.gthr = half ? at<uint32_t>(ws, pl.off_gthr) : nullptr;
+    J.gthr = pl.thr_copies ? at<uint32_t>(ws, pl.off_gthr) : nullptr;
     J.thr_copies = pl.thr_copies;
     J.eta = eta;
     J.aux = aux;
@@ -476,6 +494,8 @@ int job_prepare(const float *A, const float *B, int64_t nA, int64_t nB, int32_t 
             J.nb_castX = (int32_t)half_row_blocks(pl.T, d, false);
         }
         g = half_geom(pl.T, nB, d);
+    } else if (sad_supported(d, metric)) {
+        g = sad_geom(pl.T, nB, d, 0, J.nn_qw);
     } else {
         g = valu_geom(pl.T, nB, d);
     }
@@ -505,15 +525,18 @@ void job_share_nn(Job *jobs, int n) {
     if (n <= 1) return;
     const Job &J0 = jobs[0];
     if (lowp_supported(J0.d, J0.metric, J0.precision)) return;
-    const bool half = half_supported(J0.d, J0.metric);
+    const bool half = half_supported(J0.d, J0.metric), sad = sad_supported(J0.d, J0.metric);
     double total = 0.0;
     for (int j = 0; j < n; ++j) total += (double)jobs[j].T * (double)jobs[j].nB;
-    const double target = half ? (double)half_target_wgs(J0.d) : (double)kValuTargetWGs;
+    const double target =
+        half || sad ? (double)half_target_wgs(J0.d) : (double)kValuTargetWGs;
     for (int j = 0; j < n; ++j) {
         Job &J = jobs[j];
         const double share = target * ((double)J.T * (double)J.nB) / total;
         const int64_t t = share < 1.0 ? 1 : (int64_t)std::ceil(share);
-        const NNGeom g = half ? half_geom(J.T, J.nB, J.d, t) : valu_geom(J.T, J.nB, J.d, t);
+        const NNGeom g = half  ? half_geom(J.T, J.nB, J.d, t)
+                         : sad ? sad_geom(J.T, J.nB, J.d, t, J.nn_qw)
+                               : valu_geom(J.T, J.nB, J.d, t);
         J.nn_chunk = g.chunk;
         J.nn_nchunk = g.nchunk;
         J.nb_nn = (int32_t)g.blocks;
@@ -608,7 +631,8 @@ int chamfer_exact(const float *A, const float *B, int64_t n_A, int64_t n_B, int3
     double *partial = at<double>(ws, pl.off_partial);
     CH_TRY(launch_init_params(p, lohi, d, st));
     CH_TRY(launch_minmax_pair(A, n_A, B, n_B, d, lohi, p, st));
-    CH_TRY(launch_calib_final(lohi, d, p, half_supported(d, metric) ? B : nullptr, n_B, true, st));
+    const float *box = boxed(n_A, n_B, d, metric) ? B : nullptr;
+    CH_TRY(launch_calib_final(lohi, d, p, box, n_B, metric, true, st));
     CH_TRY(launch_fill_u64(best, reset_words(pl), ~0ull, st));
     if ((rc = nn_pass(pl, ws, A, nullptr, n_A, B, n_B, best, p, st))) return rc;
     CH_TRY(launch_nn_finalize(best, n_A, metric, rowmin_out, rownn_out, partial, p, st));
@@ -628,13 +652,13 @@ int chamfer_nn_min(const float *X, const int32_t *rows, int64_t n_x, const float
     hipStream_t st = static_cast<hipStream_t>(stream);
     DevParams *p = at<DevParams>(ws, pl.off_params);
     auto *best = at<unsigned long long>(ws, pl.off_best);
-    if (!lowp_supported(d, metric, pl.precision) && half_supported(d, metric)) {
+    if (!lowp_supported(d, metric, pl.precision) && boxed(n_x, n_B, d, metric)) {
         // the scale and centre of the exact pass, from B alone (the number of
         // rows of X is not known here); inputs are not checked
         uint32_t *lohi = at<uint32_t>(ws, pl.off_lohi);
         CH_TRY(launch_init_params(p, lohi, d, st));
         CH_TRY(launch_minmax(B, n_B, d, true, lohi, p, st));
-        CH_TRY(launch_calib_final(lohi, d, p, B, n_B, false, st));
+        CH_TRY(launch_calib_final(lohi, d, p, B, n_B, metric, false, st));
     } else {
         CH_TRY(launch_init_params(p, nullptr, d, st));
     }
@@ -693,8 +717,8 @@ int chamfer_estimate(const float *A, const float *B, int64_t n_A, int64_t n_B, i
         CH_TRY(mark(ev, 0, st));
         CH_TRY(launch_init_params(p, lohi, d, st));
         CH_TRY(launch_minmax_pair(A, n_A, B, n_B, d, lohi, p, st));
-        CH_TRY(launch_calib_final(lohi, d, p, half_supported(d, metric) ? B : nullptr, n_B, true,
-                                  st));
+        const float *box = boxed(pl.T, n_B, d, metric) ? B : nullptr;
+        CH_TRY(launch_calib_final(lohi, d, p, box, n_B, metric, true, st));
         CH_TRY(mark(ev, 1, st));
         CH_TRY(mark(ev, 2, st));
         CH_TRY(launch_unit_weights(D, ax.crude_nn, scale, n_A, p, st));

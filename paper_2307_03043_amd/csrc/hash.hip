@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256) void k_minmax(const float *__restrict__ X, int
 // is kept in C copies that lanes pick by id (minmax_copies) and folds them at
 // the end.  d = 3, 2 10^5 rows: 19.2 us with 4-byte loads, see minmax_geom.
 __host__ __device__ inline int minmax_copies(int d) {
-    return d <= 64 ? 16 : d <= 256 ? 2 : 1;
+    return d <= 16 ? 16 : d <= 32 ? 4 : d <= 64 ? 2 : 1;
 }
 inline size_t minmax_lds(int d) { return (size_t)minmax_copies(d) * 2 * d * sizeof(uint32_t); }
 
@@ -283,23 +283,29 @@ hipError_t launch_minmax_pair(const float *A, int64_t nA, const float *B, int64_
 // of up to 16 rows spread over B (any c is valid; near the mean it keeps the
 // operands, and so their rounding errors, small), the scale 2^he that takes the
 // largest |b_k - c_k| to [2^10, 2^11) (less where A's largest would leave
-// [0, 2^15); rows that were not in the min/max may be 2^5 times larger), and for d <= kHalfRawDim the corner distance of
-// B's box from c, which bounds |y|.
+// [0, 2^15); rows that were not in the min/max may be 2^5 times larger), and for
+// d <= kHalfRawDim the corner distance of B's box from c, which bounds |y|; or
+// for l1 the corner and the step of the byte differences.
 __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
-                                          const float *__restrict__ B, int64_t nB) {
+                                          const float *__restrict__ B, int64_t nB, int metric) {
     __shared__ uint32_t mxs, mbs;
     __shared__ float box[kHalfRawDim];
     if (threadIdx.x == 0) mxs = mbs = 0u;
     __syncthreads();
+    float corner = 0.0f, low = 0.0f;  // l1: of coordinate threadIdx.x (d <= blockDim.x)
     for (int k = threadIdx.x; k < d; k += blockDim.x) {
-        float c = 0.0f;
+        float c = 0.0f, smin = INFINITY, smax = -INFINITY;
         if (B) {
             // up to 16 rows in one batch of loads (rows repeat when nB < 16)
             float v[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) v[i] = ro(B)[(nB * i / 16) * d + k];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) c += v[i] * 0.0625f;
+            for (int i = 0; i < 16; ++i) {
+                c += v[i] * 0.0625f;
+                smin = fminf(smin, v[i]);
+                smax = fmaxf(smax, v[i]);
+            }
             if (!isfinite(c)) c = 0.0f;
         }
         uint32_t lo[2], hi[2];
@@ -317,20 +323,41 @@ __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
         lohi[k] = min(lo[0], lo[1]);
         lohi[d + k] = max(hi[0], hi[1]);
         if (B) {
-            lohi[2 * d + k] = __float_as_uint(c);
             const float hb = ordered_to_float(hi[1]), lb = ordered_to_float(lo[1]);
-            const float mb = isfinite(hb) && isfinite(lb) ? fmaxf(hb - c, c - lb) : INFINITY;
-            const float ma = fmaxf(ordered_to_float(max(hi[0], hi[1])) - c,
-                                   c - ordered_to_float(min(lo[0], lo[1])));
-            atomicMax(&mxs, __float_as_uint(fabsf(ma)));
-            atomicMax(&mbs, __float_as_uint(fabsf(mb)));
-            if (k < kHalfRawDim) box[k] = mb;
+            float m, b;
+            if (metric == CHAMFER_L1) {
+                low = lb;
+                corner = smin;
+                m = hb - lb;
+                b = smax - smin;
+            } else {
+                lohi[2 * d + k] = __float_as_uint(c);
+                b = isfinite(hb) && isfinite(lb) ? fmaxf(hb - c, c - lb) : INFINITY;
+                m = fmaxf(ordered_to_float(max(hi[0], hi[1])) - c,
+                          c - ordered_to_float(min(lo[0], lo[1])));
+                if (k < kHalfRawDim) box[k] = b;
+            }
+            atomicMax(&mxs, __float_as_uint(fabsf(m)));
+            atomicMax(&mbs, __float_as_uint(fabsf(b)));
         }
     }
     __syncthreads();
-    if (B && threadIdx.x == blockDim.x - 1) {
-        const float M = __uint_as_float(mxs);
-        const float MB = __uint_as_float(mbs);
+    if (B == nullptr) return;
+    const float M = __uint_as_float(mxs), MB = __uint_as_float(mbs);
+    if (metric == CHAMFER_L1) {
+        // MB: the widest of the sampled rows, M: of all.  Rows far out would make
+        // the steps too wide for all others: beyond 8 to 1 the box is that of the
+        // samples and half their width around it, and rows outside are clamped
+        const bool all = !(M > 8.0f * MB) || MB == 0.0f;
+        if ((int)threadIdx.x < d)
+            lohi[2 * d + threadIdx.x] =
+                __float_as_uint(all ? low : fmaxf(low, corner - 0.5f * MB));
+        if (threadIdx.x == 0) {
+            const float inv = 254.9997f / (all ? M : 2.0f * MB);
+            p->sad_inv = inv > 0.0f && inv < 1e30f ? inv : 0.0f;
+            p->sad_in = all;
+        }
+    } else if (threadIdx.x == blockDim.x - 1) {
         int he = 0;
         if (M > 0.0f && isfinite(M)) {
             he = 14 - ilogbf(M);
@@ -349,7 +376,7 @@ __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
 }
 
 __global__ void k_calib_final_wide(uint32_t *lohi, int d, DevParams *p, bool check) {
-    fold_lohi(lohi, d, p, nullptr, 0);
+    fold_lohi(lohi, d, p, nullptr, 0, 0);
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     double S = 0.0;
     for (int k = 0; k < d; ++k)
@@ -363,9 +390,11 @@ __global__ void k_calib_final_wide(uint32_t *lohi, int d, DevParams *p, bool che
 // The per-coordinate spans are gathered in parallel; one thread sums them
 // in order.
 __device__ __forceinline__ void calib_final(uint32_t *lohi, int d, DevParams *p,
-                                            const float *__restrict__ B, int64_t nB, bool check) {
+                                            const float *__restrict__ B, int64_t nB, int metric,
+                                            bool check) {
     extern __shared__ double span[];
-    fold_lohi(lohi, d, p, B, nB);
+    fold_lohi(lohi, d, p, B, nB, metric);
+    __syncthreads();
     for (int k = threadIdx.x; k < d; k += blockDim.x)
         span[k] = (double)ordered_to_float(lohi[d + k]) - (double)ordered_to_float(lohi[k]);
     __syncthreads();
@@ -379,12 +408,12 @@ __device__ __forceinline__ void calib_final(uint32_t *lohi, int d, DevParams *p,
 
 __global__ __launch_bounds__(256) void k_calib_final(uint32_t *lohi, int d, DevParams *p,
                                                      const float *__restrict__ B, int64_t nB,
-                                                     bool check) {
-    calib_final(lohi, d, p, B, nB, check);
+                                                     int metric, bool check) {
+    calib_final(lohi, d, p, B, nB, metric, check);
 }
 
 hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, const float *B, int64_t nB,
-                              bool check, hipStream_t st) {
+                              int metric, bool check, hipStream_t st) {
     if ((size_t)d * sizeof(double) > 60000) {
         // very wide points: spans recomputed by the summing thread
         if (B != nullptr) return hipErrorInvalidValue;
@@ -392,7 +421,7 @@ hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, const float *
         return hipGetLastError();
     }
     if (B != nullptr && nB < 1) return hipErrorInvalidValue;
-    k_calib_final<<<1, 256, (size_t)d * sizeof(double), st>>>(lohi, d, p, B, nB, check);
+    k_calib_final<<<1, 256, (size_t)d * sizeof(double), st>>>(lohi, d, p, B, nB, metric, check);
     return hipGetLastError();
 }
 
@@ -1898,8 +1927,7 @@ __global__ __launch_bounds__(256) void kb_minmax(const Batch *__restrict__ bt) {
 
 __global__ __launch_bounds__(256) void kb_calib(const Batch *__restrict__ bt) {
     batch_loop(bt, kBsCalib, [&](const Job &J, Blk) {
-        const bool half = J.metric == CHAMFER_L2 && J.d <= 256;
-        calib_final(J.lohi, J.d, J.p, half ? J.B : nullptr, J.nB, true);
+        calib_final(J.lohi, J.d, J.p, J.d <= 256 ? J.B : nullptr, J.nB, J.metric, true);
     });
 }
 

@@ -48,8 +48,9 @@ struct DevParams {
     uint32_t fallbacks;  // 32-row blocks the l2 exact pass evaluated in full
     int32_t he;          // l2 exact pass: the operands' scale is 2^he
     float half_box;      // l2 exact pass: upper bound of |(b - centre) 2^he| over B (d <= 10)
+    float sad_inv;       // l1 exact pass: byte steps per unit (0: the bytes tell nothing)
+    int32_t sad_in;      // l1 exact pass: every row of B lies in the bytes' box
     uint32_t pad32[1];
-    uint64_t pad[1];
     // The maxima of D_a and (l2 exact pass) of |y|^2 and |y - y~|^2 (words 0
     // and 1 of a replica) reduced over thousands of workgroups: each
     // workgroup's atomicMax goes to replica (id mod kMaxRepl), one 128-byte
@@ -129,7 +130,7 @@ struct Plan {
     // problem
     int64_t nA, nB, T;
     int32_t d, metric, L, ke, kh, q, precision, window, reps, sampling;
-    int32_t thr_copies;  // of the l2 exact pass's thresholds (0: it keeps none)
+    int32_t thr_copies;  // of the exact pass's thresholds (0: it keeps none)
     uint64_t seed;
     int log2cap;  // per-scale table capacity is 2^log2cap
     bool part;    // B's tables come from the partitioned build (W = 1)
@@ -201,6 +202,7 @@ struct Job {
     float4 *xstat;
     uint32_t *gthr;  // float32 l2: thresholds of the exact pass
     int32_t thr_copies;
+    int32_t nn_qw;  // l1: wavefronts of a workgroup with queries of their own
     double *eta;
     chamfer_aux aux;
     // geometry
@@ -336,6 +338,77 @@ __device__ __forceinline__ float4 half_stat(float s2, float e2) {
     return make_float4(s2, zn, sqrtf(e2 * 1.00004f) * 1.000001f + zn * 1.3e-7f, 0.0f);
 }
 
+// Canonical float32 accumulators of M pairs of rows x and b, each with LPH
+// consecutive lanes: lane s holds coordinates [s S, (s + 1) S), S <= 16, of both
+// rows (one batch of loads for all pairs) and continues the sum of lane s - 1, so
+// the terms are added in coordinate order.  The results are in the last lane.
+// All lanes must call it.
+template <int METRIC, int LPH, int MAXD, int M>
+__device__ __forceinline__ void hit_acc(const float *const *x, const float *const *b, int d,
+                                        float *out) {
+    constexpr int N = LPH == 1 ? MAXD : 16;  // coordinates per lane, at most
+    // opaque: what follows from them is rare work whose lane masks must not be
+    // hoisted into (and spilled around) the caller's tile loop
+    int s = (threadIdx.x & 63) % LPH;
+    asm volatile("" : "+v"(s), "+s"(d));
+    const int S = LPH == 1 ? d : (d + 4 * LPH - 1) / (4 * LPH) * 4;
+    const int k0 = s * S, k1 = min(d, k0 + S);
+    float t[M][N];  // zero past the lane's coordinates: adds nothing
+    uintptr_t low = 0;
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+        low |= reinterpret_cast<uintptr_t>(x[m]) | reinterpret_cast<uintptr_t>(b[m]);
+    if (LPH > 1 && (d & 3) == 0 && (low & 15) == 0) {
+        float4 u[M][N / 4 > 0 ? N / 4 : 1], v[M][N / 4 > 0 ? N / 4 : 1];
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int i = 0; i < N / 4; ++i) {
+                const int k = max(min(k0 + 4 * i, d - 4), 0);
+                u[m][i] = ld(reinterpret_cast<const CH_RO float4 *>(ro(x[m]) + k));
+                v[m][i] = ld(reinterpret_cast<const CH_RO float4 *>(ro(b[m]) + k));
+            }
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int i = 0; i < N / 4; ++i) {  // d, S multiples of 4: whole quads
+                const bool in = k0 + 4 * i < k1;
+                t[m][4 * i] = in ? u[m][i].x - v[m][i].x : 0.0f;
+                t[m][4 * i + 1] = in ? u[m][i].y - v[m][i].y : 0.0f;
+                t[m][4 * i + 2] = in ? u[m][i].z - v[m][i].z : 0.0f;
+                t[m][4 * i + 3] = in ? u[m][i].w - v[m][i].w : 0.0f;
+            }
+    } else {
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int k = min(k0 + i, d - 1);
+                const float u = ro(x[m])[k] - ro(b[m])[k];
+                t[m][i] = k0 + i < k1 ? u : 0.0f;
+            }
+    }
+    // a loop, not unrolled: this code runs once or twice per workgroup and its
+    // time is that of fetching its instructions
+#pragma unroll
+    for (int m = 0; m < M; ++m) out[m] = 0.0f;
+#pragma unroll 1
+    for (int q = 0; q < LPH; ++q) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            // the lane below's sum (row shift right by one: LPH <= 16 lanes of a row)
+            float sum = LPH > 1 ? __uint_as_float(__builtin_amdgcn_update_dpp(
+                                      0u, __float_as_uint(out[m]), 0x111, 0xf, 0xf, true))
+                                : 0.0f;
+            if (q == 0) sum = 0.0f;
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                sum = METRIC == CHAMFER_L1 ? sum + fabsf(t[m][i]) : fmaf(t[m][i], t[m][i], sum);
+            out[m] = s == q ? sum : out[m];
+        }
+    }
+}
+
 // Canonical float32 distance accumulator between rows a and b: k ascending,
 // one rounding per operation; l1: acc + |a_k - b_k|, l2: fma(t, t, acc) with
 // t = a_k - b_k (the caller takes the square root for l2).  Loads are issued
@@ -447,9 +520,10 @@ hipError_t launch_minmax(const float *X, int64_t n, int d, bool isB, uint32_t *l
 hipError_t launch_minmax_pair(const float *A, int64_t nA, const float *B, int64_t nB, int d,
                               uint32_t *lohi, DevParams *p, hipStream_t st);
 // B (may be null): also the centre and scale of the l2 exact pass
-// (half_supported).  check: a non-finite coordinate sets the status.
+// (half_supported) or the corner and step of the l1 exact pass (sad_supported).
+// check: a non-finite coordinate sets the status.
 hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, const float *B, int64_t nB,
-                              bool check, hipStream_t st);
+                              int metric, bool check, hipStream_t st);
 hipError_t launch_table_fill(Bucket *tables, size_t count, hipStream_t st);
 // mode 0: insert B into the tables; 1: probe A (CrudeNN); 2: write keys;
 // 5: write B's keys for launch_part_build (duplicates within a wavefront
@@ -535,6 +609,17 @@ hipError_t launch_nnmin_half(const float *X, const int32_t *rows, int64_t nx, co
                              const uint32_t *lohi, unsigned long long *best, uint32_t *gthr,
                              int copies, DevParams *p, hipStream_t st);
 // Low-precision (BF16 / FP8-E4M3) l2 nearest neighbours with float32 re-rank.
+// The l1 exact pass on byte differences (9 <= d <= 256), after launch_calib_final
+// with B: returns the canonical float32 minima.  seed (may be null): seed[row of X]
+// bounds the query's distance from above.  best [nx] and gthr [nx] (may be null)
+// start as all ones.
+constexpr int kSadMinDim = 8;
+bool sad_supported(int d, int metric);
+bool sad_pays(int64_t nx, int64_t nB, int d);  // against launch_nnmin, direct launches
+hipError_t launch_nnmin_sad(const float *X, const int32_t *rows, int64_t nx, const float *seed,
+                            const float *B, int64_t nB, int d, const uint32_t *lohi,
+                            unsigned long long *best, uint32_t *gthr, DevParams *p,
+                            hipStream_t st);
 int lowp_dpad(int d, int precision);
 bool lowp_supported(int d, int metric, int precision);
 size_t lowp_row_bytes(int d, int precision);
@@ -578,6 +663,7 @@ struct NNGeom {
 // target: workgroups the split of B aims for (0: the direct-launch target)
 NNGeom valu_geom(int64_t nx, int64_t nB, int d, int64_t target = 0);
 NNGeom half_geom(int64_t nx, int64_t nB, int d, int64_t target = 0);
+NNGeom sad_geom(int64_t nx, int64_t nB, int d, int64_t target, int32_t &qw);
 int64_t half_target_wgs(int d);  // the direct-launch target of half_geom
 constexpr int64_t kValuTargetWGs = 4096;
 NNGeom lowp_geom(int64_t nx, int64_t nB, int d, int precision);
@@ -595,6 +681,7 @@ hipError_t launch_batch_weights(const Batch *bt, hipStream_t st);
 hipError_t launch_batch_sample(const Batch *bt, hipStream_t st);
 hipError_t launch_batch_cast(const Batch *bt, int d, int precision, hipStream_t st);
 hipError_t launch_batch_nn(const Batch *bt, int d, int metric, int precision, hipStream_t st);
+hipError_t launch_batch_sad(const Batch *bt, int d, hipStream_t st);
 hipError_t launch_batch_half_rows(const Batch *bt, hipStream_t st);
 hipError_t launch_batch_half(const Batch *bt, int d, hipStream_t st);
 hipError_t launch_batch_lowp(const Batch *bt, int d, int precision, hipStream_t st);

@@ -400,6 +400,7 @@ static hipError_t batch_valu(const Batch *bt, int d, hipStream_t st) {
 hipError_t launch_batch_nn(const Batch *bt, int d, int metric, int precision, hipStream_t st) {
     if (lowp_supported(d, metric, precision)) return launch_batch_lowp(bt, d, precision, st);
     if (half_supported(d, metric)) return launch_batch_half(bt, d, st);
+    if (sad_supported(d, metric)) return launch_batch_sad(bt, d, st);
     if (metric == CHAMFER_L1) return batch_valu<CHAMFER_L1>(bt, d, st);
     return batch_valu<CHAMFER_L2>(bt, d, st);
 }

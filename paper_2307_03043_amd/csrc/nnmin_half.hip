@@ -270,76 +270,6 @@ __device__ __forceinline__ void bare_barrier() {
     asm volatile("s_barrier" : : : "memory");
 }
 
-// Canonical float32 accumulators of M pairs of rows x and b, each with LPH
-// consecutive lanes: lane s holds coordinates [s S, (s + 1) S), S <= 16, of both
-// rows (one batch of loads for all pairs) and continues the sum of lane s - 1, so
-// the terms are added in coordinate order.  The results are in the last lane.
-// All lanes must call it.
-template <int LPH, int MAXD, int M>
-__device__ __forceinline__ void hit_acc(const float *const *x, const float *const *b, int d,
-                                        float *out) {
-    constexpr int N = LPH == 1 ? MAXD : 16;  // coordinates per lane, at most
-    // opaque: what follows from them is rare work whose lane masks must not be
-    // hoisted into (and spilled around) the caller's tile loop
-    int s = (threadIdx.x & 63) % LPH;
-    asm volatile("" : "+v"(s), "+s"(d));
-    const int S = LPH == 1 ? d : (d + 4 * LPH - 1) / (4 * LPH) * 4;
-    const int k0 = s * S, k1 = min(d, k0 + S);
-    float t[M][N];  // zero past the lane's coordinates: adds nothing
-    uintptr_t low = 0;
-#pragma unroll
-    for (int m = 0; m < M; ++m)
-        low |= reinterpret_cast<uintptr_t>(x[m]) | reinterpret_cast<uintptr_t>(b[m]);
-    if (LPH > 1 && (d & 3) == 0 && (low & 15) == 0) {
-        float4 u[M][N / 4 > 0 ? N / 4 : 1], v[M][N / 4 > 0 ? N / 4 : 1];
-#pragma unroll
-        for (int m = 0; m < M; ++m)
-#pragma unroll
-            for (int i = 0; i < N / 4; ++i) {
-                const int k = max(min(k0 + 4 * i, d - 4), 0);
-                u[m][i] = ld(reinterpret_cast<const CH_RO float4 *>(ro(x[m]) + k));
-                v[m][i] = ld(reinterpret_cast<const CH_RO float4 *>(ro(b[m]) + k));
-            }
-#pragma unroll
-        for (int m = 0; m < M; ++m)
-#pragma unroll
-            for (int i = 0; i < N / 4; ++i) {  // d, S multiples of 4: whole quads
-                const bool in = k0 + 4 * i < k1;
-                t[m][4 * i] = in ? u[m][i].x - v[m][i].x : 0.0f;
-                t[m][4 * i + 1] = in ? u[m][i].y - v[m][i].y : 0.0f;
-                t[m][4 * i + 2] = in ? u[m][i].z - v[m][i].z : 0.0f;
-                t[m][4 * i + 3] = in ? u[m][i].w - v[m][i].w : 0.0f;
-            }
-    } else {
-#pragma unroll
-        for (int m = 0; m < M; ++m)
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int k = min(k0 + i, d - 1);
-                const float u = ro(x[m])[k] - ro(b[m])[k];
-                t[m][i] = k0 + i < k1 ? u : 0.0f;
-            }
-    }
-    // a loop, not unrolled: this code runs once or twice per workgroup and its
-    // time is that of fetching its instructions
-#pragma unroll
-    for (int m = 0; m < M; ++m) out[m] = 0.0f;
-#pragma unroll 1
-    for (int q = 0; q < LPH; ++q) {
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            // the lane below's sum (row shift right by one: LPH <= 16 lanes of a row)
-            float sum = LPH > 1 ? __uint_as_float(__builtin_amdgcn_update_dpp(
-                                      0u, __float_as_uint(out[m]), 0x111, 0xf, 0xf, true))
-                                : 0.0f;
-            if (q == 0) sum = 0.0f;
-#pragma unroll
-            for (int i = 0; i < N; ++i) sum = fmaf(t[m][i], t[m][i], sum);
-            out[m] = s == q ? sum : out[m];
-        }
-    }
-}
-
 // One chunk of B against the workgroup's queries.  RAW (d <= 10): rows of B
 // are read as float32 and split when their tile is stored; the queries too.
 // seed (may be null): seed[row of X] is an upper bound of the query's
@@ -850,7 +780,7 @@ __device__ __forceinline__ void nnmin_half(
                     xp[m] = X + (int64_t)row_s[wave][ey[m] >> kHalfRowBits] * d;
                     bp[m] = B + (b0 + (int64_t)(ey[m] & ((1u << kHalfRowBits) - 1u))) * d;
                 }
-                hit_acc<LPH, KH, M>(xp, bp, d, acc);
+                hit_acc<CHAMFER_L2, LPH, KH, M>(xp, bp, d, acc);
 #pragma unroll
                 for (int m = 0; m < M; ++m)
                     if (i + m * (64 / LPH) + lane / LPH < todo && lane % LPH == LPH - 1)
