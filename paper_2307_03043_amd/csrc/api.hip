@@ -322,7 +322,7 @@ int crude_core(const Plan &pl, const float *A, const float *B, uint64_t seed, fl
         if (r > 0) CH_TRY(launch_grid_tables(seed, pl.L, pl.kh, zf, mt, r, st));
         if (pl.part) {
             // B's keys, then the tables built region by region in LDS (every
-            // slot written, so no emptying pass)
+            // fingerprint written, so no emptying pass)
             if (r == 0) CH_TRY(mark(ev, 1, st));
             CH_TRY(launch_hash(5, B, pl.nB, B, pl.nB, pl.d, pl.metric, pl.L, pl.ke, lohi, emb, zf,
                                mt, nullptr, pl.log2cap, pw.keys, nullptr, nullptr, nullptr,
@@ -340,8 +340,9 @@ int crude_core(const Plan &pl, const float *A, const float *B, uint64_t seed, fl
         if (r == 0) CH_TRY(mark(ev, 2, st));
         const int flags = (r > 0 ? kProbeMerge : 0) | (r == pl.reps - 1 ? kProbeLast : 0);
         CH_TRY(launch_hash(W == 1 ? 1 : 4, A, pl.nA, B, pl.nB, pl.d, pl.metric, pl.L, pl.ke, lohi,
-                           emb, zf, mt, tables, pl.log2cap, nullptr, D, nn, scale, nullptr, p, W,
-                           flags, st));
+                           emb, zf, mt, tables, pl.log2cap, pl.part ? pw.keys : nullptr, D, nn,
+                           scale, nullptr, p, W, flags, st, nullptr,
+                           pl.part ? part_probe_bits(pl.nB, pl.log2cap) : 0));
     }
     CH_TRY(mark(ev, 3, st));
     return CHAMFER_OK;

@@ -594,13 +594,18 @@ __device__ void table_insert(Bucket *tab, uint8_t *fps, int log2cap, unsigned lo
 // insert.  The probe walks the fingerprint bytes, 16 per load, and reads a
 // bucket only where the fingerprint matches: a missing key (most probes
 // below a point's first colliding scale) touches only the fingerprints,
-// 1/16 of the table's bytes.
+// 1/16 of the table's bytes.  It goes round within the 2^rbits slots around
+// the home slot (the whole table, or a region of launch_part_build).  A region
+// that holds no empty slot may have had no room for a key: the scale's keys
+// (nB of them, ascending b) are searched instead.
 __device__ __forceinline__ int table_probe(const CH_RO Bucket *tab, const CH_RO uint8_t *fps,
-                                           int log2cap, unsigned long long key) {
-    const uint64_t mask = (1ull << log2cap) - 1;
+                                           int log2cap, int rbits, unsigned long long key,
+                                           const CH_RO unsigned long long *keys, int64_t nB) {
+    const uint64_t mask = (1ull << rbits) - 1;
     const uint32_t f = key_fp(key, log2cap);
     uint64_t slot = home_slot(key, log2cap);
-    for (;;) {
+    const uint64_t region = slot & ~mask, first = slot & ~15ull;
+    do {
         const uint64_t base = slot & ~15ull;
         const uint4 w = ld(reinterpret_cast<const CH_RO uint4 *>(fps + base));
         for (int q = (int)(slot - base); q < 16; ++q) {
@@ -614,8 +619,12 @@ __device__ __forceinline__ int table_probe(const CH_RO Bucket *tab, const CH_RO 
                 if (k == key) return (int)bk.z;
             }
         }
-        slot = (base + 16) & mask;
-    }
+        slot = region | ((base + 16) & mask);
+    } while (slot != first);
+    if (keys != nullptr)
+        for (int64_t b = 0; b < nB; ++b)
+            if (keys[b] == key) return (int)b;
+    return -1;
 }
 
 // Window tables (multi-probe CrudeNN): a bucket holds its key and the W
@@ -1277,9 +1286,13 @@ __device__ __forceinline__ void hash_tile(
             if (i > __hip_atomic_load(&hit_scale[lane], __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_WORKGROUP))
                 break;  // a finer scale already collided
-            const int v = table_probe(ro((const Bucket *)tables) + ((size_t)i << log2cap),
-                                      ro((const uint8_t *)table_fps(tables, L, log2cap, i)),
-                                      log2cap, key_at(i));
+            // (keys_out, half_dp: launch_part_build's keys and region)
+            const int v = table_probe(
+                ro((const Bucket *)tables) + ((size_t)i << log2cap),
+                ro((const uint8_t *)table_fps(tables, L, log2cap, i)), log2cap,
+                half_dp > 0 ? half_dp : log2cap, key_at(i),
+                keys_out ? ro((const unsigned long long *)keys_out) + (size_t)i * nB : nullptr,
+                nB);
             if (v >= 0) {
                 found = i;
                 cand = v;
@@ -1454,31 +1467,40 @@ hipError_t launch_hash(int mode, const float *X, int64_t n, const float *Bpts, i
 }
 
 // ------------------------------------------------------ partitioned build
-// The W = 1 tables of the direct path, built without global atomics.  A
-// table of 2^c slots is cut into regions of S = 2^min(c, 11) slots, and a
-// key's region is the top bits of its home slot.  From B's keys (hash mode
-// 5, a wavefront's duplicate keys dropped): per scale, each block of
-// kPartBlock keys counts its keys per region (k_part_hist), the counts
-// become offsets (small partitions: inside k_part_scatter, each workgroup
-// from its scale's counts; large ones: k_part_scan_rows and k_part_base),
-// the blocks write their (key, b) pairs grouped by region (k_part_scatter,
-// runs of a region contiguous), and one workgroup per (scale, region)
-// inserts the region's pairs into a table in LDS -- linear probing from
-// the home slot, lowest b per key, LDS atomics only -- and writes all S
-// slots out (k_region_build).  The LDS build never wraps: a pair whose
-// probe reaches the region's end is kept aside and inserted afterwards with
-// the global insert (k_spill_insert), which continues into the next region
-// like any linear probe; the probe then finds every key as after the global
-// insert.
-// A region holds at most S keys against about S / 2 expected (tables are
-// at most half full), so on hashed keys few pairs spill.
+// The W = 1 tables of the direct path, built without global atomics from B's
+// keys (hash mode 5, a wavefront's duplicate keys dropped).  A table of 2^c
+// slots is cut into regions, and a key's region is the top bits of its home
+// slot.  One workgroup per (scale, region) inserts the region's keys into a
+// table in LDS -- linear probing from the home slot that goes round within the
+// region, lowest b per key, LDS atomics only -- and writes it out: every
+// fingerprint byte, and the buckets in use (the probe reads no other).
+//
+// Up to kDirectKeys keys the workgroups (regions of up to 2^13 slots) read all
+// keys of their scale and pick theirs (k_direct_build).  Beyond, each block of
+// kPartBlock keys counts its keys per region of up to 2^11 slots (k_part_hist),
+// the counts become offsets (small partitions: inside k_part_scatter, each
+// workgroup from its scale's counts; large ones: k_part_scan_rows and
+// k_part_base), the blocks write their (key, b) pairs grouped by region
+// (k_part_scatter, runs of a region contiguous) and k_region_build inserts them.
+//
+// A region of S slots holds about S / 2 keys (tables are at most half full).
+// Where it gets more than S distinct ones, those without a slot are left out,
+// and a probe that finds neither its key nor an empty slot searches the keys.
 
 constexpr int kRegionBits = 11;
+constexpr int kDirectBits = 13;
+constexpr int64_t kDirectKeys = 20480;
 constexpr int kPartBlock = 4096;   // keys per histogram / scatter workgroup
 constexpr int kMaxRegions = 1024;  // regions per scale the scan and scatter hold in LDS
 
 __host__ __device__ inline int region_bits(int log2cap) {
     return log2cap < kRegionBits ? log2cap : kRegionBits;
+}
+
+// log2 of the slots that a probe of launch_part_build's tables goes round in.
+int part_probe_bits(int64_t nB, int log2cap) {
+    if (nB > kDirectKeys) return region_bits(log2cap);
+    return log2cap < kDirectBits ? log2cap : kDirectBits;
 }
 
 __host__ __device__ inline int64_t part_regions(int log2cap) {
@@ -1494,16 +1516,15 @@ size_t part_work_bytes(int L, int64_t nB, int log2cap, PartWork *w, char *base) 
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const size_t b_keys = al((size_t)L * nB * sizeof(uint64_t));
     const size_t b_offs = al((size_t)L * nblk * R * sizeof(uint32_t));
-    const size_t b_bins = al((size_t)L * R * 3 * sizeof(uint32_t));
+    const size_t b_bins = al((size_t)L * R * 2 * sizeof(uint32_t));
     const size_t b_ent = al((size_t)L * nB * sizeof(uint3));
     if (w) {
         w->keys = reinterpret_cast<uint64_t *>(base);
         w->offs = reinterpret_cast<uint32_t *>(base + b_keys);
         w->bins = reinterpret_cast<uint32_t *>(base + b_keys + b_offs);
         w->entries = reinterpret_cast<uint3 *>(base + b_keys + b_offs + b_bins);
-        w->spilled = reinterpret_cast<uint32_t *>(base + b_keys + b_offs + b_bins + b_ent);
     }
-    return b_keys + b_offs + b_bins + b_ent + 256;
+    return b_keys + b_offs + b_bins + b_ent;
 }
 
 __device__ __forceinline__ uint32_t key_region(unsigned long long key, int log2cap) {
@@ -1575,13 +1596,13 @@ __global__ __launch_bounds__(256) void k_part_hist(const uint64_t *__restrict__ 
 
 // Large partitions (many blocks and regions): the counts become offsets in
 // two launches (offs: the exclusive prefix over blocks of each region's
-// counts; bins[(i R + g) 3 + {0, 1, 2}] = the region's first entry in the
-// scale's [nB] span of entries, its count, and 0, the spill count):
+// counts; bins[(i R + g) 2 + {0, 1}] = the region's first entry in the scale's
+// [nB] span of entries and its count):
 // k_part_scan_rows takes 64 regions of one scale per workgroup, each
 // wavefront a contiguous quarter of the blocks (loads coalesced over the
 // regions, eight in flight per lane), and writes the regions' totals;
 // k_part_base scans the totals of each scale into the regions' first
-// entries and clears the spill flag.
+// entries.
 __global__ __launch_bounds__(256) void k_part_scan_rows(int log2cap, int64_t nblk,
                                                         uint32_t *offs, uint32_t *bins) {
     __shared__ uint32_t part[4][64];
@@ -1633,21 +1654,18 @@ __global__ __launch_bounds__(256) void k_part_scan_rows(int log2cap, int64_t nbl
         run += c;
     }
     if (w == 0) {
-        bins[((size_t)i * R + g) * 3 + 1] = tot;
-        bins[((size_t)i * R + g) * 3 + 2] = 0;
+        bins[((size_t)i * R + g) * 2 + 1] = tot;
     }
 }
 
-__global__ __launch_bounds__(256) void k_part_base(int log2cap, uint32_t *bins,
-                                                   uint32_t *spilled) {
+__global__ __launch_bounds__(256) void k_part_base(int log2cap, uint32_t *bins) {
     __shared__ uint32_t tot[kMaxRegions + 256];
     const int R = (int)part_regions(log2cap);
     const int64_t i = blockIdx.x;
-    if (i == 0 && threadIdx.x == 0) *spilled = 0;  // read after the region builds
-    for (int g = threadIdx.x; g < R; g += 256) tot[g] = bins[((size_t)i * R + g) * 3 + 1];
+    for (int g = threadIdx.x; g < R; g += 256) tot[g] = bins[((size_t)i * R + g) * 2 + 1];
     __syncthreads();
     block_exclusive_scan(tot, R, tot + R);
-    for (int g = threadIdx.x; g < R; g += 256) bins[((size_t)i * R + g) * 3 + 0] = tot[g];
+    for (int g = threadIdx.x; g < R; g += 256) bins[((size_t)i * R + g) * 2] = tot[g];
 }
 
 // The block's (key, b) pairs grouped by region: counted in LDS, placed in
@@ -1656,14 +1674,12 @@ __global__ __launch_bounds__(256) void k_part_base(int log2cap, uint32_t *bins,
 // fused (small partitions, nblk x R <= kPartScanOneGroup): offs holds the
 // raw counts of k_part_hist; the workgroup derives its offsets in every
 // region and the regions' first entries from its scale's counts itself,
-// and workgroup j = 0 of each scale writes the scale's bins and workgroup 0
-// clears the spill flag (what k_part_scan_rows and k_part_base do for large
-// partitions).
+// and workgroup j = 0 of each scale writes the scale's bins (what
+// k_part_scan_rows and k_part_base do for large partitions).
 __global__ __launch_bounds__(256) void k_part_scatter(const uint64_t *__restrict__ keys,
                                                       int64_t nB, int log2cap, int64_t nblk,
                                                       const uint32_t *__restrict__ offs,
-                                                      uint32_t *bins, uint3 *entries,
-                                                      uint32_t *spilled, int fused) {
+                                                      uint32_t *bins, uint3 *entries, int fused) {
     extern __shared__ uint32_t sm[];
     const int R = (int)part_regions(log2cap);
     uint32_t *cnt = sm;               // [R] counts, then the block's region starts
@@ -1675,7 +1691,6 @@ __global__ __launch_bounds__(256) void k_part_scatter(const uint64_t *__restrict
     __shared__ uint32_t total;
     const int64_t i = blockIdx.x / nblk, j = blockIdx.x - i * nblk;
     if (fused) {
-        if (i == 0 && j == 0 && threadIdx.x == 0) *spilled = 0;  // read after the region builds
         for (int g = threadIdx.x; g < R; g += 256) {
             const CH_RO uint32_t *o = ro(offs) + (size_t)i * nblk * R + g;
             uint32_t before = 0, all = 0;
@@ -1687,16 +1702,13 @@ __global__ __launch_bounds__(256) void k_part_scatter(const uint64_t *__restrict
             }
             gbase[g] = before;
             gtot[g] = all;
-            if (j == 0) {
-                bins[((size_t)i * R + g) * 3 + 1] = all;
-                bins[((size_t)i * R + g) * 3 + 2] = 0;
-            }
+            if (j == 0) bins[((size_t)i * R + g) * 2 + 1] = all;
         }
         __syncthreads();
         block_exclusive_scan(gtot, R, fill);
         for (int g = threadIdx.x; g < R; g += 256) {
             gbase[g] += gtot[g];
-            if (j == 0) bins[((size_t)i * R + g) * 3 + 0] = gtot[g];
+            if (j == 0) bins[((size_t)i * R + g) * 2] = gtot[g];
         }
     }
     for (int g = threadIdx.x; g < R; g += 256) cnt[g] = 0;
@@ -1728,55 +1740,136 @@ __global__ __launch_bounds__(256) void k_part_scatter(const uint64_t *__restrict
     __syncthreads();
     const uint32_t n = total;
     const uint32_t *o = offs + (size_t)(i * nblk + j) * R;
-    const uint32_t *bn = bins + (size_t)i * R * 3;
+    const uint32_t *bn = bins + (size_t)i * R * 2;
     for (uint32_t pos = threadIdx.x; pos < n; pos += 256) {
         const unsigned long long key = sk[pos];
         const uint32_t g = key_region(key, log2cap);
-        const uint32_t first = fused ? gbase[g] : bn[g * 3] + o[g];
+        const uint32_t first = fused ? gbase[g] : bn[g * 2] + o[g];
         const size_t dst = (size_t)i * nB + first + (pos - cnt[g]);
         entries[dst] = make_uint3((uint32_t)key, (uint32_t)(key >> 32), (uint32_t)sb[pos]);
     }
 }
 
+// (key, b) into the S slots of a region in LDS (lowest b per key); no effect when
+// it is full.
+__device__ __forceinline__ void region_insert(unsigned long long *tk, int32_t *tv, int S,
+                                              unsigned long long key, int b, int log2cap) {
+    const int home = (int)(home_slot(key, log2cap) & (uint64_t)(S - 1));
+    int s = home;
+    for (;;) {
+        unsigned long long cur = tk[s];
+        if (cur == kEmptyKey) cur = atomicCAS(&tk[s], kEmptyKey, key);
+        if (cur == kEmptyKey || cur == key) break;
+        s = (s + 1) & (S - 1);
+        if (s == home) return;
+    }
+    atomicMin(&tv[s], b);
+}
+
+// All fingerprints and the buckets in use (all: every bucket) of the S slots from
+// `first` of scale i.
+template <int NT>
+__device__ __forceinline__ void region_write(const unsigned long long *tk, const int32_t *tv,
+                                             int S, int64_t first, int64_t i, int L, int log2cap,
+                                             Bucket *tables, bool all) {
+    Bucket *out = tables + ((size_t)i << log2cap) + first;
+    uint8_t *ofp = table_fps(tables, L, log2cap, (int)i) + first;
+    for (int s = threadIdx.x; s < S; s += NT) {
+        const unsigned long long k = tk[s];
+        if (!all && k == kEmptyKey) continue;
+        Bucket bk;
+        bk.key = k;
+        bk.val = tv[s];
+        bk.pad = 0;
+        out[s] = bk;
+    }
+    for (int s4 = threadIdx.x; s4 < S / 4; s4 += NT) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const unsigned long long k = tk[4 * s4 + q];
+            w |= (k == kEmptyKey ? 0u : key_fp(k, log2cap)) << (8 * q);
+        }
+        reinterpret_cast<uint32_t *>(ofp)[s4] = w;
+    }
+}
+
+// Few keys: one workgroup per (scale, region of 2^rb slots) reads all of the
+// scale's keys.  Bound by latencies: one launch in place of the partition's
+// three (4096 keys, 16 scales: 28 and 11 us).  The line at kDirectKeys: whole l1
+// calls, partition and direct, 16300 keys 101 and 95 us, 32000 117 and 121, 65000 146
+// and 158.
+__global__ __launch_bounds__(1024) void k_direct_build(const uint64_t *__restrict__ keys,
+                                                       int64_t nB, int L, int log2cap, int rb,
+                                                       Bucket *tables) {
+    __shared__ unsigned long long tk[1 << kDirectBits];
+    __shared__ int32_t tv[1 << kDirectBits];
+    const int S = 1 << rb;
+    const int64_t R = (int64_t)1 << (log2cap - rb);
+    const int64_t i = blockIdx.x / R, g = blockIdx.x - i * R;
+    const CH_RO uint64_t *kr = ro(keys) + i * nB;
+    constexpr int kPer = 8;
+    unsigned long long k[kPer];
+    auto load = [&](int64_t b0) {  // in bounds, in flight together
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) k[t] = kr[min(b0 + t * 1024 + threadIdx.x, nB - 1)];
+    };
+    load(0);
+    for (int s = threadIdx.x; s < S; s += 1024) {
+        tk[s] = kEmptyKey;
+        tv[s] = INT_MAX;
+    }
+    __syncthreads();
+    for (int64_t b0 = 0; b0 < nB; b0 += 1024 * kPer) {
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) {
+            const int64_t b = b0 + t * 1024 + threadIdx.x;
+            if (b < nB && k[t] != kEmptyKey &&
+                (int64_t)(home_slot(k[t], log2cap) >> rb) == g)
+                region_insert(tk, tv, S, k[t], (int)b, log2cap);
+        }
+        if (b0 + 1024 * kPer < nB) load(b0 + 1024 * kPer);
+    }
+    __syncthreads();
+    region_write<1024>(tk, tv, S, g << rb, i, L, log2cap, tables, false);
+}
+
 // One workgroup per (scale, region): the region's pairs into an LDS table of
-// S slots (lowest b per key), then all S slots written to the table.  Pairs
-// whose probe reaches the region's end are compacted to the front of the
-// region's run of entries, counted in bins[.. + 2] and flagged in *spilled.
-// Up to kRegionPrefetch pairs per
-// thread are read before any is inserted (one round of loads).
+// S slots, written to the table.  Up to kRegionPrefetch pairs per thread are
+// read before any is inserted (one round of loads).
 constexpr int kRegionPrefetch = 8;
 
-__global__ __launch_bounds__(256) void k_region_build(uint3 *entries, int64_t nB, int L,
-                                                      int log2cap, Bucket *tables, uint32_t *bins,
-                                                      uint32_t *spilled) {
+__global__ __launch_bounds__(256) void k_region_build(const uint3 *__restrict__ entries,
+                                                      int64_t nB, int L, int log2cap,
+                                                      Bucket *tables,
+                                                      const uint32_t *__restrict__ bins) {
     extern __shared__ unsigned long long tk[];  // [S] keys, then [S] values
     const int qb = region_bits(log2cap);
     const int S = 1 << qb;
     int32_t *tv = reinterpret_cast<int32_t *>(tk + S);
-    __shared__ uint32_t nspill;
     const int64_t R = part_regions(log2cap);
     const int64_t i = blockIdx.x / R, g = blockIdx.x - i * R;
-    const uint32_t start = bins[(i * R + g) * 3], count = bins[(i * R + g) * 3 + 1];
+    const uint32_t start = bins[(i * R + g) * 2], count = bins[(i * R + g) * 2 + 1];
     for (int s = threadIdx.x; s < S; s += 256) {
         tk[s] = kEmptyKey;
         tv[s] = INT_MAX;
     }
-    if (threadIdx.x == 0) nspill = 0;
-    uint3 *run = entries + (size_t)i * nB + start;
+    const uint3 *run = entries + (size_t)i * nB + start;
     const int lane = threadIdx.x & 63;
     for (uint32_t base = 0; base < count; base += 256 * kRegionPrefetch) {
         uint3 e[kRegionPrefetch];
 #pragma unroll
         for (int q = 0; q < kRegionPrefetch; ++q) {
-            const uint32_t at = base + q * 256 + threadIdx.x;
-            e[q] = at < count ? run[at] : make_uint3(0xffffffffu, 0xffffffffu, 0u);
+            // in bounds and unconditional (predicated, each load was waited for
+            // before the next: 316 against 240 us at 10^6 points)
+            e[q] = run[min(base + q * 256 + threadIdx.x, count - 1)];
         }
-        __syncthreads();  // the table is initialised; every pair read before spills overwrite
+        if (base == 0) __syncthreads();  // the table is initialised
 #pragma unroll
         for (int q = 0; q < kRegionPrefetch; ++q) {
             const unsigned long long key = (unsigned long long)e[q].x |
                                            ((unsigned long long)e[q].y << 32);
-            const bool valid = key != kEmptyKey;
+            const bool valid = base + q * 256 + threadIdx.x < count;
             int b = (int)e[q].z;
             // the lowest lane's key: its lanes fold their b into it (a key
             // repeated across wavefronts at coarse scales goes in once per
@@ -1790,73 +1883,11 @@ __global__ __launch_bounds__(256) void k_region_build(uint3 *entries, int64_t nB
             const bool leader = same && lane == first;
             if (leader) b = mb;
             if (!valid || (same && !leader)) continue;
-            int s = (int)(home_slot(key, log2cap) & (uint64_t)(S - 1));
-            bool done = false;
-            for (; s < S; ++s) {
-                unsigned long long cur = tk[s];
-                if (cur == kEmptyKey) cur = atomicCAS(&tk[s], kEmptyKey, key);
-                if (cur == kEmptyKey || cur == key) {
-                    atomicMin(&tv[s], b);
-                    done = true;
-                    break;
-                }
-            }
-            if (!done) {
-                const uint32_t r = atomicAdd(&nspill, 1u);
-                run[r] = make_uint3((uint32_t)key, (uint32_t)(key >> 32), (uint32_t)b);
-            }
+            region_insert(tk, tv, S, key, b, log2cap);
         }
-        __syncthreads();
     }
-    // an empty region skips the loop: the fingerprints below read slots that
-    // other threads initialised
     __syncthreads();
-    Bucket *out = tables + ((size_t)i << log2cap) + ((size_t)g << qb);
-    uint8_t *ofp = table_fps(tables, L, log2cap, (int)i) + ((size_t)g << qb);
-    for (int s = threadIdx.x; s < S; s += 256) {
-        Bucket bk;
-        bk.key = tk[s];
-        bk.val = tv[s];
-        bk.pad = 0;
-        out[s] = bk;
-    }
-    for (int s4 = threadIdx.x; s4 < S / 4; s4 += 256) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const unsigned long long k = tk[4 * s4 + q];
-            w |= (k == kEmptyKey ? 0u : key_fp(k, log2cap)) << (8 * q);
-        }
-        reinterpret_cast<uint32_t *>(ofp)[s4] = w;
-    }
-    if (threadIdx.x == 0) {
-        bins[(i * R + g) * 3 + 2] = nspill;
-        if (nspill) atomicOr(spilled, 1u);
-    }
-}
-
-// The pairs the LDS builds kept aside, inserted with the global insert; a
-// single flag word says whether there are any.
-__global__ __launch_bounds__(256) void k_spill_insert(const uint32_t *__restrict__ bins,
-                                                      const uint3 *__restrict__ entries,
-                                                      int64_t nB, int L, int log2cap,
-                                                      Bucket *tables, const uint32_t *spilled) {
-    if (*spilled == 0) return;
-    const int64_t R = part_regions(log2cap);
-    const int lane = threadIdx.x & 63;
-    const int64_t nw = (int64_t)gridDim.x * 4;
-    for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < (int64_t)L * R; r += nw) {
-        const uint32_t ns = bins[r * 3 + 2];
-        if (ns == 0) continue;
-        const int64_t i = r / R;
-        const uint3 *run = entries + (size_t)i * nB + bins[r * 3];
-        for (uint32_t e = lane; e < ns; e += 64) {
-            const uint3 v = run[e];
-            table_insert(tables + ((size_t)i << log2cap), table_fps(tables, L, log2cap, (int)i),
-                         log2cap, (unsigned long long)v.x | ((unsigned long long)v.y << 32),
-                         (int)v.z);
-        }
-    }
+    region_write<256>(tk, tv, S, g << qb, i, L, log2cap, tables, count > (uint32_t)S / 4);
 }
 
 // Largest count table (blocks x regions) of one scale that each scatter
@@ -1869,6 +1900,12 @@ hipError_t launch_part_build(const PartWork &w, int64_t nB, int L, int log2cap, 
                              hipStream_t st) {
     if (nB <= 0 || L <= 0) return hipSuccess;
     if (!part_build_ok(log2cap)) return hipErrorInvalidValue;
+    if (nB <= kDirectKeys) {
+        const int rb = part_probe_bits(nB, log2cap);
+        k_direct_build<<<(unsigned)((int64_t)L << (log2cap - rb)), 1024, 0, st>>>(
+            w.keys, nB, L, log2cap, rb, tables);
+        return hipGetLastError();
+    }
     const int64_t R = part_regions(log2cap), nblk = part_blocks(nB);
     const int S = 1 << region_bits(log2cap);
     k_part_hist<<<(unsigned)(L * nblk), 256, (size_t)R * sizeof(uint32_t), st>>>(
@@ -1877,18 +1914,14 @@ hipError_t launch_part_build(const PartWork &w, int64_t nB, int L, int log2cap, 
     if (!fused) {
         k_part_scan_rows<<<(unsigned)(L * ((R + 63) / 64)), 256, 0, st>>>(log2cap, nblk, w.offs,
                                                                          w.bins);
-        k_part_base<<<(unsigned)L, 256, 0, st>>>(log2cap, w.bins, w.spilled);
+        k_part_base<<<(unsigned)L, 256, 0, st>>>(log2cap, w.bins);
     }
     const size_t lds_sc = (2 * (size_t)R + 256) * sizeof(uint32_t) + (size_t)kPartBlock * 12 +
                           (fused ? 2 * (size_t)R * sizeof(uint32_t) : 0);
     k_part_scatter<<<(unsigned)(L * nblk), 256, lds_sc, st>>>(
-        w.keys, nB, log2cap, nblk, w.offs, w.bins, w.entries, w.spilled, fused ? 1 : 0);
+        w.keys, nB, log2cap, nblk, w.offs, w.bins, w.entries, fused ? 1 : 0);
     k_region_build<<<(unsigned)(L * R), 256, (size_t)S * 12, st>>>(w.entries, nB, L, log2cap,
-                                                                   tables, w.bins, w.spilled);
-    // a wavefront per (scale, region): most have nothing kept aside, and a
-    // wavefront that walked several regions waited on each one's inserts
-    k_spill_insert<<<(unsigned)((L * R + 3) / 4), 256, 0, st>>>(w.bins, w.entries, nB, L,
-                                                                 log2cap, tables, w.spilled);
+                                                                   tables, w.bins);
     return hipGetLastError();
 }
 

@@ -527,7 +527,7 @@ hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, const float *
 hipError_t launch_table_fill(Bucket *tables, size_t count, hipStream_t st);
 // mode 0: insert B into the tables; 1: probe A (CrudeNN); 2: write keys;
 // 5: write B's keys for launch_part_build (duplicates within a wavefront
-// dropped); 3 / 4: insert / probe with a window of W points per bucket (the
+// dropped), of whose tables 1 takes the keys and, as half_dp, part_probe_bits; 3 / 4: insert / probe with a window of W points per bucket (the
 // tables are then keys [L][cap] followed by members [L][cap][W]).  Modes 0, 3
 // and 5 also write B's FP16 table of the l2 exact pass when half_out is set
 // (with nbh_out and the maxima in p).  flags: kProbe*.
@@ -546,11 +546,12 @@ size_t table_bytes(int L, int log2cap, int W);
 struct PartWork {
     uint64_t *keys;    // [L][nB] (the empty key for a dropped duplicate)
     uint32_t *offs;    // [L][blocks][regions]
-    uint32_t *bins;    // [L][regions][3]: first entry, count, spilled
+    uint32_t *bins;    // [L][regions][2]: first entry, count
     uint3 *entries;    // [L][nB] (key lo, key hi, b) grouped by region
-    uint32_t *spilled; // [1] some region kept pairs aside for the global insert
 };
 bool part_build_ok(int log2cap);
+// log2 of the slots that a probe of these tables goes round in.
+int part_probe_bits(int64_t nB, int log2cap);
 // Workspace bytes of the build; with w, also lays the regions out from base.
 size_t part_work_bytes(int L, int64_t nB, int log2cap, PartWork *w = nullptr,
                        char *base = nullptr);
