@@ -32,10 +32,19 @@ __device__ __forceinline__ float accum(float acc, float q, float b) {
 // pair is one chain of D dependent adds (k ascending), so with one query per
 // lane (d = 128) four rows are run at once: four independent chains per lane
 // (measured +40% on MI355X); with two or more queries per lane the extra
-// registers cost more than the chains gain.
-template <int QPL>
+// registers cost more than the chains gain.  In three dimensions with few queries
+// a row is a few instructions: rows are taken eight at a time so that one
+// comparison with the best serves them all (a pass with nothing better, nearly
+// every one, takes about 7 operations a pair instead of 9) and their scalar loads
+// go out together.  (Four at a time with eight queries: 5000 x 100000 exact 114 ->
+// 125 us.)
+template <int D, int QPL>
+constexpr bool valu_few() {
+    return D == 3 && QPL < 8;
+}
+template <int D, int QPL>
 constexpr int valu_rows() {
-    return QPL == 1 ? 4 : 1;
+    return valu_few<D, QPL>() ? 8 : QPL == 1 ? 4 : 1;
 }
 
 // Exact dimension D known at compile time; QPL queries per lane, RB rows of
@@ -46,18 +55,23 @@ __device__ __forceinline__ void nnmin_fixed(const float *__restrict__ X,
                                             const float *__restrict__ B, int64_t nB, int64_t chunk,
                                             int nchunk, unsigned long long *best,
                                             const DevParams *__restrict__ p, Blk blk) {
-    constexpr int RB = valu_rows<QPL>();
+    constexpr int RB = valu_rows<D, QPL>();
     if (p->status != CHAMFER_OK) return;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     int cb;
     int64_t qb;
     chunk_major(blk.id, ((nx + 64 * QPL - 1) / (64 * QPL) + 3) / 4, nchunk, cb, qb);
-    const int64_t qg = qb * 4 + wave;
+    // few queries, fewer than four groups of them: the wavefronts share the chunk's
+    // rows (50 draws x 1000 clouds of 1000 to 4000 points: 1414 -> 510 us)
+    const int64_t groups = (nx + 64 * QPL - 1) / (64 * QPL);
+    const int share = !valu_few<D, QPL>() ? 1 : groups == 1 ? 4 : groups == 2 ? 2 : 1;
+    const int64_t qg = qb * 4 + wave / share;
     const int64_t q0 = qg * 64 * QPL;
     if (q0 >= nx) return;
-    const int64_t b0 = (int64_t)cb * chunk;
-    const int64_t b1 = min(nB, b0 + chunk);
+    const int64_t rows_each = share == 1 ? chunk : ((chunk + share - 1) / share + 7) / 8 * 8;
+    const int64_t b0 = (int64_t)cb * chunk + (wave % share) * rows_each;
+    const int64_t b1 = min(min(nB, (int64_t)(cb + 1) * chunk), b0 + rows_each);
     if (b0 >= b1) return;
 
     float q[QPL][D];
@@ -94,6 +108,18 @@ __device__ __forceinline__ void nnmin_fixed(const float *__restrict__ X,
 #pragma unroll
                 for (int j = 0; j < QPL; ++j) acc[r][j] = accum<METRIC>(acc[r][j], q[j][k], bk);
             }
+        if (valu_few<D, QPL>() && !first) {
+            float m[QPL];
+            bool any = false;
+#pragma unroll
+            for (int j = 0; j < QPL; ++j) {
+                m[j] = acc[0][j];
+#pragma unroll
+                for (int r = 1; r < RB; ++r) m[j] = fminf(m[j], acc[r][j]);
+                any |= m[j] < bv[j];
+            }
+            if (__ballot(any) == 0) continue;
+        }
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
 #pragma unroll
@@ -211,20 +237,25 @@ __global__ __launch_bounds__(256) void k_nnmin_any(const float *__restrict__ X,
 // Split B into chunks so the grid has enough workgroups to fill 256 CUs;
 // the chunk count is a multiple of 8 when > 1 so that the work order
 // (chunk_major) keeps each chunk's workgroups on one XCD.
-static void split_b(int64_t qblocks, int64_t nB, int64_t target, int64_t &chunk, int &nchunk) {
+static void split_b(int64_t qblocks, int64_t nB, int64_t target, int64_t rows, int64_t pass,
+                    int64_t &chunk, int &nchunk) {
     int64_t nc = (target + qblocks - 1) / qblocks;
-    const int64_t maxc = (nB + 63) / 64;
+    const int64_t maxc = (nB + rows - 1) / rows;  // at least about `rows` rows a chunk
     if (nc > maxc) nc = maxc;
     if (nc > 1) nc = (nc + 7) / 8 * 8;
     if (nc < 1) nc = 1;
     chunk = (nB + nc - 1) / nc;
+    if (nc > 1) chunk = (chunk + pass - 1) / pass * pass;  // whole passes of rows
     nchunk = (int)((nB + chunk - 1) / chunk);
 }
 
-// Queries per lane of the fixed-dimension forms (0: the any-dimension form).
-static int valu_qpl(int d) {
+// Queries per lane of the fixed-dimension forms (0: the any-dimension form).  In
+// three dimensions: eight where there is work for the whole chip, fewer otherwise
+// (whole l1 calls with eight and two: 1000 draws of 1203 rows 62 and 55 us, 1440 of
+// 3000 75 and 66, 1700 of 90000 173 and 191).
+__host__ __device__ inline int valu_qpl(int64_t nx, int64_t nB, int d) {
     switch (d) {
-        case 3: return 8;
+        case 3: return nx <= 64 ? 1 : nx <= 1024 || (nx <= 4096 && nB <= 16384) ? 2 : 8;
         case 16: return 4;
         case 32: return 2;
         case 64: return 2;
@@ -234,11 +265,16 @@ static int valu_qpl(int d) {
 }
 
 NNGeom valu_geom(int64_t nx, int64_t nB, int d, int64_t target) {
-    const int qpl = valu_qpl(d);
+    const int qpl = valu_qpl(nx, nB, d);
     const int64_t per = 64 * (qpl ? qpl : 1);
     const int64_t qblocks = ((nx + per - 1) / per + 3) / 4;
     NNGeom g;
-    split_b(qblocks, nB, target > 0 ? target : kValuTargetWGs, g.chunk, g.nchunk);
+    // wavefronts that share a chunk's rows (nnmin_fixed) want longer chunks
+    const int64_t groups = (nx + per - 1) / per;
+    const bool few = d == 3 && qpl < 8;
+    const int64_t rows = !few ? 64 : groups == 1 ? 256 : groups == 2 ? 128 : 64;
+    split_b(qblocks, nB, target > 0 ? target : kValuTargetWGs, rows, few ? 8 : 1, g.chunk,
+            g.nchunk);
     g.blocks = qblocks * g.nchunk;
     return g;
 }
@@ -258,7 +294,12 @@ static hipError_t go_metric(const float *X, const int32_t *rows, int64_t nx, con
                             int64_t nB, int d, unsigned long long *best, const DevParams *p,
                             hipStream_t st) {
     switch (d) {
-        case 3: return go_fixed<METRIC, 3, 8>(X, rows, nx, B, nB, best, p, st);
+        case 3:
+            switch (valu_qpl(nx, nB, 3)) {
+                case 1: return go_fixed<METRIC, 3, 1>(X, rows, nx, B, nB, best, p, st);
+                case 2: return go_fixed<METRIC, 3, 2>(X, rows, nx, B, nB, best, p, st);
+                default: return go_fixed<METRIC, 3, 8>(X, rows, nx, B, nB, best, p, st);
+            }
         case 16: return go_fixed<METRIC, 16, 4>(X, rows, nx, B, nB, best, p, st);
         case 32: return go_fixed<METRIC, 32, 2>(X, rows, nx, B, nB, best, p, st);
         case 64: return go_fixed<METRIC, 64, 2>(X, rows, nx, B, nB, best, p, st);
@@ -369,10 +410,25 @@ hipError_t launch_sum_final(const double *partial, int64_t nparts, const DevPara
 constexpr unsigned kGridNNValu = 4096;
 
 template <int METRIC, int D, int QPL>
+__device__ __forceinline__ void job_nn_fixed(const Job &J, Blk b) {
+    nnmin_fixed<METRIC, D, QPL>(glb(J.A), glb(J.idx), J.T, glb(J.B), J.nB, J.nn_chunk,
+                                J.nn_nchunk, glb(J.best), glb(J.p), b);
+}
+
+template <int METRIC, int D, int QPL>
 __global__ __launch_bounds__(256) void kb_nn_fixed(const Batch *__restrict__ bt) {
+    batch_loop(bt, kBsNN, [&](const Job &J, Blk b) { job_nn_fixed<METRIC, D, QPL>(J, b); });
+}
+
+// Three dimensions: queries per lane by each job's draws.
+template <int METRIC>
+__global__ __launch_bounds__(256) void kb_nn_points(const Batch *__restrict__ bt) {
     batch_loop(bt, kBsNN, [&](const Job &J, Blk b) {
-        nnmin_fixed<METRIC, D, QPL>(glb(J.A), glb(J.idx), J.T, glb(J.B), J.nB, J.nn_chunk,
-                                    J.nn_nchunk, glb(J.best), glb(J.p), b);
+        switch (valu_qpl(J.T, J.nB, 3)) {
+            case 1: job_nn_fixed<METRIC, 3, 1>(J, b); break;
+            case 2: job_nn_fixed<METRIC, 3, 2>(J, b); break;
+            default: job_nn_fixed<METRIC, 3, 8>(J, b); break;
+        }
     });
 }
 
@@ -387,7 +443,7 @@ __global__ __launch_bounds__(256) void kb_nn_any(const Batch *__restrict__ bt) {
 template <int METRIC>
 static hipError_t batch_valu(const Batch *bt, int d, hipStream_t st) {
     switch (d) {
-        case 3: kb_nn_fixed<METRIC, 3, 8><<<kGridNNValu, 256, 0, st>>>(bt); break;
+        case 3: kb_nn_points<METRIC><<<kGridNNValu, 256, 0, st>>>(bt); break;
         case 16: kb_nn_fixed<METRIC, 16, 4><<<kGridNNValu, 256, 0, st>>>(bt); break;
         case 32: kb_nn_fixed<METRIC, 32, 2><<<kGridNNValu, 256, 0, st>>>(bt); break;
         case 64: kb_nn_fixed<METRIC, 64, 2><<<kGridNNValu, 256, 0, st>>>(bt); break;
