@@ -644,7 +644,10 @@ __device__ __forceinline__ void nnmin_half(
     // thresholds of the rows evaluated meanwhile; one that fills the queue a third
     // time (duplicates) is evaluated in full.
     int from_nb = 0, tries = 0;
-    auto compute = [&](const uint8_t *tile, int t, int hh) {
+    // scan: nothing is queued, the scores only raise the thresholds (256 slots, the
+    // first tile, before its rows are queued: 280 draws of 3000 rows 114 -> 108 us;
+    // at fewer slots, with twice the queries, it cost as much as it saved).
+    auto compute = [&](const uint8_t *tile, int t, int hh, bool scan) {
 #pragma unroll 1
         for (; hh < NH; hh += 2) {
             if (t + 32 * hh >= len) break;
@@ -681,6 +684,15 @@ __device__ __forceinline__ void nnmin_half(
                 for (int r = 1; r < 15; r += 2) m[nb] = fmaxf(fmaxf(m[nb], a[nb][r]), a[nb][r + 1]);
                 m[nb] = fmaxf(m[nb], a[nb][15]);
                 any |= m[nb] > thr[nb];
+            }
+            if (scan) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    float nt = m[nb] - marg_s[wave][32 * nb + j];
+                    nt = fmaxf(nt, __shfl_xor(nt, 32));
+                    thr[nb] = fmaxf(thr[nb], nt);
+                }
+                continue;
             }
             if (__ballot(any) != 0) {
                 bool full = false;
@@ -852,8 +864,14 @@ __device__ __forceinline__ void nnmin_half(
         }
         if (wave_active) {
             int hh = wave & 1;
+            bool scan = DP == 256 && step == 0;
             do {
-                hh = compute(tiles + slot * TB, t, hh);
+                hh = compute(tiles + slot * TB, t, hh, scan);
+                if (scan) {
+                    scan = false;
+                    hh = wave & 1;
+                    continue;
+                }
                 if (hh < NH || crowded != 0u || cnt >= QN / 2 || (!more && cnt > 0)) settle(t);
             } while (hh < NH);
         }
@@ -914,16 +932,29 @@ static bool half_small(int64_t nx, int64_t nB, int d) {
     return (double)nx * (double)nB * half_slots(d) <= 4e9;
 }
 
+// target 0: as many chunks as give the least number of rounds of resident
+// workgroups times the rows of a round (a workgroup starts and ends in the time
+// of about 128 rows).  1600 draws are 7 query blocks: with 80 chunks, the multiple
+// of 8 above 512 / 7, a second round of 48 workgroups followed the first.
 static NNGeom half_geom(int64_t nx, int64_t nB, int d, bool small, int64_t target) {
     const int64_t wq = 64 * half_nb(half_slots(d), small);
     const int64_t nq = (nx + wq - 1) / wq;
-    if (target <= 0) target = half_target_wgs(d);
-    int64_t nc = (target + nq - 1) / nq;
+    const int64_t slots = half_target_wgs(d);
     const int64_t cmin = (nB + 65535) / 65536, cmax = (nB + 63) / 64;
-    if (nc < cmin) nc = cmin;
-    if (nc > cmax) nc = cmax;
-    if (nc < 1) nc = 1;
-    if (nc > 1) nc = (nc + 7) / 8 * 8;  // one chunk's workgroups share an XCD
+    auto whole = [&](int64_t nc) {  // one chunk's workgroups share an XCD
+        if (nc < cmin) nc = cmin;
+        if (nc > cmax) nc = cmax;
+        return nc > 1 ? (nc + 7) / 8 * 8 : (int64_t)1;
+    };
+    int64_t nc = whole(((target > 0 ? target : slots) + nq - 1) / nq);
+    if (target <= 0) {
+        double least = 1e300;
+        for (int64_t c = whole(1); c <= whole(2 * slots / nq + 1); c = c < 8 ? 8 : c + 8) {
+            const double rounds = (double)((nq * c + slots - 1) / slots);
+            const double cost = rounds * ((double)nB / (double)c + 128.0);
+            if (cost < least) least = cost, nc = c;
+        }
+    }
     NNGeom g;
     g.chunk = ((nB + nc - 1) / nc + 31) / 32 * 32;  // whole 32-row blocks
     g.nchunk = (int32_t)nc;
