@@ -97,19 +97,20 @@ class HipEvents:
 
 def algorithmic_sample_pass(metric, T, n_b, d):
     """Work of the exact pass over the draws: T * n_B * d coordinate terms.
-    l2 (12 <= d <= 256) runs on the BF16 matrix cores: 2 flops (one
-    multiply-add of x.b) per term, each computed as three BF16 products of
-    the two-term split of the coordinates (four when T >= 16384), so the
-    peak is the BF16 MFMA peak and the form's own ceiling is that peak over
-    the product count.  l1 runs on the vector ALU: 2 flops (subtract, add
-    |t|) per term, against the FP32 vector peak."""
+    l2 (d <= 10, 12 <= d <= 256) runs on the FP16 matrix cores, whose dense
+    peak is that of BF16: 2 flops (one multiply-add of x.b) per term, computed
+    as one FP16 product (three for d <= 10).  l1 runs on the vector ALU (from
+    d = 9 on, where the product is large or the dimension has no form of its
+    own, as byte differences): 2 flops (subtract, add |t|) per term, against
+    the FP32 vector peak."""
     elems = float(T) * n_b * d
-    if metric == 2 and 12 <= d <= 256:
-        products = 4 if T >= 16384 else 3
+    if metric == 2 and (d <= 10 or 12 <= d <= 256):
+        products = 3 if d <= 10 else 1
         return dict(bound="mfma", unit="TFLOP/s", ops=2.0 * elems, peak=BF16_MFMA_TFLOPS,
                     products=products,
-                    note=f"2 flops (x.b multiply-add) per coordinate term, computed as {products} "
-                         "BF16 MFMA products of the two-term split coordinates")
+                    note="2 flops (x.b multiply-add) per coordinate term, computed as "
+                         f"{products} FP16 MFMA product{'s' if products > 1 else ''}; the rows "
+                         "that the score does not rule out have their float32 distance computed")
     if metric == 2:
         return dict(bound="alu", unit="TFLOP/s", ops=3.0 * elems, peak=FP32_VECTOR_TFLOPS,
                     note="3 FP32 flops (subtract, fma) per coordinate term on the vector ALU")
@@ -677,8 +678,8 @@ def target_point(args, ch, torch, workloads):
             "brute_force_ms": bt * 1e3, "speedup": bt / dt,
             "rel_err": abs(eta - exact) / exact, "eta": eta, "CH": exact,
             "stages_ms": stages,
-            "roofline": {"kernel": "exact pass over the T draws (the draws' split table, "
-                                   "matrix-core record kernel, resolve, rescans)",
+            "roofline": {"kernel": "exact pass over the T draws (the draws' FP16 table and "
+                                   "the matrix-core kernel)",
                          "bound": work["bound"], "achieved": achieved, "peak": work["peak"],
                          "unit": work["unit"], "frac": achieved / work["peak"],
                          "kernel_ms": kms}}
@@ -825,9 +826,8 @@ def main():
     lam = float(aux["D"].item())
 
     # roofline of the exact pass over the draws (stage 4 -> 5: for l2 the
-    # draws' split table, the record pass on the matrix cores and the
-    # per-draw resolve kernel; B's split table is written by the kernel that
-    # hashes B, in the bucket_B stage)
+    # draws' FP16 table and the matrix-core kernel; B's table is written by the
+    # kernel that hashes B, in the bucket_B stage)
     work = algorithmic_sample_pass(metric, T, n_b, d)
     kernel_ms = stages_ms["exact_pass"]
     achieved = work["ops"] / (kernel_ms * 1e-3) / 1e12
@@ -837,11 +837,10 @@ def main():
                 "traffic": measured_traffic(args.workload, kernel_ms), "kernel_ms": kernel_ms,
                 "algorithmic": work["note"]}
     if "products" in work:
-        roofline["kernel"] = ("k_split_rows of the draws + k_nnmin_l2_split record pass + "
-                              "k_split_resolve (exact pass over the T draws; B's split table "
-                              "is written while B is hashed, in bucket_B)")
-        roofline["mfma_dtype"] = "bf16"
-        roofline["frac_of_split_ceiling"] = achieved * work["products"] / work["peak"]
+        roofline["kernel"] = ("k_half_rows of the draws + k_nnmin_half (exact pass over the T "
+                              "draws; B's FP16 table is written while B is hashed, in bucket_B)")
+        roofline["mfma_dtype"] = "f16"
+        roofline["frac_of_form_ceiling"] = achieved * work["products"] / work["peak"]
 
     result = {
         "metric": METRIC_NAME,
