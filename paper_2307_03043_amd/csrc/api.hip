@@ -195,20 +195,18 @@ int make_plan(Plan &pl, int64_t nA, int64_t nB, int32_t d, int32_t metric, doubl
     pl.off_P = take(e_ * nA * sizeof(uint64_t));
     pl.off_idx = take(e_ * pl.T * sizeof(int32_t));
     pl.off_best = take((size_t)nrow * sizeof(uint64_t));
-    // thresholds of the l2 exact pass: the draws' live in the hash tables'
-    // region (done with by then), in copies where they fit; otherwise one copy
-    // right after best, so that one fill resets both
+    // thresholds of the exact pass: the draws' live in the hash tables' region
+    // (done with by then), in copies where they fit, and there are none where not
+    // even one does; the passes over all points keep one copy right after best, so
+    // that one fill resets both
     const size_t room = h ? table_bytes(pl.L, lc, pl.window) : 0;
-    size_t gb = (size_t)(estimating ? pl.T : nA) * sizeof(uint32_t);
-    if (!lowp_supported(d, metric, o.precision) && half_supported(d, metric)) {
-        pl.thr_copies = half_copies(pl.T, nB);
-        if (pl.thr_copies * gb > room) pl.thr_copies = 1;
-    } else if (sad_supported(d, metric) && (gb <= room || !estimating)) {
-        pl.thr_copies = 1;
-    } else {
-        gb = 0;
-    }
-    pl.off_gthr = gb <= room ? pl.off_tables : take(gb);
+    const size_t gb = (size_t)(estimating ? pl.T : nA) * sizeof(uint32_t);
+    const bool half_pass = !lowp_supported(d, metric, o.precision) && half_supported(d, metric);
+    if (!half_pass && !sad_supported(d, metric)) pl.thr_copies = 0;
+    else if (!estimating) pl.thr_copies = 1;
+    else if (half_pass && half_copies(pl.T, nB) * gb <= room) pl.thr_copies = half_copies(pl.T, nB);
+    else pl.thr_copies = gb <= room ? 1 : 0;
+    pl.off_gthr = estimating ? pl.off_tables : take(pl.thr_copies * gb);
     pl.off_partial = take((size_t)(nn_finalize_blocks(nrow) + 1) * sizeof(double));
     // low precision: cast rows of B and of the queries, scales and norms;
     // float32 l2 with 12 <= d <= 256: the FP16 tables of B and of the queries
@@ -382,7 +380,8 @@ int nn_pass(const Plan &pl, void *ws, const float *X, const int32_t *rows, int64
                                     lohi, p, st));
         }
         CH_TRY(launch_nnmin_half(X, rows, nx, xs, stat, seed, B, bs, nB, pl.d, nbh, lohi, best,
-                                 at<uint32_t>(ws, pl.off_gthr), pl.thr_copies, p, st));
+                                 pl.thr_copies ? at<uint32_t>(ws, pl.off_gthr) : nullptr, pl.thr_copies,
+                                 p, st));
         return CHAMFER_OK;
     }
     if (sad_pass(nx, nB, pl.d, pl.metric)) {

@@ -584,8 +584,8 @@ hipError_t launch_nnmin(const float *X, const int32_t *rows, int64_t nx, const f
 // bs) and of the queries (rows X[rows[i]], i < nx, or X[i]; xs, stat), then
 // launch_nnmin_half returns the canonical float32 minima.  seed (may be
 // null): seed[row of X] bounds the query's distance from above.  best [nx] and
-// gthr [copies][nx] (the thresholds known so far) start as all ones; copies is 8 (one
-// per XCD) or 1.
+// gthr [copies][nx] (the thresholds known so far; may be null) start as all ones;
+// copies is 8 (one per XCD) or 1.
 // Copies for an estimate's draws (gthr lies in table space that is dead by then;
 // the passes over all points keep to one).  A few thousand queries are in use by
 // all XCDs at once, and their thresholds lie on few cache lines: each XCD gets a

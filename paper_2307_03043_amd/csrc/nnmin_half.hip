@@ -273,8 +273,8 @@ __device__ __forceinline__ void bare_barrier() {
 // One chunk of B against the workgroup's queries.  RAW (d <= 10): rows of B
 // are read as float32 and split when their tile is stored; the queries too.
 // seed (may be null): seed[row of X] is an upper bound of the query's
-// distance.  gthr[q]: the thresholds of all workgroups (thr_code), in copies
-// gstride words apart, one per XCD, when gstride is not 0.
+// distance.  gthr[q] (may be null): the thresholds of all workgroups (thr_code),
+// in copies gstride words apart, one per XCD, when gstride is not 0.
 template <int DP, bool RAW, int NB>
 __device__ __forceinline__ void nnmin_half(
     const float *__restrict__ X, const int32_t *__restrict__ rows, int64_t nx,
@@ -341,7 +341,7 @@ __device__ __forceinline__ void nnmin_half(
     // are evaluated, written then and after; by draws with long chunks also as soon
     // as a score raises one (exact pass of 2000 draws: 2 10^5 x 3 points 58 -> 54
     // us, 10^5 x 128 116 -> 111; all-points passes of 2500 x 20001 lose 10%).
-    const bool share = nchunk > 1, eager = gstride != 0 && len > 1024;
+    const bool share = gthr != nullptr && nchunk > 1, eager = gstride != 0 && len > 1024;
     // A copy per XCD is used through that XCD's L2: workgroup-scope atomics, and
     // loads past the L1 only.  Were its users on several XCDs, they would see
     // fewer of each other's thresholds; every value stored is valid.
@@ -520,8 +520,9 @@ __device__ __forceinline__ void nnmin_half(
             if constexpr (!RAW) sq = ld(ro(stat) + qi);
             const unsigned long long known =
                 __hip_atomic_load(&best[qi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t gt = __hip_atomic_load(&gthr[qi], __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t gt = gthr ? __hip_atomic_load(&gthr[qi], __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT)
+                                     : 0xffffffffu;
             const float sd = seed ? ro(seed)[row] : INFINITY;
             const float zt = sq.y + sq.z, zn2 = sq.x;
             const float e = half_err_query(err, zt, sq.z, by, be) + 3e-7f * zn2;

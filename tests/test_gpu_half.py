@@ -108,3 +108,16 @@ def test_draws(ch, orc, d, n_b):
     torch.cuda.synchronize()
     idx = out["sample_idx"].cpu().numpy()
     same(out["sample_min"], out["sample_nn"], orc.nn_f32(A, B, L2, rows=idx))
+
+
+@pytest.mark.parametrize("metric", [1, 2])
+@pytest.mark.parametrize("d", [3, 24])
+@pytest.mark.parametrize("n_b,T,uniform", [(20, 20000, False), (2000, 300, True), (20, 9000, True)])
+def test_draws_without_shared_thresholds(ch, orc, metric, d, n_b, T, uniform):
+    """Estimates whose workspace has no room for the thresholds."""
+    A, B = workloads.clusters_l2(seed=d, n=600, d=d, k=10, n_b=n_b)
+    out = ch.chamfer_estimate(dev(A), dev(B), metric, 0.2, T, 3,
+                              sampling=ch.UNIFORM if uniform else ch.IMPORTANCE)
+    torch.cuda.synchronize()
+    idx = out["sample_idx"].cpu().numpy()
+    same(out["sample_min"], out["sample_nn"], orc.nn_f32(A, B, metric, rows=idx))
