@@ -99,10 +99,11 @@ def algorithmic_sample_pass(metric, T, n_b, d):
     """Work of the exact pass over the draws: T * n_B * d coordinate terms.
     l2 (d <= 10, 12 <= d <= 256) runs on the FP16 matrix cores, whose dense
     peak is that of BF16: 2 flops (one multiply-add of x.b) per term, computed
-    as one FP16 product (three for d <= 10).  l1 runs on the vector ALU (from
-    d = 9 on, where the product is large or the dimension has no form of its
-    own, as byte differences): 2 flops (subtract, add |t|) per term, against
-    the FP32 vector peak."""
+    as one FP16 product (three for d <= 10).  l1 runs on the vector ALU, 2 flops
+    (subtract, add |t|) per term: against the FP32 vector peak or, where it runs
+    on byte differences (9 <= d <= 256 and a large product or a dimension without
+    a form of its own), that of v_sad_u8, four terms per lane and instruction at
+    half the rate of an FP32 instruction."""
     elems = float(T) * n_b * d
     if metric == 2 and (d <= 10 or 12 <= d <= 256):
         products = 3 if d <= 10 else 1
@@ -114,6 +115,11 @@ def algorithmic_sample_pass(metric, T, n_b, d):
     if metric == 2:
         return dict(bound="alu", unit="TFLOP/s", ops=3.0 * elems, peak=FP32_VECTOR_TFLOPS,
                     note="3 FP32 flops (subtract, fma) per coordinate term on the vector ALU")
+    if 9 <= d <= 256 and (d not in (16, 32, 64, 128) or elems >= 2e9):
+        return dict(bound="alu", unit="TFLOP/s", ops=2.0 * elems, peak=2 * FP32_VECTOR_TFLOPS,
+                    note="2 operations (subtract, add |t|) per coordinate term, as byte "
+                         "differences, four a lane and instruction; the rows that their sum does "
+                         "not rule out have their float32 distance computed")
     return dict(bound="alu", unit="TFLOP/s", ops=2.0 * elems, peak=FP32_VECTOR_TFLOPS,
                 note="2 FP32 flops (subtract, add |t|) per coordinate term on the vector ALU")
 
