@@ -293,6 +293,7 @@ __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
     __shared__ float box[kHalfRawDim];
     if (threadIdx.x == 0) mxs = mbs = 0u;
     __syncthreads();
+    uint32_t mine_m = 0u, mine_b = 0u;
     float corner = 0.0f, low = 0.0f;  // l1: of coordinate threadIdx.x (d <= blockDim.x)
     for (int k = threadIdx.x; k < d; k += blockDim.x) {
         float c = 0.0f, smin = INFINITY, smax = -INFINITY;
@@ -338,8 +339,18 @@ __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
                           c - ordered_to_float(min(lo[0], lo[1])));
                 if (k < kHalfRawDim) box[k] = b;
             }
-            atomicMax(&mxs, __float_as_uint(fabsf(m)));
-            atomicMax(&mbs, __float_as_uint(fabsf(b)));
+            mine_m = max(mine_m, __float_as_uint(fabsf(m)));
+            mine_b = max(mine_b, __float_as_uint(fabsf(b)));
+        }
+    }
+    if (B) {
+        for (int off = 32; off > 0; off >>= 1) {
+            mine_m = max(mine_m, (uint32_t)__shfl_xor((int)mine_m, off));
+            mine_b = max(mine_b, (uint32_t)__shfl_xor((int)mine_b, off));
+        }
+        if ((threadIdx.x & 63) == 0 && (mine_m | mine_b) != 0u) {
+            atomicMax(&mxs, mine_m);
+            atomicMax(&mbs, mine_b);
         }
     }
     __syncthreads();
@@ -401,7 +412,13 @@ __device__ __forceinline__ void calib_final(uint32_t *lohi, int d, DevParams *p,
     __syncthreads();
     if (threadIdx.x != 0) return;
     double S = 0.0;
-    for (int k = 0; k < d; ++k) S = S + span[k];
+    for (int k = 0; k < d; k += 8) {  // in order; the reads of eight go out together
+        double v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = span[min(k + i, d - 1)];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) S = S + (k + i < d ? v[i] : 0.0);
+    }
     p->S = S;
     p->e_top = S > 0.0 ? ceil_log2_pos(S) : 0;
     if (check && p->nonfinite) p->status = CHAMFER_ENONFINITE;
