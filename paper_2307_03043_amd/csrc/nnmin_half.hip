@@ -447,13 +447,16 @@ __device__ __forceinline__ void nnmin_half(
 
     // ---- the queries' thresholds, a query per lane: with e the query's part of
     // the error bound a row can reach the canonical accumulator acc only if
-    // v >= (|z|^2 (1 - rho) - acc 2^2he (1 + 2 rho)) / 2 - e (thr_of), and a row
-    // known at v1 excludes every v below v1 - marg (marg: the parts of both
+    // v >= (|z|^2 (1 - rho) - (acc + under) 2^2he (1 + 2 rho)) / 2 - e (thr_of), and a
+    // row known at v1 excludes every v below v1 - marg (marg: the parts of both
     // rows and twice the query's; B's largest row part).  Loops that are not
     // unrolled: this code runs once, and its time is that of fetching its
     // instructions.
-    // Float32 with some slack (3e-7 |z|^2 for the roundings of |z|^2 / 2).
-    const float rho = half_rho(d);
+    // Float32 with some slack (3e-7 |z|^2 for the roundings of |z|^2 / 2).  acc is
+    // within rho of the squared distance but for what its steps lose below
+    // float32's normal range, at most 2^-150 each (and the seed's square twice):
+    // under, which the scale makes large for clouds of extent 1e-20 and less.
+    const float rho = half_rho(d), under = ldexpf((float)(d + 4), -149);
     float by, be = 0.0f, erow;
     if constexpr (RAW) {
         by = p->half_box;
@@ -468,7 +471,7 @@ __device__ __forceinline__ void nnmin_half(
     }
     const float rho2 = 2.1f * rho + 1e-6f;
     auto thr_of = [&](float tlo, float acc) {
-        const float h = ldexpf(acc, 2 * he - 1) * (1.0f + rho2);
+        const float h = ldexpf(acc + under, 2 * he - 1) * (1.0f + rho2);
         return tlo - h - (fabsf(tlo) + h) * 2.4e-7f;
     };
     auto prepare = [&](int q) {
@@ -527,7 +530,8 @@ __device__ __forceinline__ void nnmin_half(
             const float zt = sq.y + sq.z, zn2 = sq.x;
             const float e = half_err_query(err, zt, sq.z, by, be) + 3e-7f * zn2;
             const float vmax = 0.5f * by * by + 1.02f * zt * by;
-            marg = (2.0f * (e + erow) + 2.2f * rho * (0.5f * zn2 + vmax + e + erow)) * 1.00001f;
+            marg = (2.0f * (e + erow) + 2.2f * rho * (0.5f * zn2 + vmax + e + erow)) * 1.00001f +
+                   ldexpf(under, 2 * he);
             tlo = 0.5f * zn2 * (1.0f - rho - 1e-6f) - 1.00001f * e;
             t0 = -INFINITY;
             if (tlo > -INFINITY) {  // (or NaN: no bound, every row is evaluated)
