@@ -532,6 +532,9 @@ __device__ __forceinline__ void nnmin_half(
             const float vmax = 0.5f * by * by + 1.02f * zt * by;
             marg = (2.0f * (e + erow) + 2.2f * rho * (0.5f * zn2 + vmax + e + erow)) * 1.00001f +
                    ldexpf(under, 2 * he);
+            // a row whose canonical sum may overflow excludes nothing by its score:
+            // all rows at infinity are equal, and the lowest index counts
+            if (!(ldexpf((zt + by) * (zt + by), -2 * he) < 3e38f)) marg = INFINITY;
             tlo = 0.5f * zn2 * (1.0f - rho - 1e-6f) - 1.00001f * e;
             t0 = -INFINITY;
             if (tlo > -INFINITY) {  // (or NaN: no bound, every row is evaluated)

@@ -1,7 +1,8 @@
 """GPU parity of the exact passes at the ends of float32's range, where the
 canonical sums lose what the passes' own bounds are relative to: squares in the
-subnormal range or below it (rows a few quanta apart, ties at zero).  Bit for bit
-the oracle's float32 search."""
+subnormal range or below it (rows a few quanta apart, ties at zero), squares that
+overflow (every row at infinity: the lowest index is the answer).  Bit for bit the
+oracle's float32 search."""
 
 import numpy as np
 import pytest
@@ -68,3 +69,11 @@ def test_l2_underflow_draws(ch, orc, d, scale):
     assert int(out["status"].item()) == 0 and int(out["W"].item()) != 0
     idx = out["sample_idx"].cpu().numpy()
     same(out["sample_min"], out["sample_nn"], orc.nn_f32(A, B, L2, rows=idx))
+
+
+@pytest.mark.parametrize("d", [3, 9, 16, 64, 128, 256])
+@pytest.mark.parametrize("scale", [2e18, 6e18, 3e19, 1e25, 1e37])
+def test_l2_overflow(ch, orc, d, scale):
+    """Some, then all of a query's distances at infinity."""
+    A, B = clouds(np.random.default_rng(d), 500, 3000, d, scale)
+    check(ch, orc, A, B, L2)
