@@ -1121,8 +1121,11 @@ __device__ __forceinline__ void hash_tile(
                 e2 += __shfl_xor(e2, off);
             }
             const HalfErr he_ = half_err(d, half_dp);
+            // (a row outside FP16's range keeps its clamped operands: nothing
+            // beside kHalfAlways)
             if ((tid & 3) == 0 && (tid >> 2) < np)
-                nbh_out[p0 + (tid >> 2)] = half_norm(s2, e2, he_.s2, he_.e2);
+                nbh_out[p0 + (tid >> 2)] =
+                    isfinite(s2 + e2) ? half_norm(s2, e2, he_.s2, he_.e2) : kHalfAlways;
             uint32_t my = __float_as_uint(s2), me = __float_as_uint(e2);
             for (int off = 32; off > 2; off >>= 1) {
                 my = max(my, (uint32_t)__shfl_xor((int)my, off));

@@ -323,8 +323,8 @@ __host__ __device__ inline HalfErr half_err(int d, int slots) {
     return h;
 }
 // -|y|^2 / 2 raised by the row's part of the bound: the score's first term.  A
-// row outside FP16's range (non-finite points of chamfer_nn_min) has the operand
-// 0 and kHalfAlways, above any threshold.
+// row outside FP16's range (non-finite points of chamfer_nn_min, a span beyond
+// float32's) has kHalfAlways, above any threshold.
 constexpr float kHalfAlways = 3e38f;
 __device__ __forceinline__ float half_norm(float s2, float e2, float es2, float ee2) {
     return fmaf(e2, ee2, fmaf(s2, es2, -0.5f * s2));

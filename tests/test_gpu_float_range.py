@@ -1,8 +1,8 @@
 """GPU parity of the exact passes at the ends of float32's range, where the
 canonical sums lose what the passes' own bounds are relative to: squares in the
 subnormal range or below it (rows a few quanta apart, ties at zero), squares that
-overflow (every row at infinity: the lowest index is the answer).  Bit for bit the
-oracle's float32 search."""
+overflow (every row at infinity: the lowest index is the answer), spans that
+overflow themselves.  Bit for bit the oracle's float32 search."""
 
 import numpy as np
 import pytest
@@ -77,3 +77,20 @@ def test_l2_overflow(ch, orc, d, scale):
     """Some, then all of a query's distances at infinity."""
     A, B = clouds(np.random.default_rng(d), 500, 3000, d, scale)
     check(ch, orc, A, B, L2)
+
+
+@pytest.mark.parametrize("d", [3, 16, 64, 128])
+def test_l2_span_overflow(ch, orc, d):
+    """Two clouds further apart than float32 reaches: no scale holds both, the
+    distances within each are ordinary."""
+    rng = np.random.default_rng(d)
+    A, B = clouds(rng, 600, 2000, d, 1.0)
+    A[:, 0] = np.where(rng.random(600) < 0.5, -2.5e38, 2.5e38)
+    B[:, 0] = np.where(rng.random(2000) < 0.5, -2.5e38, 2.5e38)
+    check(ch, orc, A, B, L2)
+    for sampling in (ch.IMPORTANCE, ch.UNIFORM):
+        out = ch.chamfer_estimate(dev(A), dev(B), L2, 0.2, 300, 3, sampling=sampling)
+        torch.cuda.synchronize()
+        assert int(out["status"].item()) == 0 and int(out["W"].item()) != 0
+        idx = out["sample_idx"].cpu().numpy()
+        same(out["sample_min"], out["sample_nn"], orc.nn_f32(A, B, L2, rows=idx))
