@@ -207,10 +207,13 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
         e = e * 1.0001f;
         const float out = inbox ? ex * 0.99998f : 0.0f;
         const float off = e - out + 4.0f * eps + (float)E + 1.0f;
-        // a row known at s is at most s + 2 (its own part) away: excludes sums above
+        // a row known at s is at most s + 2 (its own part) away: excludes sums above,
+        // unless its canonical sum may overflow (all rows at infinity are equal, and
+        // the lowest index counts)
         const float mg = 2.0f * (e + (float)E) + 8.0f * eps + ex * 0.0002f +
                          2.4f * rho * (256.0f * (float)d + ex) + 4.0f;
-        marg[j] = inbox && mg < 1e9f ? (uint32_t)mg : 0x7fffffffu;
+        marg[j] = inbox && mg < 1e9f && 256.0f * (float)d + ex < 3e38f * inv ? (uint32_t)mg
+                                                                             : 0x7fffffffu;
         uint32_t t = 0u;
         bool live = qi < nx;
         if (live) {

@@ -1,7 +1,7 @@
 """GPU parity of the exact passes at the ends of float32's range, where the
 canonical sums lose what the passes' own bounds are relative to: squares in the
-subnormal range or below it (rows a few quanta apart, ties at zero), squares that
-overflow (every row at infinity: the lowest index is the answer), spans that
+subnormal range or below it (rows a few quanta apart, ties at zero), squares and
+sums that overflow (every row at infinity: the lowest index is the answer), spans that
 overflow themselves.  Bit for bit the oracle's float32 search."""
 
 import numpy as np
@@ -10,7 +10,7 @@ import pytest
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-L2 = 2
+L1, L2 = 1, 2
 
 
 @pytest.fixture(scope="module")
@@ -94,3 +94,13 @@ def test_l2_span_overflow(ch, orc, d):
         assert int(out["status"].item()) == 0 and int(out["W"].item()) != 0
         idx = out["sample_idx"].cpu().numpy()
         same(out["sample_min"], out["sample_nn"], orc.nn_f32(A, B, L2, rows=idx))
+
+
+@pytest.mark.parametrize("d", [9, 40, 100, 200])
+@pytest.mark.parametrize("scale", [3e36, 2e37, 1e38])
+def test_l1_overflow(ch, orc, d, scale):
+    """Some, then all of a query's sums at infinity; at 1e38 the box's span, too."""
+    rng = np.random.default_rng(d)
+    A = (rng.uniform(-1, 1, (500, d)) * 3 * scale).astype(np.float32)
+    B = (rng.uniform(-1, 1, (3000, d)) * 3 * scale).astype(np.float32)
+    check(ch, orc, A, B, L1)
