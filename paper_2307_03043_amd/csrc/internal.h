@@ -663,6 +663,12 @@ struct NNGeom {
 };
 // target: workgroups the split of B aims for (0: the direct-launch target)
 NNGeom valu_geom(int64_t nx, int64_t nB, int d, int64_t target = 0);
+// A launch has fewer than 2^32 threads: with chunks of B no longer than 65536 rows,
+// 2 10^7 x 2 10^7 points are 2.4 10^7 workgroups of 256.  The launchers of the half
+// and sad passes take their queries in parts of at most *_launch_queries.
+constexpr int64_t kMaxLaunchWGs = 1 << 23;
+int64_t half_launch_queries(int64_t nx, int64_t nB, int d);
+int64_t sad_launch_queries(int64_t nx, int64_t nB, int d);
 NNGeom half_geom(int64_t nx, int64_t nB, int d, int64_t target = 0);
 NNGeom sad_geom(int64_t nx, int64_t nB, int d, int64_t target, int32_t &qw);
 int64_t half_target_wgs(int d);  // the direct-launch target of half_geom

@@ -189,6 +189,13 @@ hipError_t launch_half_rows(const float *B, int64_t nB, uint16_t *bs, float *nbh
     const int64_t nbB = B ? half_row_blocks(nB, d, true) : 0,
                   nbX = X ? half_row_blocks(nx, d, false) : 0;
     if (nbB + nbX <= 0) return hipSuccess;
+    if (nbB + nbX > kMaxLaunchWGs && nbX > 0) {  // the queries in halves, B with the first
+        const int64_t h = nx / 2;
+        const hipError_t e = launch_half_rows(B, nB, bs, nbh, X, rows, h, xs, stat, d, lohi, p, st);
+        if (e != hipSuccess) return e;
+        return launch_half_rows(nullptr, 0, bs, nbh, rows ? X : X + h * d, rows ? rows + h : nullptr,
+                                nx - h, xs + h * half_slots(d), stat + h, d, lohi, p, st);
+    }
     k_half_rows<<<(unsigned)(nbB + nbX), 256, 0, st>>>(B, nB, bs, nbh, nbB, X, rows, nx, xs, stat,
                                                        d, half_slots(d), lohi, p);
     return hipGetLastError();
@@ -974,12 +981,31 @@ NNGeom half_geom(int64_t nx, int64_t nB, int d, int64_t target) {
     return half_geom(nx, nB, d, false, target);
 }
 
+int64_t half_launch_queries(int64_t nx, int64_t nB, int d) {
+    while (nx > 1 && half_geom(nx, nB, d, half_small(nx, nB, d), 0).blocks > kMaxLaunchWGs)
+        nx = (nx + 1) / 2;
+    return nx;
+}
+
 hipError_t launch_nnmin_half(const float *X, const int32_t *rows, int64_t nx, const uint16_t *Xs,
                              const float4 *stat, const float *seed, const float *B,
                              const uint16_t *Bs, int64_t nB, int d, const float *nbh,
                              const uint32_t *lohi, unsigned long long *best, uint32_t *gthr,
                              int copies, DevParams *p, hipStream_t st) {
     if (nx <= 0) return hipSuccess;
+    const int64_t part = half_launch_queries(nx, nB, d);
+    if (part < nx && copies <= 1) {
+        for (int64_t q = 0; q < nx; q += part) {
+            const int64_t x0 = rows ? 0 : q;  // first row of X
+            const hipError_t e = launch_nnmin_half(
+                X + x0 * d, rows ? rows + q : nullptr, nx - q < part ? nx - q : part,
+                Xs ? Xs + q * half_slots(d) : nullptr, stat ? stat + q : nullptr,
+                seed ? seed + x0 : nullptr, B, Bs, nB, d, nbh, lohi, best + q,
+                gthr ? gthr + q : nullptr, copies, p, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     const bool small = half_small(nx, nB, d);
     const NNGeom g = half_geom(nx, nB, d, small, 0);
 #define CH_HALF_NB(DP, RAW, NB)                                                              \

@@ -502,11 +502,29 @@ NNGeom sad_geom(int64_t nx, int64_t nB, int d, int64_t target, int32_t &qw) {
     }
 }
 
+int64_t sad_launch_queries(int64_t nx, int64_t nB, int d) {
+    int32_t qw;
+    while (nx > 1 && sad_geom(nx, nB, d, 0, qw).blocks > kMaxLaunchWGs) nx = (nx + 1) / 2;
+    return nx;
+}
+
 hipError_t launch_nnmin_sad(const float *X, const int32_t *rows, int64_t nx, const float *seed,
                             const float *B, int64_t nB, int d, const uint32_t *lohi,
                             unsigned long long *best, uint32_t *gthr, DevParams *p,
                             hipStream_t st) {
     if (nx <= 0) return hipSuccess;
+    const int64_t part = sad_launch_queries(nx, nB, d);
+    if (part < nx) {
+        for (int64_t q = 0; q < nx; q += part) {
+            const int64_t x0 = rows ? 0 : q;  // first row of X
+            const hipError_t e = launch_nnmin_sad(
+                X + x0 * d, rows ? rows + q : nullptr, nx - q < part ? nx - q : part,
+                seed ? seed + x0 : nullptr, B, nB, d, lohi, best + q, gthr ? gthr + q : nullptr, p,
+                st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     int32_t qw;
     const NNGeom g = sad_geom(nx, nB, d, 0, qw);
 #define CH_SAD(W)                                                                           \
