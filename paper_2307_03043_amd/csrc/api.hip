@@ -275,7 +275,7 @@ int hash_prologue(const Plan &pl, const float *A, const float *B, uint64_t seed,
     }
     CH_TRY(launch_minmax_pair(A, pl.nA, B, pl.nB, pl.d, lohi, p, st));
     const float *box = boxed(pl.T, pl.nB, pl.d, pl.metric) ? B : nullptr;
-    CH_TRY(launch_calib_final(lohi, pl.d, p, box, pl.nB, pl.metric, true, st));
+    CH_TRY(launch_calib_final(lohi, pl.d, p, box, pl.nB, pl.metric, A, nullptr, pl.nA, true, st));
     return CHAMFER_OK;
 }
 
@@ -632,7 +632,7 @@ int chamfer_exact(const float *A, const float *B, int64_t n_A, int64_t n_B, int3
     CH_TRY(launch_init_params(p, lohi, d, st));
     CH_TRY(launch_minmax_pair(A, n_A, B, n_B, d, lohi, p, st));
     const float *box = boxed(n_A, n_B, d, metric) ? B : nullptr;
-    CH_TRY(launch_calib_final(lohi, d, p, box, n_B, metric, true, st));
+    CH_TRY(launch_calib_final(lohi, d, p, box, n_B, metric, A, nullptr, n_A, true, st));
     CH_TRY(launch_fill_u64(best, reset_words(pl), ~0ull, st));
     if ((rc = nn_pass(pl, ws, A, nullptr, n_A, B, n_B, best, p, st))) return rc;
     CH_TRY(launch_nn_finalize(best, n_A, metric, rowmin_out, rownn_out, partial, p, st));
@@ -653,12 +653,12 @@ int chamfer_nn_min(const float *X, const int32_t *rows, int64_t n_x, const float
     DevParams *p = at<DevParams>(ws, pl.off_params);
     auto *best = at<unsigned long long>(ws, pl.off_best);
     if (!lowp_supported(d, metric, pl.precision) && boxed(n_x, n_B, d, metric)) {
-        // the scale and centre of the exact pass, from B alone (the number of
-        // rows of X is not known here); inputs are not checked
+        // the scale and centre of the exact pass, from B and a few of the queries
+        // (the number of rows of X is not known here); inputs are not checked
         uint32_t *lohi = at<uint32_t>(ws, pl.off_lohi);
         CH_TRY(launch_init_params(p, lohi, d, st));
         CH_TRY(launch_minmax(B, n_B, d, true, lohi, p, st));
-        CH_TRY(launch_calib_final(lohi, d, p, B, n_B, metric, false, st));
+        CH_TRY(launch_calib_final(lohi, d, p, B, n_B, metric, X, rows, n_x, false, st));
     } else {
         CH_TRY(launch_init_params(p, nullptr, d, st));
     }
@@ -718,7 +718,7 @@ int chamfer_estimate(const float *A, const float *B, int64_t n_A, int64_t n_B, i
         CH_TRY(launch_init_params(p, lohi, d, st));
         CH_TRY(launch_minmax_pair(A, n_A, B, n_B, d, lohi, p, st));
         const float *box = boxed(pl.T, n_B, d, metric) ? B : nullptr;
-        CH_TRY(launch_calib_final(lohi, d, p, box, n_B, metric, true, st));
+        CH_TRY(launch_calib_final(lohi, d, p, box, n_B, metric, A, nullptr, n_A, true, st));
         CH_TRY(mark(ev, 1, st));
         CH_TRY(mark(ev, 2, st));
         CH_TRY(launch_unit_weights(D, ax.crude_nn, scale, n_A, p, st));

@@ -279,36 +279,86 @@ hipError_t launch_minmax_pair(const float *A, int64_t nA, const float *B, int64_
     return hipGetLastError();
 }
 
+// Mean and ends of 16 values without a few that lie far from the others: where one
+// half's range is more than 16 times the other's, of that other half.  (This code
+// runs in one workgroup, once: its time is that of fetching its instructions.)
+struct Sample {
+    float mean, lo, hi;
+};
+__device__ __forceinline__ Sample sample16(const float (&v)[16]) {
+    Sample h[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        h[j] = Sample{0.0f, INFINITY, -INFINITY};
+#pragma unroll
+        for (int i = 8 * j; i < 8 * j + 8; ++i) {
+            h[j].mean += v[i] * 0.125f;
+            h[j].lo = fminf(h[j].lo, v[i]);
+            h[j].hi = fmaxf(h[j].hi, v[i]);
+        }
+    }
+    const float r0 = (h[0].hi - h[0].lo) * 0.0625f, r1 = (h[1].hi - h[1].lo) * 0.0625f;
+    if (r0 > 16.0f * r1 || !(r0 < INFINITY)) return h[1];
+    if (r1 > 16.0f * r0 || !(r1 < INFINITY)) return h[0];
+    return Sample{0.5f * h[0].mean + 0.5f * h[1].mean, fminf(h[0].lo, h[1].lo),
+                  fmaxf(h[0].hi, h[1].hi)};
+}
+
+// The scale 2^he takes B's largest coordinate to [2^10, 2^11) (rows that were not
+// in the min/max may be 2^5 times larger), less where A's largest would leave
+// [0, 2^15).  reach: the bits it may give up before the others' operands (FP16 ends
+// at 2^-14) lose what rules rows out.  Points further out than that are few or a
+// cloud of their own, as samples tell (16 times theirs is kept in range): few are
+// left outside FP16's range, each evaluated on its own (one row of B at 10^9 times
+// the extent, exact 40000^2 x 3: 5.2 ms with all of them in range, 0.3 without it).
+// Largest |x - c| of A and B (all), B (rows) and B's sample (typical).
+struct HalfScale {
+    int he;
+    bool far;    // rows of B may lie outside FP16's range
+    bool query;  // the queries' sample has to be looked at
+};
+__device__ __forceinline__ HalfScale half_scale(float all, float rows, float typical, int d,
+                                                bool known) {
+    const int reach = d <= kHalfRawDim ? 10 : 14;
+    const bool few = typical > 0.0f && !(rows <= ldexpf(typical, reach));
+    if (few) rows = ldexpf(typical, 4);
+    const bool span = all > 0.0f && isfinite(all);
+    if (!(rows > 0.0f && isfinite(rows)))  // B is one point, or not finite
+        return HalfScale{span ? 14 - ilogbf(all) : 0, true, false};
+    const int he = 10 - ilogbf(rows), least = span ? 14 - ilogbf(all) : INT_MIN;
+    const bool query = !known || least < he - reach;
+    return HalfScale{query ? he : min(he, least), few, query};
+}
+
 // Fold the kLohiReps copies of the running min/max into the first.  With B
-// (d <= 256), also the centre and the scale of the l2 exact pass: c_k the mean
-// of up to 16 rows spread over B (any c is valid; near the mean it keeps the
-// operands, and so their rounding errors, small), the scale 2^he that takes the
-// largest |b_k - c_k| to [2^10, 2^11) (less where A's largest would leave
-// [0, 2^15); rows that were not in the min/max may be 2^5 times larger), and for
-// d <= kHalfRawDim the corner distance of B's box from c, which bounds |y|; or
-// for l1 the corner and the step of the byte differences.
+// (d <= 256), also the centre and the scale of the l2 exact pass, or for l1 the
+// corner and the step of the byte differences.  Both look at 16 rows spread over B.
+// l2: c_k the mean of those (any c is valid; near the mean it keeps the operands, and
+// so their rounding errors, small), and half_scale of what is found around c.  X (nx
+// rows, or rows[i] of them): the queries, of which the min/max knows all (known) or
+// none.  d <= kHalfRawDim: the corner distance of B's box from c bounds |y|, and so
+// does FP16's range, which the rows beyond are not scored in.
 __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
-                                          const float *__restrict__ B, int64_t nB, int metric) {
-    __shared__ uint32_t mxs, mbs;
+                                          const float *__restrict__ B, int64_t nB, int metric,
+                                          const float *__restrict__ X,
+                                          const int32_t *__restrict__ rows, int64_t nx,
+                                          bool known) {
+    __shared__ uint32_t most[4];  // l2: half_scale's three, the queries' sample; l1: all, sample
     __shared__ float box[kHalfRawDim];
-    if (threadIdx.x == 0) mxs = mbs = 0u;
+    if (threadIdx.x < 4) most[threadIdx.x] = 0u;
     __syncthreads();
-    uint32_t mine_m = 0u, mine_b = 0u;
+    uint32_t mine[3] = {0u, 0u, 0u};
     float corner = 0.0f, low = 0.0f;  // l1: of coordinate threadIdx.x (d <= blockDim.x)
     for (int k = threadIdx.x; k < d; k += blockDim.x) {
-        float c = 0.0f, smin = INFINITY, smax = -INFINITY;
+        float c = 0.0f;
+        float v[16];
+        Sample e{};
         if (B) {
-            // up to 16 rows in one batch of loads (rows repeat when nB < 16)
-            float v[16];
+            // 16 rows in one batch of loads (the first row 16 times when nB < 16)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = ro(B)[(nB * i / 16) * d + k];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                c += v[i] * 0.0625f;
-                smin = fminf(smin, v[i]);
-                smax = fmaxf(smax, v[i]);
-            }
-            if (!isfinite(c)) c = 0.0f;
+            for (int i = 0; i < 16; ++i) v[i] = ro(B)[(nB / 16) * i * d + k];
+            e = sample16(v);
+            c = isfinite(e.mean) ? e.mean : 0.0f;
         }
         uint32_t lo[2], hi[2];
 #pragma unroll
@@ -326,69 +376,99 @@ __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
         lohi[d + k] = max(hi[0], hi[1]);
         if (B) {
             const float hb = ordered_to_float(hi[1]), lb = ordered_to_float(lo[1]);
-            float m, b;
+            float m[3] = {0.0f, 0.0f, 0.0f};
             if (metric == CHAMFER_L1) {
                 low = lb;
-                corner = smin;
-                m = hb - lb;
-                b = smax - smin;
+                float lo16 = v[0], hi16 = v[0];
+#pragma unroll
+                for (int i = 1; i < 16; ++i) {
+                    lo16 = fminf(lo16, v[i]);
+                    hi16 = fmaxf(hi16, v[i]);
+                }
+                corner = lo16;
+                m[0] = hb - lb;
+                m[1] = hi16 - lo16;
             } else {
                 lohi[2 * d + k] = __float_as_uint(c);
-                b = isfinite(hb) && isfinite(lb) ? fmaxf(hb - c, c - lb) : INFINITY;
-                m = fmaxf(ordered_to_float(max(hi[0], hi[1])) - c,
-                          c - ordered_to_float(min(lo[0], lo[1])));
-                if (k < kHalfRawDim) box[k] = b;
+                m[0] = fmaxf(ordered_to_float(max(hi[0], hi[1])) - c,
+                             c - ordered_to_float(min(lo[0], lo[1])));
+                m[1] = isfinite(hb) && isfinite(lb) ? fmaxf(hb - c, c - lb) : INFINITY;
+                m[2] = fmaxf(e.hi - c, c - e.lo);
+                if (k < kHalfRawDim) box[k] = m[1];
             }
-            mine_m = max(mine_m, __float_as_uint(fabsf(m)));
-            mine_b = max(mine_b, __float_as_uint(fabsf(b)));
+#pragma unroll
+            for (int i = 0; i < 3; ++i) mine[i] = max(mine[i], __float_as_uint(fabsf(m[i])));
         }
     }
     if (B) {
-        for (int off = 32; off > 0; off >>= 1) {
-            mine_m = max(mine_m, (uint32_t)__shfl_xor((int)mine_m, off));
-            mine_b = max(mine_b, (uint32_t)__shfl_xor((int)mine_b, off));
-        }
-        if ((threadIdx.x & 63) == 0 && (mine_m | mine_b) != 0u) {
-            atomicMax(&mxs, mine_m);
-            atomicMax(&mbs, mine_b);
-        }
+        for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                mine[i] = max(mine[i], (uint32_t)__shfl_xor((int)mine[i], off));
+        if ((threadIdx.x & 63) == 0)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (mine[i] != 0u) atomicMax(&most[i], mine[i]);
     }
     __syncthreads();
     if (B == nullptr) return;
-    const float M = __uint_as_float(mxs), MB = __uint_as_float(mbs);
+    const float all = __uint_as_float(most[0]), some = __uint_as_float(most[1]);
     if (metric == CHAMFER_L1) {
         // MB: the widest of the sampled rows, M: of all.  Rows far out would make
         // the steps too wide for all others: beyond 8 to 1 the box is that of the
         // samples and half their width around it, and rows outside are clamped
-        const bool all = !(M > 8.0f * MB) || MB == 0.0f;
+        const float M = all, MB = some;
+        const bool every = !(M > 8.0f * MB) || MB == 0.0f;
         if ((int)threadIdx.x < d)
             lohi[2 * d + threadIdx.x] =
-                __float_as_uint(all ? low : fmaxf(low, corner - 0.5f * MB));
+                __float_as_uint(every ? low : fmaxf(low, corner - 0.5f * MB));
         if (threadIdx.x == 0) {
-            const float inv = 254.9997f / (all ? M : 2.0f * MB);
+            const float inv = 254.9997f / (every ? M : 2.0f * MB);
             p->sad_inv = inv > 0.0f && inv < 1e30f ? inv : 0.0f;
-            p->sad_in = all;
+            p->sad_in = every;
         }
-    } else if (threadIdx.x == blockDim.x - 1) {
-        int he = 0;
-        if (M > 0.0f && isfinite(M)) {
-            he = 14 - ilogbf(M);
-            if (MB > 0.0f && isfinite(MB)) he = min(he, 10 - ilogbf(MB));
+        return;
+    }
+    HalfScale sc = half_scale(all, some, __uint_as_float(most[2]), d, known);
+    if (sc.query && X && nx > 0) {  // (uniform)
+        for (int k = threadIdx.x; k < d; k += blockDim.x) {
+            const float c = __uint_as_float(lohi[2 * d + k]);  // (this thread's store)
+            float q[2] = {0.0f, 0.0f};  // of the nearer half
+#pragma unroll 1
+            for (int i = 0; i < 16; i += 8) {
+                float w[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int64_t r = (nx / 16) * (i + j);
+                    w[j] = ro(X)[(rows ? (int64_t)ro(rows)[r] : r) * d + k];
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) q[1] = fmaxf(q[1], fabsf(w[j] - c));
+                if (i == 0) q[0] = q[1], q[1] = 0.0f;
+            }
+            atomicMax(&most[3], __float_as_uint(fminf(q[0], q[1])));
         }
+        __syncthreads();
+        const float far = __uint_as_float(most[3]);
+        if (far > 0.0f && isfinite(far)) sc.he = min(sc.he, (known ? 10 : 12) - ilogbf(far));
+    }
+    if (threadIdx.x == blockDim.x - 1) {
+        const int he = sc.he;
         p->he = he;
+        p->half_far = sc.far;
         if (d <= kHalfRawDim) {
             float s = 0.0f;
             for (int k = 0; k < d; ++k) {
                 const float y = ldexpf(box[k], he);
                 s = fmaf(y, y, s);
             }
-            p->half_box = sqrtf(s) * 1.00001f;
+            p->half_box = fminf(sqrtf(s) * 1.00001f, kHalfRawReach);
         }
     }
 }
 
 __global__ void k_calib_final_wide(uint32_t *lohi, int d, DevParams *p, bool check) {
-    fold_lohi(lohi, d, p, nullptr, 0, 0);
+    fold_lohi(lohi, d, p, nullptr, 0, 0, nullptr, nullptr, 0, false);
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     double S = 0.0;
     for (int k = 0; k < d; ++k)
@@ -403,9 +483,11 @@ __global__ void k_calib_final_wide(uint32_t *lohi, int d, DevParams *p, bool che
 // in order.
 __device__ __forceinline__ void calib_final(uint32_t *lohi, int d, DevParams *p,
                                             const float *__restrict__ B, int64_t nB, int metric,
+                                            const float *__restrict__ X,
+                                            const int32_t *__restrict__ rows, int64_t nx,
                                             bool check) {
     extern __shared__ double span[];
-    fold_lohi(lohi, d, p, B, nB, metric);
+    fold_lohi(lohi, d, p, B, nB, metric, X, rows, nx, check);
     __syncthreads();
     for (int k = threadIdx.x; k < d; k += blockDim.x)
         span[k] = (double)ordered_to_float(lohi[d + k]) - (double)ordered_to_float(lohi[k]);
@@ -426,12 +508,15 @@ __device__ __forceinline__ void calib_final(uint32_t *lohi, int d, DevParams *p,
 
 __global__ __launch_bounds__(256) void k_calib_final(uint32_t *lohi, int d, DevParams *p,
                                                      const float *__restrict__ B, int64_t nB,
-                                                     int metric, bool check) {
-    calib_final(lohi, d, p, B, nB, metric, check);
+                                                     int metric, const float *__restrict__ X,
+                                                     const int32_t *__restrict__ rows, int64_t nx,
+                                                     bool check) {
+    calib_final(lohi, d, p, B, nB, metric, X, rows, nx, check);
 }
 
 hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, const float *B, int64_t nB,
-                              int metric, bool check, hipStream_t st) {
+                              int metric, const float *X, const int32_t *rows, int64_t nx,
+                              bool check, hipStream_t st) {
     if ((size_t)d * sizeof(double) > 60000) {
         // very wide points: spans recomputed by the summing thread
         if (B != nullptr) return hipErrorInvalidValue;
@@ -439,7 +524,8 @@ hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, const float *
         return hipGetLastError();
     }
     if (B != nullptr && nB < 1) return hipErrorInvalidValue;
-    k_calib_final<<<1, 256, (size_t)d * sizeof(double), st>>>(lohi, d, p, B, nB, metric, check);
+    k_calib_final<<<1, 256, (size_t)d * sizeof(double), st>>>(lohi, d, p, B, nB, metric, X, rows, nx,
+                                                              check);
     return hipGetLastError();
 }
 
@@ -1123,10 +1209,10 @@ __device__ __forceinline__ void hash_tile(
             const HalfErr he_ = half_err(d, half_dp);
             // (a row outside FP16's range keeps its clamped operands: nothing
             // beside kHalfAlways)
+            const bool in = isfinite(s2 + e2);
             if ((tid & 3) == 0 && (tid >> 2) < np)
-                nbh_out[p0 + (tid >> 2)] =
-                    isfinite(s2 + e2) ? half_norm(s2, e2, he_.s2, he_.e2) : kHalfAlways;
-            uint32_t my = __float_as_uint(s2), me = __float_as_uint(e2);
+                nbh_out[p0 + (tid >> 2)] = in ? half_norm(s2, e2, he_.s2, he_.e2) : kHalfAlways;
+            uint32_t my = in ? __float_as_uint(s2) : 0u, me = in ? __float_as_uint(e2) : 0u;
             for (int off = 32; off > 2; off >>= 1) {
                 my = max(my, (uint32_t)__shfl_xor((int)my, off));
                 me = max(me, (uint32_t)__shfl_xor((int)me, off));
@@ -1981,7 +2067,8 @@ __global__ __launch_bounds__(256) void kb_minmax(const Batch *__restrict__ bt) {
 
 __global__ __launch_bounds__(256) void kb_calib(const Batch *__restrict__ bt) {
     batch_loop(bt, kBsCalib, [&](const Job &J, Blk) {
-        calib_final(J.lohi, J.d, J.p, J.d <= 256 ? J.B : nullptr, J.nB, J.metric, true);
+        calib_final(J.lohi, J.d, J.p, J.d <= 256 ? J.B : nullptr, J.nB, J.metric, J.A, nullptr, J.nA,
+                    true);
     });
 }
 

@@ -50,7 +50,7 @@ struct DevParams {
     float half_box;      // l2 exact pass: upper bound of |(b - centre) 2^he| over B (d <= 10)
     float sad_inv;       // l1 exact pass: byte steps per unit (0: the bytes tell nothing)
     int32_t sad_in;      // l1 exact pass: every row of B lies in the bytes' box
-    uint32_t pad32[1];
+    int32_t half_far;    // l2 exact pass: rows of B may lie outside FP16's range
     // The maxima of D_a and (l2 exact pass) of |y|^2 and |y - y~|^2 (words 0
     // and 1 of a replica) reduced over thousands of workgroups: each
     // workgroup's atomicMax goes to replica (id mod kMaxRepl), one 128-byte
@@ -323,9 +323,10 @@ __host__ __device__ inline HalfErr half_err(int d, int slots) {
     return h;
 }
 // -|y|^2 / 2 raised by the row's part of the bound: the score's first term.  A
-// row outside FP16's range (non-finite points of chamfer_nn_min, a span beyond
-// float32's) has kHalfAlways, above any threshold.
+// row outside FP16's range (half_scale) has kHalfAlways, above any threshold, and
+// no part in the maxima over B; d <= kHalfRawDim: one with |y| above kHalfRawReach.
 constexpr float kHalfAlways = 3e38f;
+constexpr float kHalfRawReach = 63300.0f;
 __device__ __forceinline__ float half_norm(float s2, float e2, float es2, float ee2) {
     return fmaf(e2, ee2, fmaf(s2, es2, -0.5f * s2));
 }
@@ -520,10 +521,13 @@ hipError_t launch_minmax(const float *X, int64_t n, int d, bool isB, uint32_t *l
 hipError_t launch_minmax_pair(const float *A, int64_t nA, const float *B, int64_t nB, int d,
                               uint32_t *lohi, DevParams *p, hipStream_t st);
 // B (may be null): also the centre and scale of the l2 exact pass
-// (half_supported) or the corner and step of the l1 exact pass (sad_supported).
-// check: a non-finite coordinate sets the status.
+// (half_supported) or the corner and step of the l1 exact pass (sad_supported);
+// X (may be null; rows[i], i < nx, of it if given): points that the queries are
+// or are drawn from.  check: a non-finite coordinate sets the status, and the
+// min/max holds X's points.
 hipError_t launch_calib_final(uint32_t *lohi, int d, DevParams *p, const float *B, int64_t nB,
-                              int metric, bool check, hipStream_t st);
+                              int metric, const float *X, const int32_t *rows, int64_t nx,
+                              bool check, hipStream_t st);
 hipError_t launch_table_fill(Bucket *tables, size_t count, hipStream_t st);
 // mode 0: insert B into the tables; 1: probe A (CrudeNN); 2: write keys;
 // 5: write B's keys for launch_part_build (duplicates within a wavefront

@@ -147,8 +147,8 @@ __device__ __forceinline__ void half_rows(const float *__restrict__ X,
                 stat[r] = half_stat(s2, e2);
             } else {
                 nbh[r] = in ? half_norm(s2, e2, he_.s2, he_.e2) : kHalfAlways;
-                my = max(my, __float_as_uint(s2));
-                me = max(me, __float_as_uint(e2));
+                my = max(my, in ? __float_as_uint(s2) : 0u);
+                me = max(me, in ? __float_as_uint(e2) : 0u);
             }
         }
     }
@@ -342,6 +342,7 @@ __device__ __forceinline__ void nnmin_half(
     const bool wave_active = qbase < nx;
     const int len = (int)(b1 - b0);
     const int he = p->he;
+    const bool far_rows = p->half_far != 0;
     const auto *cen = half_centre(lohi, d);
     const HalfErr err = half_err(d, DP);
     // Thresholds are shared through gthr: read every fourth tile and before rows
@@ -402,7 +403,7 @@ __device__ __forceinline__ void nnmin_half(
                 hb[k] = half_bits(h);
                 mb[k] = half_bits(half_of(v - (float)h));
             }
-            const bool in = s2 < 4e9f;  // no coordinate above 2^15.98
+            const bool in = s2 < 4e9f;  // kHalfRawReach squared: no coordinate above 2^15.98
             if (!in) {
 #pragma unroll
                 for (int k = 0; k < KH; ++k) hb[k] = mb[k] = 0u;
@@ -595,6 +596,7 @@ __device__ __forceinline__ void nnmin_half(
     // of the loop unless a lane has several rows.  True when the queue is full.
     auto push = [&](int nb, const v16f &acc, float m, int row) {
         float nt = m - marg_s[wave][32 * nb + j];
+        if (far_rows && m > 1e38f) nt = -INFINITY;  // (kHalfAlways)
         if (__ballot(thr[nb] == -INFINITY) != 0) nt = fmaxf(nt, __shfl_xor(nt, 32));
         if (nt > thr[nb]) {
             thr[nb] = nt;
@@ -704,6 +706,7 @@ __device__ __forceinline__ void nnmin_half(
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
                     float nt = m[nb] - marg_s[wave][32 * nb + j];
+                    if (far_rows && m[nb] > 1e38f) nt = -INFINITY;
                     nt = fmaxf(nt, __shfl_xor(nt, 32));
                     thr[nb] = fmaxf(thr[nb], nt);
                 }

@@ -701,7 +701,8 @@ int run_reduce(const RPlan &rp, const float *A, const float *B, double eps, uint
     // 5: calibration (lo of A u B) and the partition keys
     CH_TRY(launch_init_params(p, lohi, d, st));
     CH_TRY(launch_minmax_pair(A, rp.nA, B, rp.nB, d, lohi, p, st));
-    CH_TRY(launch_calib_final(lohi, d, p, nullptr, 0, rp.metric, true, st));
+    CH_TRY(launch_calib_final(lohi, d, p, nullptr, 0, rp.metric, nullptr, nullptr, 0,
+                              true, st));
     CH_TRY(launch_part_keys(A, rp.nA, d, rp.metric, rp.ke, lohi, zt, zp, mp, info, p, keysA,
                             grid_for(rp.nA), st));
     CH_TRY(launch_part_keys(B, rp.nB, d, rp.metric, rp.ke, lohi, zt, zp, mp, info, p, keysB,

@@ -1,0 +1,106 @@
+"""Exact passes over clouds with points far out of them (a sensor's "no return"
+value, a cloud beside the other): the passes' operands are scaled to what the
+clouds' samples hold, and what lies beyond is evaluated on its own.  Results bit for
+bit the oracle's; and a single far point may not make a pass slow (with all points
+in FP16's range it took 20 times as long)."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+L1, L2 = 1, 2
+KINDS = ["A 1e2", "A 1e4", "A 1e6", "A 1e9", "A 1e30", "B 1e2", "B 1e4", "B 1e6", "B 1e9",
+         "B 1e30", "B first", "B last", "both 1%", "both 20%", "A beside", "A far beside",
+         "B most at one point"]
+
+
+@pytest.fixture(scope="module")
+def ch():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2307_03043_amd as lib
+    lib.lib()
+    return lib
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to("cuda:0")
+
+
+def same(got_min, got_nn, ref):
+    torch.cuda.synchronize()
+    m32, a32 = ref
+    assert np.array_equal(got_nn.cpu().numpy(), a32)
+    assert np.array_equal(got_min.cpu().numpy().view(np.uint32), m32.view(np.uint32))
+
+
+def clouds(kind, n_a, n_b, d):
+    rng = np.random.default_rng(d)
+    A, B = rng.standard_normal((n_a, d)), rng.standard_normal((n_b, d))
+    if kind[:3] in ("A 1", "B 1"):
+        X = A if kind[0] == "A" else B
+        X[len(X) // 3 + 1] *= float(kind[2:])
+    elif kind == "B first":
+        B[0] = 1e9
+    elif kind == "B last":
+        B[-1] = -1e9
+    elif kind.startswith("both"):  # the same value in both, many at distance 0
+        share = 0.01 if kind.endswith(" 1%") else 0.2
+        A[rng.random(n_a) < share] = 1e9
+        B[rng.random(n_b) < share] = 1e9
+    elif kind == "A beside":
+        A[:, 0] += 1e3
+    elif kind == "A far beside":
+        A[:, 0] += 1e7
+    else:
+        B[rng.random(n_b) < 0.95] = B[0]
+    return A.astype(np.float32), B.astype(np.float32)
+
+
+@pytest.mark.parametrize("metric,d", [(L2, 1), (L2, 3), (L2, 10), (L2, 16), (L2, 100), (L2, 256),
+                                      (L1, 3), (L1, 20), (L1, 100)])
+@pytest.mark.parametrize("kind", KINDS)
+def test_results(ch, orc, metric, d, kind):
+    A, B = clouds(kind, 900, 2600, d)
+    print(f"[case] metric={metric} d={d} {kind}", flush=True)
+    ref = orc.nn_f32(A, B, metric)
+    _, rmin, rnn = ch.chamfer_exact(dev(A), dev(B), metric)
+    same(rmin, rnn, ref)
+    mn, arg = ch.chamfer_nn_min(dev(A), dev(B), metric)
+    same(mn, arg, ref)
+    rows = np.random.default_rng(1).integers(0, 900, 333).astype(np.int32)
+    mn, arg = ch.chamfer_nn_min(dev(A), dev(B), metric, rows=torch.from_numpy(rows).to("cuda:0"))
+    same(mn, arg, (ref[0][rows], ref[1][rows]))
+    out = ch.chamfer_estimate(dev(A), dev(B), metric, 0.2, 300, 3)
+    torch.cuda.synchronize()
+    idx = out["sample_idx"].cpu().numpy()
+    same(out["sample_min"], out["sample_nn"], (ref[0][idx], ref[1][idx]))
+
+
+def seconds(f):
+    f()
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
+
+
+@pytest.mark.parametrize("d", [3, 100])
+@pytest.mark.parametrize("kind", ["A 1e9", "B 1e9", "B first"])
+def test_one_far_point_is_not_slow(ch, d, kind):
+    rng = np.random.default_rng(d)
+    A = rng.standard_normal((16000, d)).astype(np.float32)
+    B = rng.standard_normal((16000, d)).astype(np.float32)
+    plain = seconds(lambda a=dev(A), b=dev(B): ch.chamfer_exact(a, b, L2))
+    X = A if kind[0] == "A" else B
+    X[0 if kind == "B first" else 5000] *= 1e9
+    far = seconds(lambda a=dev(A), b=dev(B): ch.chamfer_exact(a, b, L2))
+    print(f"[times] d={d} {kind}: {plain:.3f} and {far:.3f} ms", flush=True)
+    assert far < 4 * plain
