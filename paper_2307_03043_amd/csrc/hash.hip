@@ -379,15 +379,9 @@ __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
             float m[3] = {0.0f, 0.0f, 0.0f};
             if (metric == CHAMFER_L1) {
                 low = lb;
-                float lo16 = v[0], hi16 = v[0];
-#pragma unroll
-                for (int i = 1; i < 16; ++i) {
-                    lo16 = fminf(lo16, v[i]);
-                    hi16 = fmaxf(hi16, v[i]);
-                }
-                corner = lo16;
+                corner = e.lo;
                 m[0] = hb - lb;
-                m[1] = hi16 - lo16;
+                m[1] = e.hi - e.lo;
             } else {
                 lohi[2 * d + k] = __float_as_uint(c);
                 m[0] = fmaxf(ordered_to_float(max(hi[0], hi[1])) - c,
