@@ -314,20 +314,18 @@ __device__ __forceinline__ Sample sample16(const float (&v)[16]) {
 // Largest |x - c| of A and B (all), B (rows) and B's sample (typical).
 struct HalfScale {
     int he;
-    bool far;    // rows of B may lie outside FP16's range
     bool query;  // the queries' sample has to be looked at
 };
 __device__ __forceinline__ HalfScale half_scale(float all, float rows, float typical, int d,
                                                 bool known) {
     const int reach = d <= kHalfRawDim ? 10 : 14;
-    const bool few = typical > 0.0f && !(rows <= ldexpf(typical, reach));
-    if (few) rows = ldexpf(typical, 4);
+    if (typical > 0.0f && !(rows <= ldexpf(typical, reach))) rows = ldexpf(typical, 4);
     const bool span = all > 0.0f && isfinite(all);
     if (!(rows > 0.0f && isfinite(rows)))  // B is one point, or not finite
-        return HalfScale{span ? 14 - ilogbf(all) : 0, true, false};
+        return HalfScale{span ? 14 - ilogbf(all) : 0, false};
     const int he = 10 - ilogbf(rows), least = span ? 14 - ilogbf(all) : INT_MIN;
     const bool query = !known || least < he - reach;
-    return HalfScale{query ? he : min(he, least), few, query};
+    return HalfScale{query ? he : min(he, least), query};
 }
 
 // Fold the kLohiReps copies of the running min/max into the first.  With B
@@ -336,8 +334,8 @@ __device__ __forceinline__ HalfScale half_scale(float all, float rows, float typ
 // l2: c_k the mean of those (any c is valid; near the mean it keeps the operands, and
 // so their rounding errors, small), and half_scale of what is found around c.  X (nx
 // rows, or rows[i] of them): the queries, of which the min/max knows all (known) or
-// none.  d <= kHalfRawDim: the corner distance of B's box from c bounds |y|, and so
-// does FP16's range, which the rows beyond are not scored in.
+// none.  d <= kHalfRawDim: the corner distance of B's box from c bounds |y|
+// (infinite where rows lie outside FP16's range).
 __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
                                           const float *__restrict__ B, int64_t nB, int metric,
                                           const float *__restrict__ X,
@@ -449,14 +447,14 @@ __device__ __forceinline__ void fold_lohi(uint32_t *lohi, int d, DevParams *p,
     if (threadIdx.x == blockDim.x - 1) {
         const int he = sc.he;
         p->he = he;
-        p->half_far = sc.far;
         if (d <= kHalfRawDim) {
             float s = 0.0f;
             for (int k = 0; k < d; ++k) {
                 const float y = ldexpf(box[k], he);
                 s = fmaf(y, y, s);
             }
-            p->half_box = fminf(sqrtf(s) * 1.00001f, kHalfRawReach);
+            const float by = sqrtf(s) * 1.00001f;
+            p->half_box = by < kHalfRawReach ? by : INFINITY;
         }
     }
 }
@@ -1203,10 +1201,10 @@ __device__ __forceinline__ void hash_tile(
             const HalfErr he_ = half_err(d, half_dp);
             // (a row outside FP16's range keeps its clamped operands: nothing
             // beside kHalfAlways)
-            const bool in = isfinite(s2 + e2);
             if ((tid & 3) == 0 && (tid >> 2) < np)
-                nbh_out[p0 + (tid >> 2)] = in ? half_norm(s2, e2, he_.s2, he_.e2) : kHalfAlways;
-            uint32_t my = in ? __float_as_uint(s2) : 0u, me = in ? __float_as_uint(e2) : 0u;
+                nbh_out[p0 + (tid >> 2)] =
+                    isfinite(s2 + e2) ? half_norm(s2, e2, he_.s2, he_.e2) : kHalfAlways;
+            uint32_t my = __float_as_uint(s2), me = __float_as_uint(e2);
             for (int off = 32; off > 2; off >>= 1) {
                 my = max(my, (uint32_t)__shfl_xor((int)my, off));
                 me = max(me, (uint32_t)__shfl_xor((int)me, off));

@@ -50,7 +50,7 @@ struct DevParams {
     float half_box;      // l2 exact pass: upper bound of |(b - centre) 2^he| over B (d <= 10)
     float sad_inv;       // l1 exact pass: byte steps per unit (0: the bytes tell nothing)
     int32_t sad_in;      // l1 exact pass: every row of B lies in the bytes' box
-    int32_t half_far;    // l2 exact pass: rows of B may lie outside FP16's range
+    uint32_t pad32[1];
     // The maxima of D_a and (l2 exact pass) of |y|^2 and |y - y~|^2 (words 0
     // and 1 of a replica) reduced over thousands of workgroups: each
     // workgroup's atomicMax goes to replica (id mod kMaxRepl), one 128-byte
@@ -323,8 +323,9 @@ __host__ __device__ inline HalfErr half_err(int d, int slots) {
     return h;
 }
 // -|y|^2 / 2 raised by the row's part of the bound: the score's first term.  A
-// row outside FP16's range (half_scale) has kHalfAlways, above any threshold, and
-// no part in the maxima over B; d <= kHalfRawDim: one with |y| above kHalfRawReach.
+// row outside FP16's range (half_scale; d <= kHalfRawDim: |y| above kHalfRawReach) has
+// kHalfAlways, above any threshold; the maxima over B, and so every query's margin,
+// are infinite then: thresholds come from canonical distances alone.
 constexpr float kHalfAlways = 3e38f;
 constexpr float kHalfRawReach = 63300.0f;
 __device__ __forceinline__ float half_norm(float s2, float e2, float es2, float ee2) {

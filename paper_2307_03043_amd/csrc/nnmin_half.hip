@@ -35,7 +35,9 @@
 // evaluate are few (about one in 10^4) because a threshold is carried along
 // and seeded with the CrudeNN distance of a draw.
 #include <cfloat>
+#include <climits>
 #include <cmath>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -147,8 +149,8 @@ __device__ __forceinline__ void half_rows(const float *__restrict__ X,
                 stat[r] = half_stat(s2, e2);
             } else {
                 nbh[r] = in ? half_norm(s2, e2, he_.s2, he_.e2) : kHalfAlways;
-                my = max(my, in ? __float_as_uint(s2) : 0u);
-                me = max(me, in ? __float_as_uint(e2) : 0u);
+                my = max(my, __float_as_uint(s2));
+                me = max(me, __float_as_uint(e2));
             }
         }
     }
@@ -227,6 +229,12 @@ __host__ __device__ constexpr int half_queue() {
     return RAW ? (DP == 16 ? 320 : 512) : DP == 32 ? 224 : DP == 64 ? 256 : DP == 128 ? 320 : 128;
 }
 constexpr int kHalfRowBits = 25;  // chunk rows in a queue entry (7 bits of query)
+// d <= kHalfRawDim: a workgroup one of whose wavefronts has queued this many entries
+// and one per row of its chunk evaluates the rest of the chunk in full (direct).
+// Where no bound tells rows apart (a cloud 10^5 beside B; a hundredth of both clouds at
+// 10^9 times the extent), exact 40000^2 x 3 takes 0.58 and 0.44 ms, 1.54 and 1.73
+// without; with 1024 here one far row of B set it off (0.30 -> 0.35 ms).
+constexpr int kPlainFirst = 2048;
 
 // Thresholds known to other workgroups, one word per query: smaller is a
 // higher threshold, all ones (which decodes to NaN, dropped by fmaxf) is none.
@@ -322,6 +330,10 @@ __device__ __forceinline__ void nnmin_half(
     __shared__ uint32_t seen_s[4][WQ];  // gthr as last read (written by look)
     __shared__ uint32_t vtop_s[4][WQ];  // settle: each query's largest queued v,
     __shared__ uint2 lead[4][WQ];       // and its row
+    // d <= kHalfRawDim, a word per wavefront: the workgroup is to end its tiles and go
+    // on with direct; from this row; entries queued so far (scalar registers are short)
+    __shared__ __attribute__((aligned(16))) uint32_t plain_s[2][4];
+    __shared__ int32_t rest_s[4], evals_s[4];
 
     const int32_t status = p->status;  // (looked at once the first loads are out)
     const int tid = threadIdx.x;
@@ -339,10 +351,9 @@ __device__ __forceinline__ void nnmin_half(
     const int64_t b0 = (int64_t)cb * chunk;
     const int64_t b1 = min(nB, b0 + chunk);
     if (b0 >= b1) return;  // uniform over the workgroup
-    const bool wave_active = qbase < nx;
-    const int len = (int)(b1 - b0);
+    bool wave_active = qbase < nx;
+    int len = (int)(b1 - b0);
     const int he = p->he;
-    const bool far_rows = p->half_far != 0;
     const auto *cen = half_centre(lohi, d);
     const HalfErr err = half_err(d, DP);
     // Thresholds are shared through gthr: read every fourth tile and before rows
@@ -596,7 +607,6 @@ __device__ __forceinline__ void nnmin_half(
     // of the loop unless a lane has several rows.  True when the queue is full.
     auto push = [&](int nb, const v16f &acc, float m, int row) {
         float nt = m - marg_s[wave][32 * nb + j];
-        if (far_rows && m > 1e38f) nt = -INFINITY;  // (kHalfAlways)
         if (__ballot(thr[nb] == -INFINITY) != 0) nt = fmaxf(nt, __shfl_xor(nt, 32));
         if (nt > thr[nb]) {
             thr[nb] = nt;
@@ -706,7 +716,6 @@ __device__ __forceinline__ void nnmin_half(
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
                     float nt = m[nb] - marg_s[wave][32 * nb + j];
-                    if (far_rows && m[nb] > 1e38f) nt = -INFINITY;
                     nt = fmaxf(nt, __shfl_xor(nt, 32));
                     thr[nb] = fmaxf(thr[nb], nt);
                 }
@@ -753,7 +762,16 @@ __device__ __forceinline__ void nnmin_half(
         __builtin_amdgcn_wave_barrier();
     };
     // Evaluate the queue, and every row of the crowded blocks of the tile at t.
-    auto settle = [&](int t) {
+    auto settle = [&](int t, int step) {
+        if constexpr (RAW) {
+            const int evals = evals_s[wave] + cnt + QN * __popc(crowded);
+            evals_s[wave] = evals;
+            if (__builtin_amdgcn_readfirstlane(evals) > kPlainFirst + t) {
+                wave_active = false;
+                rest_s[wave] = t;
+                plain_s[(step >> 2) & 1][wave] = 1u;
+            }
+        }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         // what the other workgroups know by now: most queued rows were queued
@@ -863,9 +881,81 @@ __device__ __forceinline__ void nnmin_half(
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) thr[nb] = fmaxf(thr[nb], thr_s[wave][32 * nb + j]);
     };
+    // Every row from t on (the wavefront's blocks) for every query, d <= kHalfRawDim: on the vector ALU (9
+    // operations a pair), a lane with queries l, l + 64 .., rows wave-uniform (scalar
+    // loads).  From row 0 where a query has no bound at all (2 10^5 x 3 points, 1700
+    // draws of one point at 10^9 times the extent: whole call 1232 -> 256 us).
+    auto direct = [&](int t) {
+        constexpr int NQ = WQ / 64, NR = 8;
+        float x[NQ][KH];
+        uint32_t bv[NQ];
+        int bi[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const auto *xr = ro(X) + (int64_t)row_s[wave][64 * i + lane] * d;
+#pragma unroll
+            for (int k = 0; k < KH; ++k) x[i][k] = xr[min(k, d - 1)];
+            bv[i] = 0xffffffffu;
+            bi[i] = 0;
+        }
+        auto rows8 = [&](int r, int left, auto dim) {
+            constexpr int D = decltype(dim)::value;  // 0: d
+            const int dd = D ? D : d;
+            const auto *b = ro(B) + (b0 + r) * dd;
+            float acc[NR][NQ] = {};
+#pragma unroll
+            for (int k = 0; k < (D ? D : KH); ++k) {
+                if (k >= dd) break;
+#pragma unroll
+                for (int j = 0; j < NR; ++j) {
+                    const float bk = b[(D ? j : min(j, left - 1)) * dd + k];
+#pragma unroll
+                    for (int i = 0; i < NQ; ++i) {
+                        const float u = x[i][k] - bk;
+                        acc[j][i] = fmaf(u, u, acc[j][i]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) {  // (bits order like the values, NaN last)
+                    const uint32_t a = __float_as_uint(acc[j][i]);
+                    if (a < bv[i] && j < left) bv[i] = a, bi[i] = r + j;
+                }
+        };
+#pragma unroll 1
+        for (int hb = t + 32 * (wave & 1); hb < len; hb += 64)
+#pragma unroll 1
+            for (int r = hb; r < min(len, hb + 32); r += NR) {
+                if (d == 3 && r + NR <= len) rows8(r, NR, std::integral_constant<int, 3>());
+                else rows8(r, min(NR, len - r), std::integral_constant<int, 0>());
+            }
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+            if (bv[i] != 0xffffffffu)
+                atomicMin(&best_s[wave][64 * i + lane],
+                          ((unsigned long long)bv[i] << 32) | (uint32_t)(b0 + bi[i]));
+    };
+    if constexpr (RAW) {
+        bool none = false;
+        for (int q = lane; q < WQ; q += 64)
+            none |= qbase + q < nx && !(tlo_s[wave][q] > -INFINITY);
+        evals_s[wave] = 0;
+        rest_s[wave] = INT_MAX;
+        plain_s[0][wave] = 0u;
+        plain_s[1][wave] = __ballot(none) != 0 ? 1u : 0u;
+    }
     // (the builtin: the compiler then knows that the queries' loads are done too)
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     __syncthreads();
+    // (four steps write one set of words, read after the barrier of the last of them;
+    // by the time that it is written again every wavefront has passed that read)
+    auto any_plain = [&](int g) {
+        const uint4 w = *reinterpret_cast<const uint4 *>(plain_s[g & 1]);
+        return __builtin_amdgcn_readfirstlane((int)(w.x | w.y | w.z | w.w)) != 0;
+    };
+    if (RAW && any_plain(1)) len = 0;
     for (int t = 0, slot = 0, step = 0;; t += TR, ++step) {
         // start the loads of the tile NT - 1 ahead (its slot was read before the
         // barrier that ended the previous step; RAW: two ahead, into registers),
@@ -890,8 +980,8 @@ __device__ __forceinline__ void nnmin_half(
                     hh = wave & 1;
                     continue;
                 }
-                if (hh < NH || crowded != 0u || cnt >= QN / 2 || (!more && cnt > 0)) settle(t);
-            } while (hh < NH);
+                if (hh < NH || crowded != 0u || cnt >= QN / 2 || (!more && cnt > 0)) settle(t, step);
+            } while (hh < NH && wave_active);
         }
         const bool polls = share && more && (step & 3) == 0;
         if (polls) look();
@@ -903,10 +993,16 @@ __device__ __forceinline__ void nnmin_half(
         }
         if (!more) break;
         bare_barrier();
+        if (RAW && (step & 3) == 3 && any_plain(step >> 2)) len = min(len, t + 2 * TR);
         if (share && (step & 3) <= 1) take_up();
         slot = next;
     }
-    if (!wave_active) return;
+    if (qbase >= nx) return;
+    if constexpr (RAW) {
+        const int rest = min(len, __builtin_amdgcn_readfirstlane(rest_s[wave]));
+        len = (int)(b1 - b0);
+        if (rest < len) direct(rest);
+    }
 #pragma unroll
     for (int i = 0; i < WQ / 64; ++i) {
         const int64_t qi = qbase + 64 * i + lane;

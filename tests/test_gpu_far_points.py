@@ -104,3 +104,23 @@ def test_one_far_point_is_not_slow(ch, metric, d, kind):
     far = seconds(lambda a=dev(A), b=dev(B): ch.chamfer_exact(a, b, metric))
     print(f"[times] metric={metric} d={d} {kind}: {plain:.3f} and {far:.3f} ms", flush=True)
     assert far < 4 * plain
+
+
+@pytest.mark.parametrize("kind", ["both 1%", "A far beside"])
+def test_points_without_a_bound_are_not_slow(ch, kind):
+    """Three dimensions, where the vector form took the same time on any data."""
+    plain = [dev(x) for x in clouds("A 1e2", 40000, 40000, 3)]
+    far = [dev(x) for x in clouds(kind, 40000, 40000, 3)]
+    t = [seconds(lambda c=c: ch.chamfer_exact(c[0], c[1], L2)) for c in (plain, far)]
+    print(f"[times] exact {kind}: {t[0]:.3f} and {t[1]:.3f} ms", flush=True)
+    assert t[1] < 4 * t[0]
+
+
+def test_draws_without_a_bound_are_not_slow(ch):
+    """All draws are one far point: no row is ruled out for any of them."""
+    A, B = clouds("A 1e9", 100000, 100000, 3)
+    plain = [dev(x) for x in clouds("A 1e2", 100000, 100000, 3)]
+    t = [seconds(lambda c=c: ch.chamfer_estimate(c[0], c[1], L2, 0.1, 0, 3))
+         for c in (plain, [dev(A), dev(B)])]
+    print(f"[times] estimate: {t[0]:.3f} and {t[1]:.3f} ms", flush=True)
+    assert t[1] < 2 * t[0]
