@@ -26,6 +26,7 @@
 // exact 30000^2 x 100, which the VALU form takes in its any-dimension kernel: 33.4
 // and 1.4 ms.
 #include <cfloat>
+#include <climits>
 #include <cmath>
 
 #include "internal.h"
@@ -55,6 +56,15 @@ __device__ __forceinline__ unsigned long long sad_pack(float v, int64_t b) {
 // Entries of a wavefront's queue; half full, it is evaluated.
 constexpr int kSadQueue = 384;
 constexpr int kSadRowBits = 24;  // chunk rows in an entry (8 bits of query)
+// A workgroup one of whose wavefronts has queued this many entries and eight per row of
+// its chunk, or holds this many queries that no bound reaches, evaluates the rest of
+// the chunk in full (direct): a row costs a wavefront's 128 queries 4 d vector
+// operations there, an entry about a fifth of that.  An estimate whose draws are all
+// one point at 10^9 times the extent: 2 10^5 x 64 27 -> 2.1 ms, 6 10^4 x 100 15.4 ->
+// 1.2; with four queries, exact 20000^2 x 64 with a hundredth of both clouds there took
+// 2.0 ms instead of 0.8.
+constexpr int kSadPlainFirst = 8192;
+constexpr int kSadPlainQueries = 16;
 
 // Up to 16 coordinates from k0 of a row, in registers (clamped past d).
 __device__ __forceinline__ void sad_load(const float *__restrict__ x, int d, int k0, bool quads,
@@ -125,6 +135,10 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
     __shared__ uint32_t thr_s[4][WQ];
     __shared__ uint32_t top_s[4][WQ];  // settle: each query's least queued sum
     __shared__ int32_t row_s[4][WQ];
+    // a word per wavefront: the workgroup is to end its tiles and go on with direct;
+    // from this row; entries queued so far
+    __shared__ __attribute__((aligned(16))) uint32_t plain_s[2][4];
+    __shared__ int32_t rest_s[4], evals_s[4];
 
     if (p->status != CHAMFER_OK) return;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -135,10 +149,10 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
     chunk_major(blk.id, nq, nchunk, cb, qb);
     const int64_t b0 = (int64_t)cb * chunk, b1 = min(nB, b0 + chunk);
     if (b0 >= b1) return;  // uniform over the workgroup
-    const int len = (int)(b1 - b0);
+    int len = (int)(b1 - b0);
     const int64_t qbase = qb * wgq + (int64_t)(wave & (qw - 1)) * WQ;
     const int phase = wave / qw, step4 = 4 / qw * 4;  // its first row group, rows to the next
-    const bool active = qbase < nx;
+    bool active = qbase < nx;
     const float inv = p->sad_inv;
     const bool inbox = p->sad_in != 0;
     const bool quads = (d & 3) == 0 && ((reinterpret_cast<uintptr_t>(X) |
@@ -186,6 +200,7 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
     // ---- the queries: bytes in registers, thresholds
     uint32_t x[Q][W];
     uint32_t thr[Q], marg[Q];
+    int none = 0;  // queries without a bound
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
         const int q = 64 * j + lane;
@@ -227,6 +242,8 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
                                              __HIP_MEMORY_SCOPE_AGENT));
         }
         thr[j] = t;
+        const float lost = inv == 0.0f ? INFINITY : inbox ? mg : ex;
+        none += __popcll(__ballot(live && !(lost < 255.0f * (float)d)));
         // lanes without a query: no sum is below E - d / 2 - 1 >= 1
         if (!live) marg[j] = 0u;
         thr_s[wave][q] = t;
@@ -236,6 +253,10 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
     }
     land(0);
     if (TR < len) fetch(TR);
+    evals_s[wave] = 0;
+    rest_s[wave] = INT_MAX;
+    plain_s[0][wave] = 0u;
+    plain_s[1][wave] = none >= kSadPlainQueries ? 1u : 0u;
 
     auto sync_lds = [] {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -308,7 +329,14 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
         }
         sync_lds();
     };
-    auto settle = [&] {
+    auto settle = [&](int t, int step) {
+        const int evals = evals_s[wave] + cnt;
+        evals_s[wave] = evals;
+        if (__builtin_amdgcn_readfirstlane(evals) > kSadPlainFirst + 2 * qw * t) {
+            active = false;
+            rest_s[wave] = t;
+            plain_s[(step >> 2) & 1][wave] = 1u;
+        }
         // thresholds to LDS and to the other workgroups, and theirs
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
@@ -400,7 +428,87 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
         for (int j = 0; j < Q; ++j) thr[j] = min(thr[j], thr_s[wave][64 * j + lane]);
     };
 
+    // Every row from t on (the wavefront's groups) for its queries: eight rows and four
+    // coordinates at a time, a lane with queries l and l + 64, rows wave-uniform (scalar
+    // loads).
+    auto direct = [&](int t) {
+        constexpr int NR = 8;
+        const CH_RO float *xr[Q];
+        uint32_t bv[Q];
+        int bi[Q];
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            xr[j] = ro(X) + (int64_t)row_s[wave][64 * j + lane] * d;
+            bv[j] = 0xffffffffu;
+            bi[j] = 0;
+        }
+        // (a tile's groups of four: the wavefronts share them as in the tile loop)
+        int r = 4 * phase;
+#pragma unroll 1
+        for (; t < len; r = 4 * phase, t += TR)
+#pragma unroll 1
+          for (; r < TR && t + r < len; r += 2 * step4) {
+            const CH_RO float *b[NR];
+            int row[NR];
+            float acc[NR][Q] = {};
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const int g = r + (i >> 2) * step4;
+                row[i] = g < TR ? t + g + (i & 3) : len;
+                b[i] = ro(B) + (b0 + min(row[i], len - 1)) * d;
+            }
+            int k = 0;
+#pragma unroll 1
+            for (; k + 4 <= d; k += 4) {
+                float x[Q][4];
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    if (quads) {
+                        const float4 u = ld(reinterpret_cast<const CH_RO float4 *>(xr[j] + k));
+                        x[j][0] = u.x, x[j][1] = u.y, x[j][2] = u.z, x[j][3] = u.w;
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) x[j][c] = xr[j][k + c];
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int i = 0; i < NR; ++i) {
+                        const float bk = b[i][k + c];
+#pragma unroll
+                        for (int j = 0; j < Q; ++j) acc[i][j] += fabsf(x[j][c] - bk);
+                    }
+            }
+#pragma unroll 1
+            for (; k < d; ++k)
+#pragma unroll
+                for (int i = 0; i < NR; ++i)
+#pragma unroll
+                    for (int j = 0; j < Q; ++j) acc[i][j] += fabsf(xr[j][k] - b[i][k]);
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {  // (bits order like the values, NaN last)
+                    const uint32_t a = __float_as_uint(acc[i][j]);
+                    if (a < bv[j] && row[i] < len) bv[j] = a, bi[j] = row[i];
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < Q; ++j)
+            if (bv[j] != 0xffffffffu)
+                atomicMin(&best_s[wave][64 * j + lane],
+                          ((unsigned long long)bv[j] << 32) | (uint32_t)(b0 + bi[j]));
+    };
+
     __syncthreads();
+    // (four steps write one set of words, read after the barrier of the last of them;
+    // by the time that it is written again every wavefront has passed that read)
+    auto any_plain = [&](int g) {
+        const uint4 w = *reinterpret_cast<const uint4 *>(plain_s[g & 1]);
+        return __builtin_amdgcn_readfirstlane((int)(w.x | w.y | w.z | w.w)) != 0;
+    };
+    if (any_plain(1)) len = 0;
     for (int t = 0, slot = 0, step = 0;; t += TR, slot ^= 1, ++step) {
         const bool more = t + TR < len;  // uniform
         if (more) land(slot ^ 1);
@@ -424,12 +532,12 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
                 const bool whole = tries == 3;
                 if (!full || whole) r += step4;
                 const bool end = !(r < TR && t + r < len);
-                if (full || cnt >= QN / 2 || (end && !more && cnt > 0)) settle();
+                if (full || cnt >= QN / 2 || (end && !more && cnt > 0)) settle(t, step);
                 if (whole) {
                     evaluate(t + r - step4);
                     tries = 0;
                 }
-                if (end) break;
+                if (end || !active) break;
             }
         }
         if (!more) break;
@@ -441,8 +549,13 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
                                                        __HIP_MEMORY_SCOPE_AGENT));
         }
         __syncthreads();
+        if ((step & 3) == 3 && any_plain(step >> 2)) len = min(len, t + 2 * TR);
     }
-    if (!active) return;
+    if (qbase >= nx) return;
+    const int rest = min(len, __builtin_amdgcn_readfirstlane(rest_s[wave]));
+    len = (int)(b1 - b0);
+    if (rest < len) direct(rest);
+    sync_lds();
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
         const int64_t qi = qbase + 64 * j + lane;
