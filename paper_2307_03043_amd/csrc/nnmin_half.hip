@@ -78,9 +78,13 @@ __device__ __forceinline__ unsigned long long half_pack(float v, int64_t b) {
 // ------------------------------------------------------------- row tables
 
 // Rows per thread group.  B's maxima cost two global atomics per workgroup, so
-// its workgroups take four; the few rows of a draw are spread as wide as they go
-// (2000 x 128 draws: 6.9 us with four passes, 4.6 with one).
-__host__ __device__ inline int half_row_passes(bool isB) { return isB ? 4 : 1; }
+// its workgroups take four once they fill the chip; few rows, and those of a draw, are
+// spread as wide as they go (2000 x 128 draws: 6.9 us with four passes, 4.6 with one;
+// 2500 queries and 20001 rows x 16: 9.3 and 5).
+constexpr int64_t kHalfRowsWide = 1 << 18;
+__host__ __device__ inline int half_row_passes(int64_t n, int slots, bool isB) {
+    return isB && n * (slots / 8) > kHalfRowsWide ? 4 : 1;
+}
 
 // Rows of 12 <= d <= 256 coordinates: slots / 8 consecutive lanes per row, 8
 // coordinates each.  For queries (rows may pick them) stat[r] = (|z|^2, |z|
@@ -101,7 +105,7 @@ __device__ __forceinline__ void half_rows(const float *__restrict__ X,
     const auto *cen = half_centre(lohi, d);
     const int64_t total = n * per;
     const HalfErr he_ = half_err(d, slots);
-    const int passes = half_row_passes(nbh != nullptr);
+    const int passes = half_row_passes(n, slots, nbh != nullptr);
     uint32_t my = 0u, me = 0u;
 #pragma unroll 1
     for (int64_t t = blk.id * (256 * passes) + threadIdx.x, i = 0; i < passes && t < total;
@@ -181,7 +185,7 @@ __global__ __launch_bounds__(256) void k_half_rows(
 }
 
 int64_t half_row_blocks(int64_t n, int d, bool isB) {
-    const int64_t per_wg = 256 * half_row_passes(isB);
+    const int64_t per_wg = 256 * half_row_passes(n, half_slots(d), isB);
     return (n * (half_slots(d) / 8) + per_wg - 1) / per_wg;
 }
 
@@ -671,9 +675,11 @@ __device__ __forceinline__ void nnmin_half(
     // thresholds of the rows evaluated meanwhile; one that fills the queue a third
     // time (duplicates) is evaluated in full.
     int from_nb = 0, tries = 0;
-    // scan: nothing is queued, the scores only raise the thresholds (256 slots, the
-    // first tile, before its rows are queued: 280 draws of 3000 rows 114 -> 108 us;
-    // at fewer slots, with twice the queries, it cost as much as it saved).
+    // scan: nothing is queued, the scores only raise the thresholds, the first tile,
+    // before its rows are queued.  At 256 slots (280 draws of 3000 rows 114 -> 108 us),
+    // and on small launches whose queries start without a distance (2000 x 10000 x 20
+    // 50.6 -> 46.5, 2500 x 20001 x 16 59.3 -> 58.7); with twice the queries, or with
+    // one, it cost as much as it saved.
     auto compute = [&](const uint8_t *tile, int t, int hh, bool scan) {
 #pragma unroll 1
         for (; hh < NH; hh += 2) {
@@ -972,7 +978,7 @@ __device__ __forceinline__ void nnmin_half(
         }
         if (wave_active) {
             int hh = wave & 1;
-            bool scan = DP == 256 && step == 0;
+            bool scan = step == 0 && (DP == 256 || (!RAW && DP <= 64 && NB == 2 && seed == nullptr));
             do {
                 hh = compute(tiles + slot * TB, t, hh, scan);
                 if (scan) {

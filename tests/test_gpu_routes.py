@@ -1,0 +1,59 @@
+"""GPU parity of the exact passes on both sides of the lines between their forms:
+bit for bit the oracle's float32 search, whichever form a size takes."""
+
+import numpy as np
+import pytest
+
+import workloads
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+L1, L2 = 1, 2
+
+
+@pytest.fixture(scope="module")
+def ch():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2307_03043_amd as lib
+    lib.lib()
+    return lib
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to("cuda:0")
+
+
+def same(got_min, got_nn, ref):
+    torch.cuda.synchronize()
+    m32, a32 = ref
+    assert np.array_equal(got_nn.cpu().numpy(), a32)
+    assert np.array_equal(got_min.cpu().numpy().view(np.uint32), m32.view(np.uint32))
+
+
+def check(ch, orc, n_a, n_b, d, metric, rows):
+    """All rows of A against a sample of the oracle's: the product is large."""
+    A, B = workloads.clusters_l2(seed=n_a + n_b + d, n=n_a, d=d, k=20, n_b=n_b)
+    print(f"[case] metric={metric} n_a={n_a} n_b={n_b} d={d}", flush=True)
+    idx = np.unique(np.random.default_rng(d).integers(0, n_a, rows)).astype(np.int32)
+    ref = orc.nn_f32(A, B, metric, rows=idx)
+    _, rmin, rnn = ch.chamfer_exact(dev(A), dev(B), metric)
+    pick = torch.from_numpy(idx.astype(np.int64)).to("cuda:0")
+    same(rmin[pick], rnn[pick], ref)
+    mn, arg = ch.chamfer_nn_min(dev(A), dev(B), metric, rows=torch.from_numpy(idx).to("cuda:0"))
+    same(mn, arg, ref)
+
+
+# the table of B in one pass of 256 units a workgroup and in four (2^18 units of eight
+# coordinates), and a small launch's first scan with B of one tile and a little more
+@pytest.mark.parametrize("d,n_b", [(20, 65536), (20, 65537), (64, 32768), (64, 32769),
+                                   (200, 8192), (200, 8193)])
+def test_row_tables(ch, orc, d, n_b):
+    check(ch, orc, 70, n_b, d, L2, 70)
+
+
+@pytest.mark.parametrize("d", [12, 32, 33, 64])
+@pytest.mark.parametrize("n_a,n_b", [(300, 127), (300, 129), (2000, 5000)])
+def test_first_scan(ch, orc, d, n_a, n_b):
+    check(ch, orc, n_a, n_b, d, L2, 300)
