@@ -122,13 +122,17 @@ int64_t default_samples(int64_t nA, double eps) {
     return T < 1 ? 1 : T;
 }
 
-// Whether the exact pass takes the l1 byte form, and whether it needs a box or
-// centre of B (launch_calib_final).
+// Whether the exact pass takes the l2 matrix-core form or the l1 byte form, and
+// whether it needs a box or centre of B (launch_calib_final).  seeded: the queries
+// have distances to start from (an estimate's draws after CrudeNN).
+bool half_pass(int64_t nx, int64_t nB, int d, int metric, bool seeded) {
+    return half_supported(d, metric) && half_pays(nx, nB, d, seeded);
+}
 bool sad_pass(int64_t nx, int64_t nB, int d, int metric) {
     return sad_supported(d, metric) && sad_pays(nx, nB, d);
 }
-bool boxed(int64_t nx, int64_t nB, int d, int metric) {
-    return half_supported(d, metric) || sad_pass(nx, nB, d, metric);
+bool boxed(int64_t nx, int64_t nB, int d, int metric, bool seeded) {
+    return half_pass(nx, nB, d, metric, seeded) || sad_pass(nx, nB, d, metric);
 }
 
 // Validate and lay out the workspace.  estimating: the entry point draws T
@@ -201,10 +205,10 @@ int make_plan(Plan &pl, int64_t nA, int64_t nB, int32_t d, int32_t metric, doubl
     // that one fill resets both
     const size_t room = h ? table_bytes(pl.L, lc, pl.window) : 0;
     const size_t gb = (size_t)(estimating ? pl.T : nA) * sizeof(uint32_t);
-    const bool half_pass = !lowp_supported(d, metric, o.precision) && half_supported(d, metric);
-    if (!half_pass && !sad_supported(d, metric)) pl.thr_copies = 0;
+    const bool matrix = !lowp_supported(d, metric, o.precision) && half_supported(d, metric);
+    if (!matrix && !sad_supported(d, metric)) pl.thr_copies = 0;
     else if (!estimating) pl.thr_copies = 1;
-    else if (half_pass && half_copies(pl.T, nB) * gb <= room) pl.thr_copies = half_copies(pl.T, nB);
+    else if (matrix && half_copies(pl.T, nB) * gb <= room) pl.thr_copies = half_copies(pl.T, nB);
     else pl.thr_copies = gb <= room ? 1 : 0;
     pl.off_gthr = estimating ? pl.off_tables : take(pl.thr_copies * gb);
     pl.off_partial = take((size_t)(nn_finalize_blocks(nrow) + 1) * sizeof(double));
@@ -274,7 +278,7 @@ int hash_prologue(const Plan &pl, const float *A, const float *B, uint64_t seed,
                               hipMemcpyHostToDevice, st));
     }
     CH_TRY(launch_minmax_pair(A, pl.nA, B, pl.nB, pl.d, lohi, p, st));
-    const float *box = boxed(pl.T, pl.nB, pl.d, pl.metric) ? B : nullptr;
+    const float *box = boxed(pl.T, pl.nB, pl.d, pl.metric, true) ? B : nullptr;
     CH_TRY(launch_calib_final(lohi, pl.d, p, box, pl.nB, pl.metric, A, nullptr, pl.nA, true, st));
     return CHAMFER_OK;
 }
@@ -348,8 +352,8 @@ int crude_core(const Plan &pl, const float *A, const float *B, uint64_t seed, fl
 
 // Exact pass over queries (rows of X, or X[rows[q]]): the low-precision
 // form when requested and supported, else the float32 result (FP16 matrix
-// cores and canonical distances for l2 where half_supported, after the
-// calibration with B; vector ALU otherwise).  B_ready: B's FP16 table is
+// cores or byte differences and canonical distances where half_pass or
+// sad_pass, after the calibration with B; vector ALU otherwise).  B_ready: B's FP16 table is
 // already in the workspace.  seed (may be null): seed[row of X] bounds the
 // distance of the query from above.
 int nn_pass(const Plan &pl, void *ws, const float *X, const int32_t *rows, int64_t nx,
@@ -366,7 +370,7 @@ int nn_pass(const Plan &pl, void *ws, const float *X, const int32_t *rows, int64
                                  best, p, st));
         return CHAMFER_OK;
     }
-    if (half_supported(pl.d, pl.metric)) {
+    if (half_pass(nx, nB, pl.d, pl.metric, seed != nullptr)) {
         const uint32_t *lohi = at<uint32_t>(ws, pl.off_lohi);
         uint16_t *bs = nullptr, *xs = nullptr;
         float *nbh = nullptr;
@@ -631,7 +635,7 @@ int chamfer_exact(const float *A, const float *B, int64_t n_A, int64_t n_B, int3
     double *partial = at<double>(ws, pl.off_partial);
     CH_TRY(launch_init_params(p, lohi, d, st));
     CH_TRY(launch_minmax_pair(A, n_A, B, n_B, d, lohi, p, st));
-    const float *box = boxed(n_A, n_B, d, metric) ? B : nullptr;
+    const float *box = boxed(n_A, n_B, d, metric, false) ? B : nullptr;
     CH_TRY(launch_calib_final(lohi, d, p, box, n_B, metric, A, nullptr, n_A, true, st));
     CH_TRY(launch_fill_u64(best, reset_words(pl), ~0ull, st));
     if ((rc = nn_pass(pl, ws, A, nullptr, n_A, B, n_B, best, p, st))) return rc;
@@ -652,7 +656,7 @@ int chamfer_nn_min(const float *X, const int32_t *rows, int64_t n_x, const float
     hipStream_t st = static_cast<hipStream_t>(stream);
     DevParams *p = at<DevParams>(ws, pl.off_params);
     auto *best = at<unsigned long long>(ws, pl.off_best);
-    if (!lowp_supported(d, metric, pl.precision) && boxed(n_x, n_B, d, metric)) {
+    if (!lowp_supported(d, metric, pl.precision) && boxed(n_x, n_B, d, metric, false)) {
         // the scale and centre of the exact pass, from B and a few of the queries
         // (the number of rows of X is not known here); inputs are not checked
         uint32_t *lohi = at<uint32_t>(ws, pl.off_lohi);
@@ -717,7 +721,7 @@ int chamfer_estimate(const float *A, const float *B, int64_t n_A, int64_t n_B, i
         CH_TRY(mark(ev, 0, st));
         CH_TRY(launch_init_params(p, lohi, d, st));
         CH_TRY(launch_minmax_pair(A, n_A, B, n_B, d, lohi, p, st));
-        const float *box = boxed(pl.T, n_B, d, metric) ? B : nullptr;
+        const float *box = boxed(pl.T, n_B, d, metric, false) ? B : nullptr;
         CH_TRY(launch_calib_final(lohi, d, p, box, n_B, metric, A, nullptr, n_A, true, st));
         CH_TRY(mark(ev, 1, st));
         CH_TRY(mark(ev, 2, st));

@@ -603,6 +603,7 @@ __host__ __device__ inline int half_copies(int64_t nx, int64_t nB) {
     return nx < 16384 && (nB < 262144 || nx < 1024) ? 8 : 1;
 }
 bool half_supported(int d, int metric);
+bool half_pays(int64_t nx, int64_t nB, int d, bool seeded);  // against launch_nnmin, direct launches
 bool half_tabled(int d);
 size_t half_table_bytes(int64_t n, int d);
 int64_t half_row_blocks(int64_t n, int d, bool isB);

@@ -56,6 +56,18 @@ bool half_supported(int d, int metric) {
     return metric == CHAMFER_L2 && (d <= kHalfRawDim || (d >= 12 && d <= 256));
 }
 bool half_tabled(int d) { return d > kHalfRawDim; }
+
+// Three dimensions have a compiled vector form, which starts and ends faster.  A pass
+// whose queries have no distance to start from (seeded: they do) takes it while B is
+// small, or the product is (exact calls in us, matrix cores and vector: 10^6 x 1000 350
+// and 208, 10^5 x 10^4 198 and 184, 10^5 x 20000 297 and 342; 30000^2 181 and 172,
+// 60000 x 30000 263 and 317; 10000 x 40000 97 and 92, 20000 x 40000 141 and 161;
+// 400 x 10^5 58 and 55, 5000 x 10^5 117 and 120, 1500 x 150000 83 and 92).
+bool half_pays(int64_t nx, int64_t nB, int d, bool seeded) {
+    if (d != 3 || seeded) return true;
+    const double pairs = (double)nx * (double)nB;
+    return nB > 12288 && pairs > (nB <= 32768 ? 9e8 : nB <= 100000 ? 4e8 : 0.0);
+}
 size_t half_table_bytes(int64_t n, int d) { return (size_t)n * half_slots(d) * 2; }
 
 // Bound of the relative error of the canonical accumulator against the exact

@@ -57,3 +57,21 @@ def test_row_tables(ch, orc, d, n_b):
 @pytest.mark.parametrize("n_a,n_b", [(300, 127), (300, 129), (2000, 5000)])
 def test_first_scan(ch, orc, d, n_a, n_b):
     check(ch, orc, n_a, n_b, d, L2, 300)
+
+
+# three dimensions, l2: the vector form up to 12288 rows, and on small products
+@pytest.mark.parametrize("n_a,n_b", [(73300, 12288), (73300, 12289), (73200, 12289),
+                                     (30000, 30000), (30001, 30000), (27000, 32768),
+                                     (13000, 32769), (12000, 32769), (4000, 100000),
+                                     (4001, 100000), (50, 100001), (50, 100000)])
+def test_points(ch, orc, n_a, n_b):
+    check(ch, orc, n_a, n_b, 3, L2, 200)
+
+
+@pytest.mark.parametrize("n_b", [500, 40000])
+def test_points_uniform_draws(ch, orc, n_b):
+    A, B = workloads.clusters_l2(seed=n_b, n=3000, d=3, k=20, n_b=n_b)
+    out = ch.chamfer_estimate(dev(A), dev(B), L2, 0.2, 300, 3, sampling=ch.UNIFORM)
+    torch.cuda.synchronize()
+    idx = out["sample_idx"].cpu().numpy()
+    same(out["sample_min"], out["sample_nn"], orc.nn_f32(A, B, L2, rows=idx))
