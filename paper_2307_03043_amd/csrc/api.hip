@@ -128,11 +128,11 @@ int64_t default_samples(int64_t nA, double eps) {
 bool half_pass(int64_t nx, int64_t nB, int d, int metric, bool seeded) {
     return half_supported(d, metric) && half_pays(nx, nB, d, seeded);
 }
-bool sad_pass(int64_t nx, int64_t nB, int d, int metric) {
-    return sad_supported(d, metric) && sad_pays(nx, nB, d);
+bool sad_pass(int64_t nx, int64_t nB, int d, int metric, bool seeded) {
+    return sad_supported(d, metric) && sad_pays(nx, nB, d, seeded);
 }
 bool boxed(int64_t nx, int64_t nB, int d, int metric, bool seeded) {
-    return half_pass(nx, nB, d, metric, seeded) || sad_pass(nx, nB, d, metric);
+    return half_pass(nx, nB, d, metric, seeded) || sad_pass(nx, nB, d, metric, seeded);
 }
 
 // Validate and lay out the workspace.  estimating: the entry point draws T
@@ -388,7 +388,7 @@ int nn_pass(const Plan &pl, void *ws, const float *X, const int32_t *rows, int64
                                  p, st));
         return CHAMFER_OK;
     }
-    if (sad_pass(nx, nB, pl.d, pl.metric)) {
+    if (sad_pass(nx, nB, pl.d, pl.metric, seed != nullptr)) {
         CH_TRY(launch_nnmin_sad(X, rows, nx, seed, B, nB, pl.d, at<uint32_t>(ws, pl.off_lohi), best,
                                 pl.thr_copies ? at<uint32_t>(ws, pl.off_gthr) : nullptr, p, st));
         return CHAMFER_OK;

@@ -603,7 +603,7 @@ __host__ __device__ inline int half_copies(int64_t nx, int64_t nB) {
     return nx < 16384 && (nB < 262144 || nx < 1024) ? 8 : 1;
 }
 bool half_supported(int d, int metric);
-bool half_pays(int64_t nx, int64_t nB, int d, bool seeded);  // against launch_nnmin, direct launches
+bool half_pays(int64_t nx, int64_t nB, int d, bool seeded);  // against launch_nnmin
 bool half_tabled(int d);
 size_t half_table_bytes(int64_t n, int d);
 int64_t half_row_blocks(int64_t n, int d, bool isB);
@@ -615,18 +615,18 @@ hipError_t launch_nnmin_half(const float *X, const int32_t *rows, int64_t nx, co
                              const uint16_t *Bs, int64_t nB, int d, const float *nbh,
                              const uint32_t *lohi, unsigned long long *best, uint32_t *gthr,
                              int copies, DevParams *p, hipStream_t st);
-// Low-precision (BF16 / FP8-E4M3) l2 nearest neighbours with float32 re-rank.
 // The l1 exact pass on byte differences (9 <= d <= 256), after launch_calib_final
 // with B: returns the canonical float32 minima.  seed (may be null): seed[row of X]
 // bounds the query's distance from above.  best [nx] and gthr [nx] (may be null)
 // start as all ones.
 constexpr int kSadMinDim = 8;
 bool sad_supported(int d, int metric);
-bool sad_pays(int64_t nx, int64_t nB, int d);  // against launch_nnmin, direct launches
+bool sad_pays(int64_t nx, int64_t nB, int d, bool seeded);  // against launch_nnmin
 hipError_t launch_nnmin_sad(const float *X, const int32_t *rows, int64_t nx, const float *seed,
                             const float *B, int64_t nB, int d, const uint32_t *lohi,
                             unsigned long long *best, uint32_t *gthr, DevParams *p,
                             hipStream_t st);
+// Low-precision (BF16 / FP8-E4M3) l2 nearest neighbours with float32 re-rank.
 int lowp_dpad(int d, int precision);
 bool lowp_supported(int d, int metric, int precision);
 size_t lowp_row_bytes(int d, int precision);

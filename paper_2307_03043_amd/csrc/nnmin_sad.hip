@@ -35,13 +35,25 @@ namespace chamfer {
 
 bool sad_supported(int d, int metric) { return metric == CHAMFER_L1 && d > kSadMinDim && d <= 256; }
 
-// At the dimensions that the VALU form is compiled for it starts and ends faster,
-// and is kept for small products (whole calls in us, bytes and VALU: exact 2500 x
-// 20001 x 16, 8e8 products: 91 and 67; 1800 draws of 3000 x 64, 3e8: 273 and 267;
-// 475 draws of 50000 x 128, 3e9: 318 and 363; 1600 of 50000 x 32, 3e9: 219 and 236).
-bool sad_pays(int64_t nx, int64_t nB, int d) {
-    const bool fixed = d == 16 || d == 32 || d == 64 || d == 128;
-    return !fixed || (double)nx * (double)nB * d >= 2e9;
+// At the dimensions that the VALU form is compiled for it starts and ends faster: a
+// query without a distance to start from (seeded: it has one) first meets rows that
+// its threshold does not rule out.  Bytes need a product that makes up for that, and
+// at d = 16, where they hardly save operations, a long B.  Calls in us, VALU and bytes:
+// d = 16, 10^6 x 1000 565 and 953, 20000^2 252 and 298, 10^5 x 20000 1114 and 947; 1700
+// draws of 10^5 rows 270 and 281, 2000 of 10^5 612 and 604.  d = 32, 10^5 x 2000 253 and
+// 280, 2500 x 100000 301 and 237; 450 draws of 2 10^5 379 and 442, 1600 of 50000 234 and
+// 211.  d = 64, 10^5 x 1000 261 and 292, 10^6 x 1000 2116 and 1879, 2500 x 20001 160 and
+// 134; 400 draws of 50000 217 and 241.  d = 128, 300 draws of 4096 154 and 164, 400 of
+// 50000 372 and 318.
+bool sad_pays(int64_t nx, int64_t nB, int d, bool seeded) {
+    const double pairs = (double)nx * (double)nB;
+    switch (d) {
+        case 16: return seeded ? nB >= 65536 && pairs >= 2e8 : nB >= 16384 && pairs >= 5e8;
+        case 32: return pairs >= 2.5e8 || (seeded && nx >= 1024 && pairs >= 7e7);
+        case 64: return pairs >= 3e7 && (seeded || nB >= 2048 || pairs >= 5e8);
+        case 128: return pairs >= 1.6e7;
+        default: return true;
+    }
 }
 
 // Dwords per row: whole 16-byte units.

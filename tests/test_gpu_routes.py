@@ -75,3 +75,24 @@ def test_points_uniform_draws(ch, orc, n_b):
     torch.cuda.synchronize()
     idx = out["sample_idx"].cpu().numpy()
     same(out["sample_min"], out["sample_nn"], orc.nn_f32(A, B, L2, rows=idx))
+
+
+# l1 at the dimensions that the vector form is compiled for: bytes from a product on
+@pytest.mark.parametrize("d,n_a,n_b", [
+    (16, 30600, 16383), (16, 30600, 16384), (16, 30500, 16384),
+    (32, 2500, 99999), (32, 2500, 100000),
+    (64, 14700, 2047), (64, 14700, 2048), (64, 300, 99999), (64, 300, 100000),
+    (128, 160, 99999), (128, 160, 100000)])
+def test_l1(ch, orc, d, n_a, n_b):
+    check(ch, orc, n_a, n_b, d, L1, 100)
+
+
+@pytest.mark.parametrize("d,n_b,T", [(16, 65535, 3200), (16, 65536, 3200), (32, 69000, 1023),
+                                     (32, 69000, 1024), (64, 2000, 15001), (64, 2000, 14999)])
+def test_l1_draws(ch, orc, d, n_b, T):
+    A, B = workloads.clusters_l2(seed=n_b, n=3000, d=d, k=20, n_b=n_b)
+    print(f"[case] draws n_b={n_b} d={d} T={T}", flush=True)
+    out = ch.chamfer_estimate(dev(A), dev(B), L1, 0.2, T, 3)
+    torch.cuda.synchronize()
+    idx = out["sample_idx"].cpu().numpy()[:100]
+    same(out["sample_min"][:100], out["sample_nn"][:100], orc.nn_f32(A, B, L1, rows=idx))
