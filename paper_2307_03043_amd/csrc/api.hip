@@ -477,10 +477,10 @@ int job_prepare(const float *A, const float *B, int64_t nA, int64_t nB, int32_t 
     J.nb_grid = (int32_t)grid_table_blocks(pl.L, pl.kh);
     J.nb_fill = (int32_t)table_fill_blocks((size_t)J.table_count);
     int64_t blocks, stride;
-    minmax_geom(nA, d, true, &blocks, &stride);
+    minmax_geom(nA, d, true, &blocks, &stride, true);
     J.nb_mmA = (int32_t)blocks;
     J.mm_strideA = stride;
-    minmax_geom(nB, d, true, &blocks, &stride);
+    minmax_geom(nB, d, true, &blocks, &stride, true);
     J.nb_mmB = (int32_t)blocks;
     J.mm_strideB = stride;
     J.nb_hashB = (int32_t)hash_blocks(nB);
@@ -492,16 +492,17 @@ int job_prepare(const float *A, const float *B, int64_t nA, int64_t nB, int32_t 
         J.nb_castB = (int32_t)cast_blocks(nB);
         J.nb_castX = (int32_t)cast_blocks(pl.T);
         g = lowp_geom(pl.T, nB, d, pl.precision);
+    } else if (batch_vector(pl.T, nB, d, metric)) {
+        J.nn_vector = 1;
+        g = valu_geom(pl.T, nB, d);
     } else if (half) {
         if (tabled) {
             J.nb_castB = (int32_t)half_row_blocks(nB, d, true);
             J.nb_castX = (int32_t)half_row_blocks(pl.T, d, false);
         }
-        g = half_geom(pl.T, nB, d);
-    } else if (sad_supported(d, metric)) {
-        g = sad_geom(pl.T, nB, d, 0, J.nn_qw);
+        g = half_batch_geom(pl.T, nB, d);
     } else {
-        g = valu_geom(pl.T, nB, d);
+        g = sad_geom(pl.T, nB, d, 0, J.nn_qw);
     }
     J.nn_chunk = g.chunk;
     J.nn_nchunk = g.nchunk;
@@ -529,18 +530,24 @@ void job_share_nn(Job *jobs, int n) {
     if (n <= 1) return;
     const Job &J0 = jobs[0];
     if (lowp_supported(J0.d, J0.metric, J0.precision)) return;
-    const bool half = half_supported(J0.d, J0.metric), sad = sad_supported(J0.d, J0.metric);
-    double total = 0.0;
-    for (int j = 0; j < n; ++j) total += (double)jobs[j].T * (double)jobs[j].nB;
-    const double target =
-        half || sad ? (double)half_target_wgs(J0.d) : (double)kValuTargetWGs;
+    const bool half = half_supported(J0.d, J0.metric);
+    double total = 0.0, vector = 0.0;
+    for (int j = 0; j < n; ++j) {
+        const double w = (double)jobs[j].T * (double)jobs[j].nB;
+        total += w;
+        if (jobs[j].nn_vector) vector += w;
+    }
+    // one form for all: each of two would leave part of the device idle in its turn
+    const bool all = vector * 2.0 >= total;
+    const double target = all ? (double)kValuTargetWGs : (double)half_target_wgs(J0.d);
     for (int j = 0; j < n; ++j) {
         Job &J = jobs[j];
+        J.nn_vector = all;
         const double share = target * ((double)J.T * (double)J.nB) / total;
         const int64_t t = share < 1.0 ? 1 : (int64_t)std::ceil(share);
-        const NNGeom g = half  ? half_geom(J.T, J.nB, J.d, t)
-                         : sad ? sad_geom(J.T, J.nB, J.d, t, J.nn_qw)
-                               : valu_geom(J.T, J.nB, J.d, t);
+        const NNGeom g = all    ? valu_geom(J.T, J.nB, J.d, t)
+                         : half ? half_batch_geom(J.T, J.nB, J.d, t)
+                                : sad_geom(J.T, J.nB, J.d, t, J.nn_qw);
         J.nn_chunk = g.chunk;
         J.nn_nchunk = g.nchunk;
         J.nb_nn = (int32_t)g.blocks;

@@ -228,15 +228,17 @@ __global__ __launch_bounds__(256) void k_minmax4(const float *__restrict__ A, in
 
 bool minmax_wide(int d) { return d <= 2048; }
 
-void minmax_geom(int64_t n, int d, bool wide, int64_t *blocks_out, int64_t *stride_out) {
+void minmax_geom(int64_t n, int d, bool wide, int64_t *blocks_out, int64_t *stride_out,
+                 bool batch) {
     const int64_t total = n * (int64_t)d;
     int64_t blocks;
     if (wide) {
         // float4 per thread: 16 where a block ends with many global atomics
         // (2 d of them; 50000 x 64 points: 11.5 us with 4, 7.6 with 16), 4 for
         // small d, whose clouds are a few MB and would otherwise leave most of
-        // the chip idle
-        const int64_t per = d >= 64 ? 16 : d > 16 ? 8 : 4;
+        // the chip idle (the jobs of a batch fill it: 48 of 8000 x 16 15 us with 4, 9
+        // with 16)
+        const int64_t per = d >= 64 || batch ? 16 : d > 16 ? 8 : 4;
         const int64_t total4 = total / 4, p4 = (d & 3) == 0 ? d / 4 : (d & 1) == 0 ? d / 2 : d;
         blocks = (total4 + 256 * per - 1) / (256 * per);
         if (blocks > 1024) blocks = 1024;

@@ -203,6 +203,7 @@ struct Job {
     uint32_t *gthr;  // float32 l2: thresholds of the exact pass
     int32_t thr_copies;
     int32_t nn_qw;  // l1: wavefronts of a workgroup with queries of their own
+    int32_t nn_vector;  // the exact pass takes this job in the vector form (batch_vector)
     double *eta;
     chamfer_aux aux;
     // geometry
@@ -656,8 +657,9 @@ int64_t init_blocks(int d);
 int64_t grid_table_blocks(int L, int kh);
 int64_t table_fill_blocks(size_t count);
 // minmax over n rows: the 16-byte form when wide (d <= 2048), stride in float4;
-// else in elements
-void minmax_geom(int64_t n, int d, bool wide, int64_t *blocks, int64_t *stride);
+// else in elements.  batch: one of many jobs
+void minmax_geom(int64_t n, int d, bool wide, int64_t *blocks, int64_t *stride,
+                 bool batch = false);
 bool minmax_wide(int d);
 int64_t hash_blocks(int64_t n);
 int64_t scan_blocks(int64_t nA);
@@ -676,8 +678,13 @@ constexpr int64_t kMaxLaunchWGs = 1 << 23;
 int64_t half_launch_queries(int64_t nx, int64_t nB, int d);
 int64_t sad_launch_queries(int64_t nx, int64_t nB, int d);
 NNGeom half_geom(int64_t nx, int64_t nB, int d, int64_t target = 0);
+NNGeom half_batch_geom(int64_t nx, int64_t nB, int d, int64_t target = 0);
 NNGeom sad_geom(int64_t nx, int64_t nB, int d, int64_t target, int32_t &qw);
 int64_t half_target_wgs(int d);  // the direct-launch target of half_geom
+// Whether a job of a batch takes the vector form; batches of the dimensions where
+// there is another one too (batch_both) launch both.
+bool batch_both(int d, int metric);
+bool batch_vector(int64_t T, int64_t nB, int d, int metric);
 constexpr int64_t kValuTargetWGs = 4096;
 NNGeom lowp_geom(int64_t nx, int64_t nB, int d, int precision);
 constexpr int kMaxLdsL1Dim = 240;  // widest l1 tile staged in LDS by the hash

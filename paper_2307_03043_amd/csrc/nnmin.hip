@@ -417,13 +417,16 @@ __device__ __forceinline__ void job_nn_fixed(const Job &J, Blk b) {
 
 template <int METRIC, int D, int QPL>
 __global__ __launch_bounds__(256) void kb_nn_fixed(const Batch *__restrict__ bt) {
-    batch_loop(bt, kBsNN, [&](const Job &J, Blk b) { job_nn_fixed<METRIC, D, QPL>(J, b); });
+    batch_loop(bt, kBsNN, [&](const Job &J, Blk b) {
+        if (J.nn_vector) job_nn_fixed<METRIC, D, QPL>(J, b);
+    });
 }
 
 // Three dimensions: queries per lane by each job's draws.
 template <int METRIC>
 __global__ __launch_bounds__(256) void kb_nn_points(const Batch *__restrict__ bt) {
     batch_loop(bt, kBsNN, [&](const Job &J, Blk b) {
+        if (!J.nn_vector) return;
         switch (valu_qpl(J.T, J.nB, 3)) {
             case 1: job_nn_fixed<METRIC, 3, 1>(J, b); break;
             case 2: job_nn_fixed<METRIC, 3, 2>(J, b); break;
@@ -438,6 +441,32 @@ __global__ __launch_bounds__(256) void kb_nn_any(const Batch *__restrict__ bt) {
         nnmin_any<METRIC, 32, 8>(glb(J.A), glb(J.idx), J.T, glb(J.B), J.nB, J.d, J.nn_chunk,
                                  J.nn_nchunk, glb(J.best), glb(J.p), b);
     });
+}
+
+bool batch_both(int d, int metric) {
+    return metric == CHAMFER_L2 ? d == 3 : d == 16 || d == 32 || d == 64 || d == 128;
+}
+
+// Many jobs fill the chip, so what counts is the work: matrix cores and bytes start a
+// chunk with rows that the vector form would not look at twice, and few draws leave
+// most of its lanes idle.  Whole retrievals in us, vector form and the other (256 jobs
+// of 1000 points, 128 of 3000, 48 of 8000, 16 of 40000): l2, d = 3, 400 draws 666 and
+// 764, 614 and 676, 545 and 552, 879 and 896 (one call with 10^5 rows: the matrix cores,
+// see half_pays).  l1, d = 16, 400 draws 690 and 730, 686 and 680, 657 and 679, 1655 and
+// 1636, 50 draws 659 and 548 at 8000; d = 32, 1600 draws 1123 and 1140, 1267 and 2033,
+// 1294 and 1194; d = 64, 1600 draws 2009 and 1917, 2605 and 3181, 2875 and 1806;
+// d = 128, 1600 draws 2820 and 3690, 3627 and 6594, 3926 and 3399, 200 draws 1113 and
+// 1192, 1264 and 1287, 1384 and 1302.
+bool batch_vector(int64_t T, int64_t nB, int d, int metric) {
+    if (!half_supported(d, metric) && !sad_supported(d, metric)) return true;
+    if (!batch_both(d, metric)) return false;
+    switch (d) {
+        case 3: return nB <= 49152;
+        case 16: return T >= 300 && nB <= 20000;
+        case 32: return T >= 300 && nB <= 6000;
+        case 64: return T >= 1000 && nB <= 4000;
+        default: return T >= 150 && nB <= 4000;
+    }
 }
 
 template <int METRIC>
@@ -455,8 +484,11 @@ static hipError_t batch_valu(const Batch *bt, int d, hipStream_t st) {
 
 hipError_t launch_batch_nn(const Batch *bt, int d, int metric, int precision, hipStream_t st) {
     if (lowp_supported(d, metric, precision)) return launch_batch_lowp(bt, d, precision, st);
-    if (half_supported(d, metric)) return launch_batch_half(bt, d, st);
-    if (sad_supported(d, metric)) return launch_batch_sad(bt, d, st);
+    if (half_supported(d, metric) || sad_supported(d, metric)) {
+        const hipError_t e = metric == CHAMFER_L2 ? launch_batch_half(bt, d, st)
+                                                  : launch_batch_sad(bt, d, st);
+        if (e != hipSuccess || !batch_both(d, metric)) return e;
+    }
     if (metric == CHAMFER_L1) return batch_valu<CHAMFER_L1>(bt, d, st);
     return batch_valu<CHAMFER_L2>(bt, d, st);
 }

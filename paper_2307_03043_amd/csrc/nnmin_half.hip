@@ -1097,6 +1097,13 @@ static NNGeom half_geom(int64_t nx, int64_t nB, int d, bool small, int64_t targe
 NNGeom half_geom(int64_t nx, int64_t nB, int d, int64_t target) {
     return half_geom(nx, nB, d, false, target);
 }
+// Jobs of a batch: few draws each, so a workgroup takes 128 of them where the table is
+// in memory (whole retrievals in us with 256 and 128: 48 pairs of 8000 x 128, 1600
+// draws 1972 and 1696; 256 of 1000 x 20, 400 draws 896 and 763).
+__host__ __device__ constexpr bool half_batch_small(bool raw) { return !raw; }
+NNGeom half_batch_geom(int64_t nx, int64_t nB, int d, int64_t target) {
+    return half_geom(nx, nB, d, half_batch_small(!half_tabled(d)), target);
+}
 
 int64_t half_launch_queries(int64_t nx, int64_t nB, int d) {
     while (nx > 1 && half_geom(nx, nB, d, half_small(nx, nB, d), 0).blocks > kMaxLaunchWGs)
@@ -1173,7 +1180,8 @@ template <int DP, bool RAW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP == 16 ? 3 : 2)))
 void kb_nn_half(const Batch *__restrict__ bt) {
     batch_loop(bt, kBsNN, [&](const Job &J, Blk b) {
-        nnmin_half<DP, RAW, half_nb(DP, false)>(glb(J.A), glb(J.idx), J.T, glb(J.xhalf), glb(J.xstat), glb(J.D),
+        if (J.nn_vector) return;
+        nnmin_half<DP, RAW, half_nb(DP, half_batch_small(RAW))>(glb(J.A), glb(J.idx), J.T, glb(J.xhalf), glb(J.xstat), glb(J.D),
                             glb(J.B), glb(J.bhalf), J.nB, J.d, glb(J.nbh), glb(J.lohi),
                             J.nn_chunk, J.nn_nchunk, glb(J.best), glb(J.gthr),
                             J.thr_copies > 1 ? J.T : 0, glb(J.p), b);

@@ -118,11 +118,101 @@ __device__ __forceinline__ uint4 sad_bytes(const float *v, const float2 *box, fl
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// Every row from t on (the wavefront's groups of four in tiles of TR rows) for its 128
+// queries: eight rows and four coordinates at a time, a lane with queries l and l + 64,
+// rows wave-uniform (scalar loads).
+__device__ __forceinline__ uint4 sad_direct(const float *Xv, int32_t row0, int32_t row1,
+                                            const float *Bv, int tv, int lenv, int dv, int TRv,
+                                            int first, int stepv, int quadsv) {
+    constexpr int NR = 8, Q = 2;
+    auto u32 = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    auto ptr = [&](const float *q) {
+        const uint64_t a = reinterpret_cast<uint64_t>(q);
+        return reinterpret_cast<const float *>(((uint64_t)(uint32_t)u32((int)(a >> 32)) << 32) |
+                                               (uint32_t)u32((int)(uint32_t)a));
+    };
+    const float *B = ptr(Bv);
+    const int len = u32(lenv), d = u32(dv), TR = u32(TRv), step4 = u32(stepv);
+    const bool quads = u32(quadsv) != 0;
+    int t = u32(tv);
+    const CH_RO float *xr[Q];
+    uint32_t bv[Q];
+    int bi[Q];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+        xr[j] = ro(Xv) + (int64_t)(j == 0 ? row0 : row1) * d;
+        bv[j] = 0xffffffffu;
+        bi[j] = 0;
+    }
+    const int r0 = u32(first);
+    int r = r0;
+#pragma unroll 1
+    for (; t < len; r = r0, t += TR)
+#pragma unroll 1
+        for (; r < TR && t + r < len; r += 2 * step4) {
+            const CH_RO float *b[NR];
+            int row[NR];
+            float acc[NR][Q] = {};
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const int g = r + (i >> 2) * step4;
+                row[i] = g < TR ? t + g + (i & 3) : len;
+                b[i] = ro(B) + (int64_t)min(row[i], len - 1) * d;
+            }
+            int k = 0;
+#pragma unroll 1
+            for (; k + 4 <= d; k += 4) {
+                float x[Q][4];
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    if (quads) {
+                        const float4 u = ld(reinterpret_cast<const CH_RO float4 *>(xr[j] + k));
+                        x[j][0] = u.x, x[j][1] = u.y, x[j][2] = u.z, x[j][3] = u.w;
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) x[j][c] = xr[j][k + c];
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int i = 0; i < NR; ++i) {
+                        const float bk = b[i][k + c];
+#pragma unroll
+                        for (int j = 0; j < Q; ++j) acc[i][j] += fabsf(x[j][c] - bk);
+                    }
+            }
+#pragma unroll 1
+            for (; k < d; ++k)
+#pragma unroll
+                for (int i = 0; i < NR; ++i)
+#pragma unroll
+                    for (int j = 0; j < Q; ++j) acc[i][j] += fabsf(xr[j][k] - b[i][k]);
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {  // (bits order like the values, NaN last)
+                    const uint32_t a = __float_as_uint(acc[i][j]);
+                    if (a < bv[j] && row[i] < len) bv[j] = a, bi[j] = row[i];
+                }
+        }
+    return make_uint4(bv[0], (uint32_t)bi[0], bv[1], (uint32_t)bi[1]);
+}
+
+// The same as a function of its own, for the batched kernels, whose registers are
+// short (inlined, its values cost the tile loop 30 spilled registers at d = 100).
+__device__ __attribute__((noinline)) uint4 sad_direct_call(const float *X, int32_t row0,
+                                                           int32_t row1, const float *B, int t,
+                                                           int len, int d, int TR, int first,
+                                                           int step, int quads) {
+    return sad_direct(X, row0, row1, B, t, len, d, TR, first, step, quads);
+}
+
 // One chunk of B against the workgroup's queries.  qw (1, 2 or 4) wavefronts
 // have queries of their own; 4 / qw share a tile's row groups.  seed (may be
 // null): seed[row of X] bounds the query's distance from above.  gthr (may be
 // null): the thresholds of all workgroups, all ones at first.
-template <int W>
+template <int W, bool BATCH>
 __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
                                           const int32_t *__restrict__ rows, int64_t nx,
                                           const float *__restrict__ seed,
@@ -347,7 +437,7 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
         if (__builtin_amdgcn_readfirstlane(evals) > kSadPlainFirst + 2 * qw * t) {
             active = false;
             rest_s[wave] = t;
-            plain_s[(step >> 2) & 1][wave] = 1u;
+            plain_s[(step >> 4) & 1][wave] = 1u;
         }
         // thresholds to LDS and to the other workgroups, and theirs
 #pragma unroll
@@ -440,81 +530,8 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
         for (int j = 0; j < Q; ++j) thr[j] = min(thr[j], thr_s[wave][64 * j + lane]);
     };
 
-    // Every row from t on (the wavefront's groups) for its queries: eight rows and four
-    // coordinates at a time, a lane with queries l and l + 64, rows wave-uniform (scalar
-    // loads).
-    auto direct = [&](int t) {
-        constexpr int NR = 8;
-        const CH_RO float *xr[Q];
-        uint32_t bv[Q];
-        int bi[Q];
-#pragma unroll
-        for (int j = 0; j < Q; ++j) {
-            xr[j] = ro(X) + (int64_t)row_s[wave][64 * j + lane] * d;
-            bv[j] = 0xffffffffu;
-            bi[j] = 0;
-        }
-        // (a tile's groups of four: the wavefronts share them as in the tile loop)
-        int r = 4 * phase;
-#pragma unroll 1
-        for (; t < len; r = 4 * phase, t += TR)
-#pragma unroll 1
-          for (; r < TR && t + r < len; r += 2 * step4) {
-            const CH_RO float *b[NR];
-            int row[NR];
-            float acc[NR][Q] = {};
-#pragma unroll
-            for (int i = 0; i < NR; ++i) {
-                const int g = r + (i >> 2) * step4;
-                row[i] = g < TR ? t + g + (i & 3) : len;
-                b[i] = ro(B) + (b0 + min(row[i], len - 1)) * d;
-            }
-            int k = 0;
-#pragma unroll 1
-            for (; k + 4 <= d; k += 4) {
-                float x[Q][4];
-#pragma unroll
-                for (int j = 0; j < Q; ++j) {
-                    if (quads) {
-                        const float4 u = ld(reinterpret_cast<const CH_RO float4 *>(xr[j] + k));
-                        x[j][0] = u.x, x[j][1] = u.y, x[j][2] = u.z, x[j][3] = u.w;
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) x[j][c] = xr[j][k + c];
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-#pragma unroll
-                    for (int i = 0; i < NR; ++i) {
-                        const float bk = b[i][k + c];
-#pragma unroll
-                        for (int j = 0; j < Q; ++j) acc[i][j] += fabsf(x[j][c] - bk);
-                    }
-            }
-#pragma unroll 1
-            for (; k < d; ++k)
-#pragma unroll
-                for (int i = 0; i < NR; ++i)
-#pragma unroll
-                    for (int j = 0; j < Q; ++j) acc[i][j] += fabsf(xr[j][k] - b[i][k]);
-#pragma unroll
-            for (int i = 0; i < NR; ++i)
-#pragma unroll
-                for (int j = 0; j < Q; ++j) {  // (bits order like the values, NaN last)
-                    const uint32_t a = __float_as_uint(acc[i][j]);
-                    if (a < bv[j] && row[i] < len) bv[j] = a, bi[j] = row[i];
-                }
-        }
-#pragma unroll
-        for (int j = 0; j < Q; ++j)
-            if (bv[j] != 0xffffffffu)
-                atomicMin(&best_s[wave][64 * j + lane],
-                          ((unsigned long long)bv[j] << 32) | (uint32_t)(b0 + bi[j]));
-    };
-
     __syncthreads();
-    // (four steps write one set of words, read after the barrier of the last of them;
+    // (16 steps write one set of words, read after the barrier of the last of them;
     // by the time that it is written again every wavefront has passed that read)
     auto any_plain = [&](int g) {
         const uint4 w = *reinterpret_cast<const uint4 *>(plain_s[g & 1]);
@@ -561,12 +578,24 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
                                                        __HIP_MEMORY_SCOPE_AGENT));
         }
         __syncthreads();
-        if ((step & 3) == 3 && any_plain(step >> 2)) len = min(len, t + 2 * TR);
+        if ((step & 15) == 15 && any_plain(step >> 4)) len = min(len, t + 2 * TR);
     }
     if (qbase >= nx) return;
     const int rest = min(len, __builtin_amdgcn_readfirstlane(rest_s[wave]));
     len = (int)(b1 - b0);
-    if (rest < len) direct(rest);
+    if (rest < len) {
+        const int32_t r0 = row_s[wave][lane], r1 = row_s[wave][64 + lane];
+        const uint4 f = BATCH ? sad_direct_call(X, r0, r1, B + b0 * d, rest, len, d, TR, 4 * phase,
+                                                step4, quads)
+                              : sad_direct(X, r0, r1, B + b0 * d, rest, len, d, TR, 4 * phase,
+                                           step4, quads);
+        if (f.x != 0xffffffffu)
+            atomicMin(&best_s[wave][lane],
+                      ((unsigned long long)f.x << 32) | (uint32_t)(b0 + f.y));
+        if (f.z != 0xffffffffu)
+            atomicMin(&best_s[wave][64 + lane],
+                      ((unsigned long long)f.z << 32) | (uint32_t)(b0 + f.w));
+    }
     sync_lds();
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
@@ -588,7 +617,7 @@ void k_nnmin_sad(const float *__restrict__ X, const int32_t *__restrict__ rows, 
                  const float *__restrict__ seed, const float *__restrict__ B, int64_t nB, int d,
                  const uint32_t *__restrict__ lohi, int64_t chunk, int nchunk, int qw,
                  unsigned long long *best, uint32_t *gthr, DevParams *p) {
-    nnmin_sad<W>(X, rows, nx, seed, B, nB, d, lohi, chunk, nchunk, qw, best, gthr, p, grid_blk());
+    nnmin_sad<W, false>(X, rows, nx, seed, B, nB, d, lohi, chunk, nchunk, qw, best, gthr, p, grid_blk());
 }
 
 static int sad_resident_wgs(int d) {
@@ -675,7 +704,8 @@ template <int W>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sad_waves<W>())))
 void kb_nn_sad(const Batch *__restrict__ bt) {
     batch_loop(bt, kBsNN, [&](const Job &J, Blk b) {
-        nnmin_sad<W>(glb(J.A), glb(J.idx), J.T, glb(J.D), glb(J.B), J.nB, J.d, glb(J.lohi),
+        if (J.nn_vector) return;
+        nnmin_sad<W, true>(glb(J.A), glb(J.idx), J.T, glb(J.D), glb(J.B), J.nB, J.d, glb(J.lohi),
                      J.nn_chunk, J.nn_nchunk, J.nn_qw, glb(J.best), glb(J.gthr), glb(J.p), b);
     });
 }

@@ -96,3 +96,26 @@ def test_l1_draws(ch, orc, d, n_b, T):
     torch.cuda.synchronize()
     idx = out["sample_idx"].cpu().numpy()[:100]
     same(out["sample_min"][:100], out["sample_nn"][:100], orc.nn_f32(A, B, L1, rows=idx))
+
+
+# batches: vector form and the other by each batch's draws and sizes
+@pytest.mark.parametrize("metric,d", [(L2, 3), (L1, 16), (L1, 32), (L1, 64), (L1, 128), (L1, 20),
+                                      (L2, 20), (L2, 128), (L2, 7)])
+@pytest.mark.parametrize("T", [40, 310, 1100])
+@pytest.mark.parametrize("sizes", [(900, 1500, 33), (700, 9000, 60000, 100)])
+def test_batches(ch, metric, d, T, sizes):
+    """Every symmetric estimate of a retrieval is that of its own call, bit for bit,
+    far points among them."""
+    rng = np.random.default_rng(d + T)
+    A = rng.standard_normal((800, d)).astype(np.float32)
+    clouds = [rng.standard_normal((n, d)).astype(np.float32) for n in sizes]
+    clouds[-1][5] *= 1e9
+    print(f"[case] metric={metric} d={d} T={T} sizes={sizes}", flush=True)
+    Bs = [dev(c) for c in clouds]
+    est, top, vals = ch.chamfer_retrieve(dev(A), Bs, metric, 0.2, T, 3, 1, n_scales=12)
+    ref = [ch.chamfer_estimate_symmetric(dev(A), B, metric, 0.2, T, 3, n_scales=12)[0].item()
+           for B in Bs]
+    torch.cuda.synchronize()
+    assert est.cpu().tolist() == ref
+    exact = [ch.chamfer_exact_symmetric(dev(A), B, metric)[0].item() for B in Bs]
+    assert vals[0] == exact[top[0]] and top[0] == int(np.argmin(ref))
