@@ -201,13 +201,13 @@ int make_plan(Plan &pl, int64_t nA, int64_t nB, int32_t d, int32_t metric, doubl
     pl.off_best = take((size_t)nrow * sizeof(uint64_t));
     // thresholds of the exact pass: the draws' live in the hash tables' region
     // (done with by then), in copies where they fit, and there are none where not
-    // even one does; the passes over all points keep one copy right after best, so
-    // that one fill resets both
+    // even one does; the passes over all points keep theirs right after best, so that
+    // one fill resets both, in copies for few points (half_copies)
     const size_t room = h ? table_bytes(pl.L, lc, pl.window) : 0;
     const size_t gb = (size_t)(estimating ? pl.T : nA) * sizeof(uint32_t);
     const bool matrix = !lowp_supported(d, metric, o.precision) && half_supported(d, metric);
     if (!matrix && !sad_supported(d, metric)) pl.thr_copies = 0;
-    else if (!estimating) pl.thr_copies = 1;
+    else if (!estimating) pl.thr_copies = matrix && nA <= 1024 ? 8 : 1;
     else if (matrix && half_copies(pl.T, nB) * gb <= room) pl.thr_copies = half_copies(pl.T, nB);
     else pl.thr_copies = gb <= room ? 1 : 0;
     pl.off_gthr = estimating ? pl.off_tables : take(pl.thr_copies * gb);
@@ -286,7 +286,7 @@ int hash_prologue(const Plan &pl, const float *A, const float *B, uint64_t seed,
 // 64-bit words of best and the thresholds after it (entry points that lay
 // them out one after the other).
 int64_t reset_words(const Plan &pl) {
-    const size_t end = pl.thr_copies ? pl.off_gthr + align_up(pl.nA * sizeof(uint32_t))
+    const size_t end = pl.thr_copies ? pl.off_gthr + align_up(pl.thr_copies * pl.nA * sizeof(uint32_t))
                                      : pl.off_best + (size_t)pl.nA * sizeof(uint64_t);
     return (int64_t)((end - pl.off_best) / sizeof(uint64_t));
 }

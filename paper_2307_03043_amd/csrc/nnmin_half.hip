@@ -34,6 +34,7 @@
 // two-term split: the pass is bound by the matrix cores, and the rows left to
 // evaluate are few (about one in 10^4) because a threshold is carried along
 // and seeded with the CrudeNN distance of a draw.
+#include <algorithm>
 #include <cfloat>
 #include <climits>
 #include <cmath>
@@ -1059,20 +1060,26 @@ int64_t half_target_wgs(int d) {
 // calls in us: 300 draws of 3000 x 150000 x 3 (7e8 products) 211 and 206, exact
 // 2500 x 20001 x 16 (1.6e9) 67 and 60, x 64 (3.2e9) 81 and 73; 1600 draws of
 // 40000 x 50000 x 64 (5e9) 183 and 185, 1800 of 2 10^5 x 3 (6e9) 336 and 350, exact
-// 30000^2 x 128 (1e11) 397 and 431.
+// 30000^2 x 128 (1e11) 397 and 431.  Few rows of few slots are over before the larger
+// workgroup has paid for its start: 10^6 x 1000 x 16 537 and 512.
 static bool half_small(int64_t nx, int64_t nB, int d) {
-    return (double)nx * (double)nB * half_slots(d) <= 4e9;
+    return (double)nx * (double)nB * half_slots(d) <= 4e9 || (nB <= 1024 && half_slots(d) <= 32);
 }
 
 // target 0: as many chunks as give the least number of rounds of resident
 // workgroups times the rows of a round (a workgroup starts and ends in the time
 // of about 128 rows).  1600 draws are 7 query blocks: with 80 chunks, the multiple
 // of 8 above 512 / 7, a second round of 48 workgroups followed the first.
-static NNGeom half_geom(int64_t nx, int64_t nB, int d, bool small, int64_t target) {
+// cold: the queries start without a distance.
+static NNGeom half_geom(int64_t nx, int64_t nB, int d, bool small, bool cold, int64_t target) {
     const int64_t wq = 64 * half_nb(half_slots(d), small);
     const int64_t nq = (nx + wq - 1) / wq;
     const int64_t slots = half_target_wgs(d);
-    const int64_t cmin = (nB + 65535) / 65536, cmax = (nB + 63) / 64;
+    // few cold queries: every workgroup evaluates its first rows and writes to the same
+    // few (100 x 20000 x 20 in 320 chunks 71 us, in 128 43; 100 x 400000 in 512 219 and 122)
+    const int64_t cmin = (nB + 65535) / 65536,
+                  cmax = cold && nq <= 4 ? std::min((nB + 155) / 156, std::max<int64_t>(128, cmin))
+                                         : (nB + 63) / 64;
     auto whole = [&](int64_t nc) {  // one chunk's workgroups share an XCD
         if (nc < cmin) nc = cmin;
         if (nc > cmax) nc = cmax;
@@ -1098,18 +1105,18 @@ static NNGeom half_geom(int64_t nx, int64_t nB, int d, bool small, int64_t targe
 }
 
 NNGeom half_geom(int64_t nx, int64_t nB, int d, int64_t target) {
-    return half_geom(nx, nB, d, false, target);
+    return half_geom(nx, nB, d, false, false, target);
 }
 // Jobs of a batch: few draws each, so a workgroup takes 128 of them where the table is
 // in memory (whole retrievals in us with 256 and 128: 48 pairs of 8000 x 128, 1600
 // draws 1972 and 1696; 256 of 1000 x 20, 400 draws 896 and 763).
 __host__ __device__ constexpr bool half_batch_small(bool raw) { return !raw; }
 NNGeom half_batch_geom(int64_t nx, int64_t nB, int d, int64_t target) {
-    return half_geom(nx, nB, d, half_batch_small(!half_tabled(d)), target);
+    return half_geom(nx, nB, d, half_batch_small(!half_tabled(d)), false, target);
 }
 
 int64_t half_launch_queries(int64_t nx, int64_t nB, int d) {
-    while (nx > 1 && half_geom(nx, nB, d, half_small(nx, nB, d), 0).blocks > kMaxLaunchWGs)
+    while (nx > 1 && half_geom(nx, nB, d, half_small(nx, nB, d), false, 0).blocks > kMaxLaunchWGs)
         nx = (nx + 1) / 2;
     return nx;
 }
@@ -1134,7 +1141,7 @@ hipError_t launch_nnmin_half(const float *X, const int32_t *rows, int64_t nx, co
         return hipSuccess;
     }
     const bool small = half_small(nx, nB, d);
-    const NNGeom g = half_geom(nx, nB, d, small, 0);
+    const NNGeom g = half_geom(nx, nB, d, small, seed == nullptr, 0);
 #define CH_HALF_NB(DP, RAW, NB)                                                              \
     k_nnmin_half<DP, RAW, NB><<<(unsigned)g.blocks, 256, 0, st>>>(                           \
         X, rows, nx, Xs, stat, seed, B, Bs, nB, d, nbh, lohi, g.chunk, g.nchunk, best, gthr, \

@@ -25,6 +25,7 @@
 // points, 2000 draws: 5.04 ms in the VALU form, 1.43 here (the differences alone 0.93);
 // exact 30000^2 x 100, which the VALU form takes in its any-dimension kernel: 33.4
 // and 1.4 ms.
+#include <algorithm>
 #include <cfloat>
 #include <climits>
 #include <cmath>
@@ -43,16 +44,19 @@ bool sad_supported(int d, int metric) { return metric == CHAMFER_L1 && d > kSadM
 // draws of 10^5 rows 270 and 281, 2000 of 10^5 612 and 604.  d = 32, 10^5 x 2000 253 and
 // 280, 2500 x 100000 301 and 237; 450 draws of 2 10^5 379 and 442, 1600 of 50000 234 and
 // 211.  d = 64, 10^5 x 1000 261 and 292, 10^6 x 1000 2116 and 1879, 2500 x 20001 160 and
-// 134; 400 draws of 50000 217 and 241.  d = 128, 300 draws of 4096 154 and 164, 400 of
-// 50000 372 and 318.
+// 134, 1000 x 40000 126 and 140, 300 x 400000 509 and 336; 400 draws of 50000 217 and
+// 241.  d = 128, 300 draws of 4096 154 and 164, 400 of 50000 372 and 318.  Other
+// dimensions up to 16: d = 12, 500 x 10000 64 and 76, 3000^2 70 and 67.
 bool sad_pays(int64_t nx, int64_t nB, int d, bool seeded) {
     const double pairs = (double)nx * (double)nB;
     switch (d) {
         case 16: return seeded ? nB >= 65536 && pairs >= 2e8 : nB >= 16384 && pairs >= 5e8;
         case 32: return pairs >= 2.5e8 || (seeded && nx >= 1024 && pairs >= 7e7);
-        case 64: return pairs >= 3e7 && (seeded || nB >= 2048 || pairs >= 5e8);
+        case 64:
+            return pairs >= 3e7 && (seeded || ((nB >= 2048 || pairs >= 5e8) &&
+                                               (nx >= 2048 || pairs >= 1e8)));
         case 128: return pairs >= 1.6e7;
-        default: return true;
+        default: return d > 16 || seeded || pairs > 6e6;
     }
 }
 
@@ -628,10 +632,16 @@ static int sad_resident_wgs(int d) {
 // Wavefronts with queries of their own (qw) and the split of B.  target 0: as many
 // chunks as give the least number of rounds of resident workgroups times the rows
 // of a round (a workgroup starts and ends in the time of about 128 rows); qw is
-// lowered where too few workgroups would be left.
-NNGeom sad_geom(int64_t nx, int64_t nB, int d, int64_t target, int32_t &qw) {
+// lowered where too few workgroups would be left.  cold: the queries start without a
+// distance.  Every workgroup of few such queries evaluates its first rows and writes
+// to the same few (100 x 100000 x 20 in 768 chunks 385 us, in 256 130; 500 x 100000
+// x 20 188 and 145, x 100 214 and 300).
+static NNGeom sad_geom(int64_t nx, int64_t nB, int d, bool cold, int64_t target, int32_t &qw) {
     const int64_t slots = sad_resident_wgs(d);
-    const int64_t cmin = (nB + 65535) / 65536, cmax = (nB + 63) / 64;
+    const bool few = cold && nx <= (sad_words(d) <= 8 ? 512 : 256);
+    const int64_t cmin = (nB + 65535) / 65536,
+                  cmax = few ? std::min((nB + 155) / 156, std::max<int64_t>(256, cmin))
+                             : (nB + 63) / 64;
     NNGeom g;
     for (qw = nx > 256 ? 4 : nx > 128 ? 2 : 1;; qw /= 2) {
         const int64_t nq = (nx + 128 * qw - 1) / (128 * qw);
@@ -656,9 +666,13 @@ NNGeom sad_geom(int64_t nx, int64_t nB, int d, int64_t target, int32_t &qw) {
     }
 }
 
+NNGeom sad_geom(int64_t nx, int64_t nB, int d, int64_t target, int32_t &qw) {
+    return sad_geom(nx, nB, d, false, target, qw);
+}
+
 int64_t sad_launch_queries(int64_t nx, int64_t nB, int d) {
     int32_t qw;
-    while (nx > 1 && sad_geom(nx, nB, d, 0, qw).blocks > kMaxLaunchWGs) nx = (nx + 1) / 2;
+    while (nx > 1 && sad_geom(nx, nB, d, false, 0, qw).blocks > kMaxLaunchWGs) nx = (nx + 1) / 2;
     return nx;
 }
 
@@ -680,7 +694,7 @@ hipError_t launch_nnmin_sad(const float *X, const int32_t *rows, int64_t nx, con
         return hipSuccess;
     }
     int32_t qw;
-    const NNGeom g = sad_geom(nx, nB, d, 0, qw);
+    const NNGeom g = sad_geom(nx, nB, d, seed == nullptr, 0, qw);
 #define CH_SAD(W)                                                                           \
     k_nnmin_sad<W><<<(unsigned)g.blocks, 256, 0, st>>>(X, rows, nx, seed, B, nB, d, lohi,   \
                                                        g.chunk, g.nchunk, qw, best, gthr, p)

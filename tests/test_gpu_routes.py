@@ -87,6 +87,20 @@ def test_l1(ch, orc, d, n_a, n_b):
     check(ch, orc, n_a, n_b, d, L1, 100)
 
 
+@pytest.mark.parametrize("metric,d", [(L2, 3), (L2, 10), (L2, 20), (L2, 128), (L1, 20), (L1, 64),
+                                      (L1, 100)])
+@pytest.mark.parametrize("n_a,n_b", [(1, 20000), (256, 19969), (257, 40001), (512, 39936),
+                                     (513, 20000), (1024, 20001), (1025, 20001), (2048, 50001)])
+def test_few_queries(ch, orc, metric, d, n_a, n_b):
+    check(ch, orc, n_a, n_b, d, metric, 40)
+
+
+@pytest.mark.parametrize("metric,d,n_b", [(L2, 20, 1024), (L2, 32, 1025), (L2, 8, 1024),
+                                          (L1, 20, 500), (L1, 12, 500)])
+def test_few_rows(ch, orc, metric, d, n_b):
+    check(ch, orc, 150001, n_b, d, metric, 100)
+
+
 @pytest.mark.parametrize("d,n_b,T", [(16, 65535, 3200), (16, 65536, 3200), (32, 69000, 1023),
                                      (32, 69000, 1024), (64, 2000, 15001), (64, 2000, 14999)])
 def test_l1_draws(ch, orc, d, n_b, T):
