@@ -34,6 +34,8 @@ __device__ __forceinline__ void init_params(DevParams *p, uint32_t *lohi, int d,
         p->fallbacks = 0;
         p->he = 0;
         p->half_box = 0.0f;
+        p->sad_inv = 0.0f;
+        p->sad_in = 0;
     }
     for (int64_t k = t; k < kMaxRepl; k += b.n * blockDim.x) {
         p->max_d_rep[k * kReplStride] = 0u;

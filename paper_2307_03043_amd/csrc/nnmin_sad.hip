@@ -295,7 +295,8 @@ __device__ __forceinline__ void nnmin_sad(const float *__restrict__ X,
         if (mine) {
             tile_s[slot][fr * UPR + fu] = w;
             if (fu == 0) {
-                // (0 when a coordinate is not a number: the row is always evaluated)
+                // (0, the lowest, when a coordinate is not a number: such a row answers
+                // no query, and as sad_inv is 0 then it rules none out either)
                 const float m = ceilf(sum * 1.0001f + eps);
                 base_s[slot][fr] = m < (float)E ? E - (uint32_t)m : 0u;
             }
