@@ -290,34 +290,43 @@ static hipError_t go_fixed(const float *X, const int32_t *rows, int64_t nx, cons
 }
 
 template <int METRIC>
-static hipError_t go_metric(const float *X, const int32_t *rows, int64_t nx, const float *B,
-                            int64_t nB, int d, unsigned long long *best, const DevParams *p,
+static hipError_t go_points(const float *X, const int32_t *rows, int64_t nx, const float *B,
+                            int64_t nB, unsigned long long *best, const DevParams *p,
                             hipStream_t st) {
-    switch (d) {
-        case 3:
-            switch (valu_qpl(nx, nB, 3)) {
-                case 1: return go_fixed<METRIC, 3, 1>(X, rows, nx, B, nB, best, p, st);
-                case 2: return go_fixed<METRIC, 3, 2>(X, rows, nx, B, nB, best, p, st);
-                default: return go_fixed<METRIC, 3, 8>(X, rows, nx, B, nB, best, p, st);
-            }
-        case 16: return go_fixed<METRIC, 16, 4>(X, rows, nx, B, nB, best, p, st);
-        case 32: return go_fixed<METRIC, 32, 2>(X, rows, nx, B, nB, best, p, st);
-        case 64: return go_fixed<METRIC, 64, 2>(X, rows, nx, B, nB, best, p, st);
-        case 128: return go_fixed<METRIC, 128, 1>(X, rows, nx, B, nB, best, p, st);
-        default: break;
+    switch (valu_qpl(nx, nB, 3)) {
+        case 1: return go_fixed<METRIC, 3, 1>(X, rows, nx, B, nB, best, p, st);
+        case 2: return go_fixed<METRIC, 3, 2>(X, rows, nx, B, nB, best, p, st);
+        default: return go_fixed<METRIC, 3, 8>(X, rows, nx, B, nB, best, p, st);
     }
+}
+
+template <int METRIC>
+static hipError_t go_any(const float *X, const int32_t *rows, int64_t nx, const float *B,
+                         int64_t nB, int d, unsigned long long *best, const DevParams *p,
+                         hipStream_t st) {
     const NNGeom g = valu_geom(nx, nB, d);
     k_nnmin_any<METRIC, 32, 8><<<(unsigned)g.blocks, 256, 0, st>>>(X, rows, nx, B, nB, d, g.chunk,
                                                                     g.nchunk, best, p);
     return hipGetLastError();
 }
 
+// l2 above three dimensions comes here only where the matrix cores do not go.
 hipError_t launch_nnmin(const float *X, const int32_t *rows, int64_t nx, const float *B,
                         int64_t nB, int d, int metric, unsigned long long *best, DevParams *p,
                         hipStream_t st) {
+    constexpr int L1 = CHAMFER_L1, L2 = CHAMFER_L2;
     if (nx <= 0) return hipSuccess;
-    if (metric == CHAMFER_L1) return go_metric<CHAMFER_L1>(X, rows, nx, B, nB, d, best, p, st);
-    return go_metric<CHAMFER_L2>(X, rows, nx, B, nB, d, best, p, st);
+    if (metric == L2)
+        return d == 3 ? go_points<L2>(X, rows, nx, B, nB, best, p, st)
+                      : go_any<L2>(X, rows, nx, B, nB, d, best, p, st);
+    switch (d) {
+        case 3: return go_points<L1>(X, rows, nx, B, nB, best, p, st);
+        case 16: return go_fixed<L1, 16, 4>(X, rows, nx, B, nB, best, p, st);
+        case 32: return go_fixed<L1, 32, 2>(X, rows, nx, B, nB, best, p, st);
+        case 64: return go_fixed<L1, 64, 2>(X, rows, nx, B, nB, best, p, st);
+        case 128: return go_fixed<L1, 128, 1>(X, rows, nx, B, nB, best, p, st);
+        default: return go_any<L1>(X, rows, nx, B, nB, d, best, p, st);
+    }
 }
 
 __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long v) {
@@ -469,15 +478,20 @@ bool batch_vector(int64_t T, int64_t nB, int d, int metric) {
     }
 }
 
-template <int METRIC>
-static hipError_t batch_valu(const Batch *bt, int d, hipStream_t st) {
+static hipError_t batch_valu(const Batch *bt, int d, int metric, hipStream_t st) {
+    constexpr int L1 = CHAMFER_L1, L2 = CHAMFER_L2;
+    if (metric == L2) {
+        if (d == 3) kb_nn_points<L2><<<kGridNNValu, 256, 0, st>>>(bt);
+        else kb_nn_any<L2><<<kGridNNValu, 256, 0, st>>>(bt);
+        return hipGetLastError();
+    }
     switch (d) {
-        case 3: kb_nn_points<METRIC><<<kGridNNValu, 256, 0, st>>>(bt); break;
-        case 16: kb_nn_fixed<METRIC, 16, 4><<<kGridNNValu, 256, 0, st>>>(bt); break;
-        case 32: kb_nn_fixed<METRIC, 32, 2><<<kGridNNValu, 256, 0, st>>>(bt); break;
-        case 64: kb_nn_fixed<METRIC, 64, 2><<<kGridNNValu, 256, 0, st>>>(bt); break;
-        case 128: kb_nn_fixed<METRIC, 128, 1><<<kGridNNValu, 256, 0, st>>>(bt); break;
-        default: kb_nn_any<METRIC><<<kGridNNValu, 256, 0, st>>>(bt); break;
+        case 3: kb_nn_points<L1><<<kGridNNValu, 256, 0, st>>>(bt); break;
+        case 16: kb_nn_fixed<L1, 16, 4><<<kGridNNValu, 256, 0, st>>>(bt); break;
+        case 32: kb_nn_fixed<L1, 32, 2><<<kGridNNValu, 256, 0, st>>>(bt); break;
+        case 64: kb_nn_fixed<L1, 64, 2><<<kGridNNValu, 256, 0, st>>>(bt); break;
+        case 128: kb_nn_fixed<L1, 128, 1><<<kGridNNValu, 256, 0, st>>>(bt); break;
+        default: kb_nn_any<L1><<<kGridNNValu, 256, 0, st>>>(bt); break;
     }
     return hipGetLastError();
 }
@@ -489,8 +503,7 @@ hipError_t launch_batch_nn(const Batch *bt, int d, int metric, int precision, hi
                                                   : launch_batch_sad(bt, d, st);
         if (e != hipSuccess || !batch_both(d, metric)) return e;
     }
-    if (metric == CHAMFER_L1) return batch_valu<CHAMFER_L1>(bt, d, st);
-    return batch_valu<CHAMFER_L2>(bt, d, st);
+    return batch_valu(bt, d, metric, st);
 }
 
 }  // namespace chamfer
