@@ -122,7 +122,10 @@ typedef struct chamfer_aux {
      * d <= 10 one matrix-core kernel, with 12 <= d <= 256 the FP16 table of
      * the draws and that kernel (B's table is written in stage 1->2 by the
      * kernel that hashes B, or in stage 4->5 for the uniform-sampling
-     * baseline); otherwise one vector-ALU kernel. */
+     * baseline); for l1 with 9 <= d <= 256 one kernel of byte differences or
+     * of the vector ALU, by the sizes; otherwise, and for the
+     * uniform-sampling baseline in three dimensions where it is faster, one
+     * vector-ALU kernel. */
     void **stage_events;
 } chamfer_aux;
 
@@ -459,7 +462,7 @@ const char *chamfer_strerror(int status);
  * of terms = 3 (hh, mh, hm) or 4 products per coordinate is within E of
  * |b|^2 - 2 x.b, assuming that each product is added to a float32 accumulator
  * with one rounding to nearest.  Returns -1 for d outside 1..256 or other
- * terms. */
+ * terms.  The formula only: no pass of the library forms such scores. */
 double chamfer_split_score_bound(int32_t d, int32_t terms, float xn2, float b2max);
 /* The bound of the l2 exact pass (chamfer_exact, chamfer_nn_min and
  * chamfer_estimate for l2 with d <= 10 or 12 <= d <= 256, FP32 precision): its

@@ -548,7 +548,8 @@ hipError_t launch_hash(int mode, const float *X, int64_t n, const float *Bpts, i
 size_t table_bytes(int L, int log2cap, int W);
 // The partitioned build of the W = 1 tables (no global atomics): keys of B
 // from launch_hash mode 5 into w.keys, then launch_part_build.  Usable when
-// part_build_ok(log2cap) (at most 4096 regions of 4096 slots per scale).
+// part_build_ok(log2cap) (at most 1024 regions of 2^11 slots per scale;
+// up to 20480 keys regions have up to 2^13).
 struct PartWork {
     uint64_t *keys;    // [L][nB] (the empty key for a dropped duplicate)
     uint32_t *offs;    // [L][blocks][regions]
