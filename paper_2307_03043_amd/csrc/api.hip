@@ -138,10 +138,11 @@ bool boxed(int64_t nx, int64_t nB, int d, int metric, bool seeded) {
 // Validate and lay out the workspace.  estimating: the entry point draws T
 // points (needs eps, the weight, prefix and draw regions) and, with
 // importance sampling, runs CrudeNN (the table regions); otherwise only the
-// regions of the nearest-neighbour pass are laid out, so its total never
-// exceeds the estimating total for the same sizes.
+// regions of the nearest-neighbour pass are laid out.  lean: with one copy of its
+// thresholds; that total never exceeds the estimating total for the same sizes, nor
+// that of larger ones.
 int make_plan(Plan &pl, int64_t nA, int64_t nB, int32_t d, int32_t metric, double eps,
-              int64_t T, const chamfer_opts *opts, bool estimating) {
+              int64_t T, const chamfer_opts *opts, bool estimating, bool lean = false) {
     const bool need_eps = estimating;
     std::memset(&pl, 0, sizeof(pl));
     if (d < 1 || (metric != CHAMFER_L1 && metric != CHAMFER_L2)) return CHAMFER_EINVAL;
@@ -207,7 +208,7 @@ int make_plan(Plan &pl, int64_t nA, int64_t nB, int32_t d, int32_t metric, doubl
     const size_t gb = (size_t)(estimating ? pl.T : nA) * sizeof(uint32_t);
     const bool matrix = !lowp_supported(d, metric, o.precision) && half_supported(d, metric);
     if (!matrix && !sad_supported(d, metric)) pl.thr_copies = 0;
-    else if (!estimating) pl.thr_copies = matrix && nA <= 1024 ? 8 : 1;
+    else if (!estimating) pl.thr_copies = matrix && nA <= 1024 && !lean ? 8 : 1;
     else if (matrix && half_copies(pl.T, nB) * gb <= room) pl.thr_copies = half_copies(pl.T, nB);
     else pl.thr_copies = gb <= room ? 1 : 0;
     pl.off_gthr = estimating ? pl.off_tables : take(pl.thr_copies * gb);
@@ -226,6 +227,14 @@ int make_plan(Plan &pl, int64_t nA, int64_t nB, int32_t d, int32_t metric, doubl
     pl.off_lpf = take(lp ? 2 * ((size_t)nB + (size_t)nrow) * sizeof(float) : 0);
     pl.total = off;
     return CHAMFER_OK;
+}
+
+// The plan of the exact entry points, lean where the workspace is only enough for that.
+int exact_plan(Plan &pl, int64_t nA, int64_t nB, int32_t d, int32_t metric,
+               const chamfer_opts *opts, size_t ws_bytes) {
+    const int rc = make_plan(pl, nA, nB, d, metric, 0.5, 0, opts, false);
+    if (rc || ws_bytes >= pl.total) return rc;
+    return make_plan(pl, nA, nB, d, metric, 0.5, 0, opts, false, true);
 }
 
 template <class T>
@@ -627,7 +636,7 @@ int chamfer_exact(const float *A, const float *B, int64_t n_A, int64_t n_B, int3
                   int32_t metric, double *ch_out, float *rowmin_out, int32_t *rownn_out,
                   const chamfer_opts *opts, void *ws, size_t ws_bytes, void *stream) {
     Plan pl;
-    int rc = make_plan(pl, n_A, n_B, d, metric, 0.5, 0, opts, false);
+    int rc = exact_plan(pl, n_A, n_B, d, metric, opts, ws_bytes);
     if (rc) return rc;
     if (ch_out == nullptr || (A == nullptr && n_A > 0) || B == nullptr) return CHAMFER_EINVAL;
     if ((rc = check_ws(pl, ws, ws_bytes))) return rc;
@@ -655,7 +664,7 @@ int chamfer_nn_min(const float *X, const int32_t *rows, int64_t n_x, const float
                    int64_t n_B, int32_t d, int32_t metric, float *min_out, int32_t *arg_out,
                    const chamfer_opts *opts, void *ws, size_t ws_bytes, void *stream) {
     Plan pl;
-    int rc = make_plan(pl, n_x, n_B, d, metric, 0.5, 0, opts, false);
+    int rc = exact_plan(pl, n_x, n_B, d, metric, opts, ws_bytes);
     if (rc) return rc;
     if ((X == nullptr && n_x > 0) || B == nullptr) return CHAMFER_EINVAL;
     if ((rc = check_ws(pl, ws, ws_bytes))) return rc;
@@ -829,8 +838,8 @@ int chamfer_exact_symmetric(const float *A, const float *B, int64_t n_A, int64_t
                             size_t ws_bytes, void *stream) {
     if (n_A < 1 || n_B < 1 || ch_out == nullptr) return CHAMFER_EINVAL;
     Plan ab, ba;
-    int rc = make_plan(ab, n_A, n_B, d, metric, 0.5, 0, opts, false);
-    if (rc || (rc = make_plan(ba, n_B, n_A, d, metric, 0.5, 0, opts, false))) return rc;
+    int rc = exact_plan(ab, n_A, n_B, d, metric, opts, ws_bytes);
+    if (rc || (rc = exact_plan(ba, n_B, n_A, d, metric, opts, ws_bytes))) return rc;
     if (ws == nullptr || ws_bytes < ab.total || ws_bytes < ba.total) return CHAMFER_EWORKSPACE;
     rc = chamfer_exact(A, B, n_A, n_B, d, metric, ch_out + 1, nullptr, nullptr, opts, ws, ws_bytes,
                        stream);

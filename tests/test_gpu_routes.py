@@ -95,6 +95,33 @@ def test_few_queries(ch, orc, metric, d, n_a, n_b):
     check(ch, orc, n_a, n_b, d, metric, 40)
 
 
+@pytest.mark.parametrize("d,n_b", [(3, 1), (3, 20000), (64, 1), (64, 20000)])
+@pytest.mark.parametrize("n_a", [63, 1024])
+def test_smallest_workspace(ch, orc, d, n_b, n_a):
+    """A workspace sized for any entry point with the same options is enough for the
+    exact ones, whatever they lay out with a larger one."""
+    A, B = workloads.clusters_l2(seed=n_a + d, n=n_a, d=d, k=20, n_b=max(n_b, 20))
+    A, B = dev(A), dev(B[:n_b])
+    print(f"[case] n_a={n_a} n_b={n_b} d={d}", flush=True)
+    ref = orc.nn_f32(A.cpu().numpy(), B.cpu().numpy(), L2)
+    size = ch.chamfer_workspace_bytes(n_a, n_b, d, L2, 0.1, 1, sampling=ch.UNIFORM)
+    assert size < ch.chamfer_workspace_bytes(n_a, n_b, d, L2, 0.0, 0)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+    out = torch.empty(3, dtype=torch.float64, device="cuda:0")
+    mn = torch.empty(n_a, dtype=torch.float32, device="cuda:0")
+    nn = torch.empty(n_a, dtype=torch.int32, device="cuda:0")
+    st = torch.cuda.current_stream().cuda_stream
+    lib = ch.lib()
+    rc = lib.chamfer_exact(A.data_ptr(), B.data_ptr(), n_a, n_b, d, L2, out.data_ptr(),
+                           mn.data_ptr(), nn.data_ptr(), None, ws.data_ptr(), size, st)
+    assert rc == 0
+    same(mn, nn, ref)
+    rc = lib.chamfer_nn_min(A.data_ptr(), None, n_a, B.data_ptr(), n_b, d, L2, mn.data_ptr(),
+                            nn.data_ptr(), None, ws.data_ptr(), size, st)
+    assert rc == 0
+    same(mn, nn, ref)
+
+
 @pytest.mark.parametrize("metric,d,n_b", [(L2, 20, 1024), (L2, 32, 1025), (L2, 8, 1024),
                                           (L1, 20, 500), (L1, 12, 500)])
 def test_few_rows(ch, orc, metric, d, n_b):
